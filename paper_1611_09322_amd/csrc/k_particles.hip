@@ -1374,63 +1374,113 @@ __global__ void k_lz_update_pc(const typename vec4<T>::type *__restrict__ t,
   if (threadIdx.x == 0) partials[blockIdx.x] = v;
 }
 
+// Value of v in lane i (wave-uniform i) as a scalar.
+__device__ __forceinline__ float lane_value(float v, int i) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i));
+}
+__device__ __forceinline__ double lane_value(double v, int i) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), i),
+                          __builtin_amdgcn_readlane(__double2loint(v), i));
+}
+
+// r = sqrt(x) and ri = 1 / sqrt(x) for normal x > 0: the hardware estimate
+// of 1 / sqrt(x), refined by the coupled Newton iteration g -> sqrt(x),
+// h -> 1 / (2 sqrt(x)) to within about an ulp.
+__device__ __forceinline__ void sqrt_pair(float x, float &r, float &ri) {
+  const float y = __builtin_amdgcn_rsqf(x);
+  float g = x * y, h = 0.5f * y;
+  const float d = fmaf(-h, g, 0.5f);
+  r = fmaf(g, d, g);
+  ri = 2.0f * fmaf(h, d, h);
+}
+__device__ __forceinline__ void sqrt_pair(double x, double &r, double &ri) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const double d = fma(-h, g, 0.5);
+    g = fma(g, d, g);
+    h = fma(h, d, h);
+  }
+  r = g;
+  ri = 2.0 * h;
+}
+
 // s = T^{1/2} e_1 for the n x n tridiagonal T (diag d, off-diagonal e with
 // e[i] coupling i, i+1), by implicit QL with Wilkinson-type shifts.  One
 // wavefront: lane j holds d[j], e[j]; lane k owns row k of the eigenvector
 // matrix Q (stored column-major in LDS).  Returns s_k in lane k.
+// A serial chain of rotations bounds it, so each rotation is kept short:
+// uniform values are read from their lane as scalars instead of through LDS
+// permutes, one reciprocal square root gives r, 1/r and with them the sine
+// and cosine (no hypot, no divisions), the deflation test looks at every
+// lane at once, and the updated column of Q stays in a register for the
+// next rotation.  T is scaled by a power of two to diagonal entries of order
+// 1, which keeps f^2 + g^2 in range.
 template <typename A>
 __device__ A tridiag_sqrt_e1(int n, A d, A e, A *Q, int &ok) {
   const int lane = threadIdx.x & 63;
-  const A eps = sizeof(A) == 8 ? A(2.2e-16) : A(1.2e-7);
+  const A eps = sizeof(A) == 8 ? A(2.2e-16) : A(1.2e-7), tiny = sizeof(A) == 8 ? A(1e-290) : A(1e-35);
   for (int j = 0; j < n; ++j) Q[j * 64 + lane] = (lane == j) ? A(1) : A(0);
-  auto gd = [&](int i) { return __shfl(d, i, 64); };
-  auto ge = [&](int i) { return __shfl(e, i, 64); };
   ok = 1;
+  const A d0 = lane_value(d, 0);
+  int ex = d0 > A(0) && isfinite(d0) ? ilogb(d0) : 0;
+  ex -= ex & 1;  // even: the square root's scale is a power of two too
+  d = ldexp(d, -ex);
+  e = ldexp(e, -ex);
   for (int l = 0; l < n; ++l) {
     int iter = 0;
     while (true) {
-      int mm;
-      for (mm = l; mm < n - 1; ++mm) {
-        const A dd = fabs(gd(mm)) + fabs(gd(mm + 1));
-        if (fabs(ge(mm)) <= eps * dd) break;
-      }
+      // the first negligible off-diagonal entry at or after l
+      const A ad = fabs(d), an = __shfl_down(ad, 1, 64);
+      const bool cut = lane >= n - 1 || fabs(e) <= eps * (ad + an);
+      const unsigned long long cuts = __ballot(cut) >> l;
+      const int mm = l + (cuts ? __ffsll((long long)cuts) - 1 : 0);
       if (mm == l) break;
       if (++iter > 60) {
         ok = 0;
         break;
       }
-      A g = (gd(l + 1) - gd(l)) / (A(2) * ge(l));
-      A r = hypot(g, A(1));
-      g = gd(mm) - gd(l) + ge(l) / (g + copysign(r, g));
+      const A dl = lane_value(d, l), el = lane_value(e, l);
+      A g = (lane_value(d, l + 1) - dl) / (A(2) * el);
+      A r = sqrt(g * g + A(1));
+      g = lane_value(d, mm) - dl + el / (g + copysign(r, g));
       A s = 1, c = 1, p = 0;
       bool early = false;
+      A q1 = Q[mm * 64 + lane], dn = lane_value(d, mm);
       for (int i = mm - 1; i >= l; --i) {
-        const A f = s * ge(i), b = c * ge(i);
-        r = hypot(f, g);
-        if (lane == i + 1) e = r;
-        if (r == A(0)) {
-          const A v = gd(i + 1) - p;
-          if (lane == i + 1) d = v;
+        const A qi = Q[i * 64 + lane];
+        const A ei = lane_value(e, i), di = lane_value(d, i);
+        const A f = s * ei, b = c * ei;
+        const A h2 = f * f + g * g;
+        if (h2 < tiny) {
+          if (lane == i + 1) {
+            e = A(0);
+            d = dn - p;
+          }
           if (lane == mm) e = A(0);
           early = true;
+          Q[(i + 1) * 64 + lane] = q1;
           break;
         }
-        s = f / r;
-        c = g / r;
-        g = gd(i + 1) - p;
-        r = (gd(i) - g) * s + A(2) * c * b;
+        A ri;
+        sqrt_pair(h2, r, ri);
+        if (lane == i + 1) e = r;
+        s = f * ri;
+        c = g * ri;
+        g = dn - p;
+        r = (di - g) * s + A(2) * c * b;
         p = s * r;
-        const A nd = g + p;
-        if (lane == i + 1) d = nd;
+        if (lane == i + 1) d = g + p;
         g = c * r - b;
-        const A qi1 = Q[(i + 1) * 64 + lane], qi = Q[i * 64 + lane];
-        Q[(i + 1) * 64 + lane] = s * qi + c * qi1;
-        Q[i * 64 + lane] = c * qi - s * qi1;
+        Q[(i + 1) * 64 + lane] = s * qi + c * q1;
+        q1 = c * qi - s * q1;
+        dn = di;
       }
       if (early) continue;
-      const A nl = gd(l) - p;
+      Q[l * 64 + lane] = q1;
       if (lane == l) {
-        d = nl;
+        d = dn - p;
         e = g;
       }
       if (lane == mm) e = A(0);
@@ -1438,12 +1488,10 @@ __device__ A tridiag_sqrt_e1(int n, A d, A e, A *Q, int &ok) {
     if (!ok) break;
   }
   __builtin_amdgcn_wave_barrier();
+  const A root = sqrt(d > A(0) ? d : A(0));
   A acc = 0;
-  for (int j = 0; j < n; ++j) {
-    const A lam = gd(j);
-    acc += Q[j * 64 + lane] * sqrt(lam > A(0) ? lam : A(0)) * Q[j * 64];
-  }
-  return acc;
+  for (int j = 0; j < n; ++j) acc += Q[j * 64 + lane] * lane_value(root, j) * Q[j * 64];
+  return ldexp(acc, ex / 2);
 }
 
 // After iteration m: beta_{m+1} = |w|, s = T_{m+1}^{1/2} e_1, convergence test
@@ -1474,14 +1522,14 @@ __device__ __forceinline__ void lz_check_body(const A *__restrict__ partials, in
   const A sk = tridiag_sqrt_e1<A>(nn, d, e, Q, ok);
   const A sold = (lane < m) ? st->s[lane] : A(0);
   const A dif = lane < nn ? (sk - sold) : A(0);
-  const A num = wave_sum(dif * dif);
-  const A den = wave_sum(lane < nn ? sk * sk : A(0));
-  const A rel = den > A(0) ? sqrt(num / den) : A(0);
-  A scale2 = 0;
+  A num = 0, den = 0, scale2 = 0;
   for (int j = 0; j < nn; ++j) {
-    const A aj = __shfl(d, j, 64);
+    const A dj = lane_value(dif, j), sj = lane_value(sk, j), aj = lane_value(d, j);
+    num += dj * dj;
+    den += sj * sj;
     scale2 += aj * aj;
   }
+  const A rel = den > A(0) ? sqrt(num / den) : A(0);
   const A bdn = (sizeof(A) == 8 ? A(1e-11) : A(1e-6)) * sqrt(scale2 + bb * bb);
   const bool finite = isfinite(bb) && isfinite(den) && ok;
   if (lane < nn) st->s[lane] = sk;
