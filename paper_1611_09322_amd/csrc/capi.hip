@@ -52,7 +52,7 @@ inline size_t asize(const pse_ctx *c) { return c->acc_dbl ? 8 : 4; }
 void free_ctx(pse_ctx *c) {
   if (!c) return;
   void *dev[] = {c->pos_w, c->pos_s, c->perm, c->cell_of, c->cell_count, c->cell_start, c->nbr, c->nbr_cnt,
-                 c->flags, c->V, c->lz, c->partials, c->counter, c->table, c->series, c->grid, c->rgrid, c->grid2, c->tw_M,
+                 c->flags, c->V, c->lz, c->lz_nodes, c->partials, c->table, c->series, c->grid, c->rgrid, c->grid2, c->tw_M,
                  c->tw_H, c->pc_w, c->pc_feat, c->pc_y, c->pc_P, c->pc_Pinv, c->pc_user, c->fl_V, c->fl_ab,
                  c->fl_coef};
   for (void *p : dev)
@@ -141,18 +141,20 @@ hipEvent_t next_event(pse_ctx *c) {
 }
 
 // ---------------------------------------------------------- hot path
-// The Krylov sample in two halves.  lz_start launches the first chunk of
-// iterations (as many as the previous sample needed; the kernels stop
-// themselves once converged) and queues the read-back of the state;
-// lz_finish, after the stream has been synchronised, continues one
-// iteration at a time if needed and combines the iterate.  Split so that a
-// batch of contexts needs one synchronisation per stream, not per context.
+// The Krylov sample in two halves, on the start vector in the basis' first
+// slot.  lz_start launches the first chunk of iterations (as many as the
+// previous sample needed; the kernels stop themselves once converged) and
+// queues the read-back of the state; lz_finish, after the stream has been
+// synchronised, continues one iteration at a time if needed.  Split so that
+// a batch of contexts needs one synchronisation per stream, not per context.
+// The iterate is left to the final sum (launch_finalize_krylov); only a
+// preconditioned one is formed here, into y_sorted (*formed).
 template <typename T, typename A>
-pse_status lz_start(pse_ctx *c, const void *z_sorted) {
-  launch_lz_init<T, A>(c, z_sorted);
+pse_status lz_start(pse_ctx *c) {
   if (c->lz_external) {
     // captured batch step: the batch launches the iterations of all its
     // replicas together, and lz_finish reads the state back
+    launch_lz_norm<T, A>(c, false);
     c->lz_launched = c->graph_iters;
     return hip_status(hipGetLastError());
   }
@@ -162,10 +164,7 @@ pse_status lz_start(pse_ctx *c, const void *z_sorted) {
   int k = c->last_iters < 2 ? 2 : c->last_iters;
   if (c->graph) k = c->graph_iters;  // no host decision: the kernels stop themselves once converged
   if (k > maxit) k = maxit;
-  for (int i = 0; i < k; ++i) {
-    if (pc) launch_lz_iter_pc<T, A>(c, i, z_sorted);
-    else launch_lz_iter<T, A>(c, i, z_sorted);
-  }
+  launch_lz_iters<T, A>(c, 0, k, pc);
   c->lz_launched = k;
   if (c->status_external) return hip_status(hipGetLastError());  // read back with the batch's status
   return hip_status(hipMemcpyAsync(c->lz_h, c->lz, sizeof(LzState<A>), hipMemcpyDeviceToHost, c->stream));
@@ -182,7 +181,12 @@ void take_pc_fallbacks(pse_ctx *c, bool synced) {
 }
 
 template <typename T, typename A>
-pse_status lz_finish(pse_ctx *c, const void *z_sorted, void *y_sorted, pse_stats *stats) {
+pse_status lz_finish(pse_ctx *c, void *y_sorted, bool *formed, pse_stats *stats) {
+  auto form = [&] {  // y = P^-1 A^1/2 z
+    launch_lz_combine<T, A>(c, y_sorted);
+    launch_pc_apply_inv<T>(c, y_sorted);
+  };
+  *formed = pc_active(c);
   if (c->graph) {
     // captured: the iterate of the iterations queued by lz_start (or by the
     // batch); the state copied back tells the host after the replay
@@ -190,17 +194,15 @@ pse_status lz_finish(pse_ctx *c, const void *z_sorted, void *y_sorted, pse_stats
     if (c->lz_external && !c->status_external &&
         hipMemcpyAsync(c->lz_h, c->lz, sizeof(LzState<A>), hipMemcpyDeviceToHost, c->stream) != hipSuccess)
       return PSE_ERR_HIP;
-    launch_lz_combine<T, A>(c, y_sorted);
-    if (pc_active(c)) launch_pc_apply_inv<T>(c, y_sorted);
+    if (*formed) form();
     return hip_status(hipGetLastError());
   }
   take_pc_fallbacks(c, true);
   auto *h = (LzState<A> *)c->lz_h;
-  const bool pc = pc_active(c);
+  const bool pc = *formed;
   const int maxit = c->lz_maxit;
   while (!h->done && c->lz_launched < maxit) {
-    if (pc) launch_lz_iter_pc<T, A>(c, c->lz_launched, z_sorted);
-    else launch_lz_iter<T, A>(c, c->lz_launched, z_sorted);
+    launch_lz_iters<T, A>(c, c->lz_launched, 1, pc);
     ++c->lz_launched;
     if (hipMemcpyAsync(h, c->lz, sizeof(LzState<A>), hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
         hipStreamSynchronize(c->stream) != hipSuccess)
@@ -211,15 +213,14 @@ pse_status lz_finish(pse_ctx *c, const void *z_sorted, void *y_sorted, pse_stats
     // the tolerance not met within max_iter), so the same z is sampled
     // again with P = I, and every particle counts as fallen back
     c->pc_suspend = true;
-    pse_status st = lz_start<T, A>(c, z_sorted);
+    pse_status st = lz_start<T, A>(c);
     if (st == PSE_OK && hipStreamSynchronize(c->stream) != hipSuccess) st = PSE_ERR_HIP;
-    if (st == PSE_OK) st = lz_finish<T, A>(c, z_sorted, y_sorted, stats);
+    if (st == PSE_OK) st = lz_finish<T, A>(c, y_sorted, formed, stats);
     c->pc_suspend = false;
     if (stats) stats->precond_fallbacks = c->n;
     return st == PSE_OK || st == PSE_WARN_PRECOND_FALLBACK ? PSE_WARN_PRECOND_FALLBACK : st;
   }
-  launch_lz_combine<T, A>(c, y_sorted);
-  if (pc) launch_pc_apply_inv<T>(c, y_sorted);  // y = P^-1 A^1/2 z
+  if (pc) form();
   c->last_iters = h->m;
   if (stats) {
     stats->max_neighbors = c->flags_h[5];
@@ -235,14 +236,6 @@ pse_status lz_finish(pse_ctx *c, const void *z_sorted, void *y_sorted, pse_stats
   if (!h->converged) return PSE_ERR_NOT_CONVERGED;
   if (c->pc_on && c->pc_fallbacks > 0) return PSE_WARN_PRECOND_FALLBACK;
   return PSE_OK;
-}
-
-template <typename T, typename A>
-pse_status real_sample_core(pse_ctx *c, const void *z_sorted, void *y_sorted, pse_stats *stats) {
-  pse_status st = lz_start<T, A>(c, z_sorted);
-  if (st != PSE_OK) return st;
-  if (hipStreamSynchronize(c->stream) != hipSuccess) return PSE_ERR_HIP;
-  return lz_finish<T, A>(c, z_sorted, y_sorted, stats);
 }
 
 // Wave-space velocity/displacement in sorted order into `out`:
@@ -296,7 +289,7 @@ pse_status sample_begin(pse_ctx *c, bool philox, uint64_t seed, uint64_t counter
   if (!c->have_pos) return PSE_ERR_NO_POSITIONS;
   if (!(dt >= 0)) return PSE_ERR_INVALID_ARG;
   ss.cr = std::sqrt(2.0 * c->p.kT * dt);
-  void *z_s = c->vbuf[0], *wave = c->vbuf[4], *f_s = c->vbuf[6], *ur = c->vbuf[7];
+  void *z_s = c->V, *wave = c->vbuf[4], *f_s = c->vbuf[6], *ur = c->vbuf[7];
   ss.real = false;
   if (philox) {
     launch_real_noise<T>(c, z_s, seed, counter);  // caller-order noise, written in sorted order
@@ -307,7 +300,7 @@ pse_status sample_begin(pse_ctx *c, bool philox, uint64_t seed, uint64_t counter
   }
   ss.real = ss.real && ss.cr > 0;
   if (ss.real) {
-    const pse_status st = lz_start<T, A>(c, z_s);
+    const pse_status st = lz_start<T, A>(c);
     if (st != PSE_OK) return st;
   }
   ss.forces = (forces || f_add) && dt > 0;
@@ -315,7 +308,7 @@ pse_status sample_begin(pse_ctx *c, bool philox, uint64_t seed, uint64_t counter
     // caller-order forces, plus the sorted overlap repulsion of a Brownian step
     if (f_add) launch_gather3_add<T>(c, forces, f_add, f_s);
     else launch_gather3<T>(c, forces, f_s);
-    launch_spmv<T, A>(c, f_s, ur, false, nullptr);
+    launch_spmv<T>(c, f_s, ur);
   }
   const WaveCoef wc = step_wave_coef(c, dt, seed, counter);
   const int noise = (ss.cr > 0) ? (philox ? 1 : (W ? 2 : 0)) : 0;
@@ -325,10 +318,11 @@ pse_status sample_begin(pse_ctx *c, bool philox, uint64_t seed, uint64_t counter
 
 template <typename T, typename A>
 pse_status sample_end(pse_ctx *c, const SampleState &ss, double dt, void *disp, pse_stats *stats) {
-  void *z_s = c->vbuf[0], *yr = c->vbuf[1], *wave = c->vbuf[4], *ur = c->vbuf[7];
+  void *yr = c->vbuf[1], *wave = c->vbuf[4], *ur = ss.forces ? c->vbuf[7] : nullptr;
   pse_status st = PSE_OK;
+  bool formed = false;
   if (ss.real) {
-    st = lz_finish<T, A>(c, z_s, yr, stats);
+    st = lz_finish<T, A>(c, yr, &formed, stats);
     if (st < 0 && st != PSE_ERR_NOT_CONVERGED) return st;  // warnings (> 0) continue
   } else if (stats) {
     stats->lanczos_iters = 0;
@@ -336,7 +330,8 @@ pse_status sample_end(pse_ctx *c, const SampleState &ss, double dt, void *disp, 
     stats->lanczos_rel_change = 0;
     stats->precond_fallbacks = 0;
   }
-  launch_finalize<T>(c, ss.real ? yr : nullptr, ss.cr, ss.forces ? ur : nullptr, dt, wave, disp);
+  if (ss.real && !formed) launch_finalize_krylov<T, A>(c, ss.cr, ur, dt, wave, disp);
+  else launch_finalize<T>(c, ss.real ? yr : nullptr, ss.cr, ur, dt, wave, disp);
   if (c->graph) {
     // the device flags of this step (list and halo overflow, non-finite
     // positions) for the host's check after the replay
@@ -552,7 +547,7 @@ pse_status full_sample_impl(pse_ctx *c, const void *z, void *y, pse_stats *stats
   double rel = 1.0;
   while (!conv && m < maxit) {
     const T4 *vm = V + (size_t)m * n;
-    launch_spmv<T, A>(c, vm, t, false, nullptr);                                   // M_r v_m
+    launch_spmv<T>(c, vm, t);                                                       // M_r v_m
     const pse_status ws = wave_core<T>(c, vm, 0, nullptr, wc, u);                   // M_w v_m
     if (ws != PSE_OK) return ws;
     launch_fl_alpha<T, A>(c, t, u, vm, ab + m);                                     // t = M v_m, alpha_m
@@ -601,20 +596,25 @@ pse_status full_sample_impl(pse_ctx *c, const void *z, void *y, pse_stats *stats
   return hip_status(hipGetLastError());
 }
 
-template <typename T, typename A>
+template <typename T>
 pse_status real_matvec_impl(pse_ctx *c, const void *v, void *w) {
   launch_gather3<T>(c, v, c->vbuf[0]);
-  launch_spmv<T, A>(c, c->vbuf[0], c->vbuf[7], false, nullptr);
+  launch_spmv<T>(c, c->vbuf[0], c->vbuf[7]);
   launch_finalize<T>(c, nullptr, 0.0, c->vbuf[7], 1.0, nullptr, w);
   return hip_status(hipGetLastError());
 }
 
 template <typename T, typename A>
 pse_status real_sample_impl(pse_ctx *c, const void *z, void *y, pse_stats *stats) {
-  launch_gather3<T>(c, z, c->vbuf[0]);
-  pse_status st = real_sample_core<T, A>(c, c->vbuf[0], c->vbuf[1], stats);
+  launch_gather3<T>(c, z, c->V);
+  pse_status st = lz_start<T, A>(c);
+  if (st != PSE_OK) return st;
+  if (hipStreamSynchronize(c->stream) != hipSuccess) return PSE_ERR_HIP;
+  bool formed = false;
+  st = lz_finish<T, A>(c, c->vbuf[1], &formed, stats);
   if (st < 0 && st != PSE_ERR_NOT_CONVERGED) return st;  // warnings (> 0) continue
-  launch_finalize<T>(c, c->vbuf[1], 1.0, nullptr, 0.0, nullptr, y);
+  if (formed) launch_finalize<T>(c, c->vbuf[1], 1.0, nullptr, 0.0, nullptr, y);
+  else launch_finalize_krylov<T, A>(c, 1.0, nullptr, 0.0, nullptr, y);
   const pse_status se = hip_status(hipGetLastError());
   return se != PSE_OK ? se : st;
 }
@@ -629,14 +629,14 @@ pse_status wave_sample_impl(pse_ctx *c, const void *W, void *y) {
   return hip_status(hipGetLastError());
 }
 
-template <typename T, typename A>
+template <typename T>
 pse_status wave_apply_impl(pse_ctx *c, const void *F, void *u, bool with_real) {
   const double M3 = (double)c->p.grid * c->p.grid * c->p.grid;
   launch_gather3<T>(c, F, c->vbuf[6]);
   WaveCoef wc = wave_coef(c, 1.0 / (c->p.eta * M3), 0.0, 0, 0);
   pse_status st = wave_core<T>(c, c->vbuf[6], 0, nullptr, wc, c->vbuf[4]);
   if (st != PSE_OK) return st;
-  if (with_real) launch_spmv<T, A>(c, c->vbuf[6], c->vbuf[7], false, nullptr);
+  if (with_real) launch_spmv<T>(c, c->vbuf[6], c->vbuf[7]);
   launch_finalize<T>(c, nullptr, 0.0, with_real ? c->vbuf[7] : nullptr, 1.0, c->vbuf[4], u);
   return hip_status(hipGetLastError());
 }
@@ -690,10 +690,10 @@ struct pse_batch {
   // loop per Lanczos scalar type ([0] FP32, [1] FP64)
   struct LzBatch {
     void *reps = nullptr;              // LzRep<A> [nrep], device
-    int2 *maps = nullptr;              // product blocks of every group, then the vector blocks
+    int2 *maps = nullptr;              // product blocks of every group, the vector blocks, the two lists of systems
     std::vector<pse::LzGroup> groups;  // pmap pointers into maps
-    const int2 *vmap = nullptr;
-    int nrep = 0, nv = 0, iters = 0;
+    pse::LzVecMaps vm{};               // pointers into maps
+    int nrep = 0, iters = 0;
     std::vector<int> members;  // replica of each LzRep
   } lzb[2];
   // replicas whose whole captured step is batched ([0] FP32, [1] FP64
@@ -887,11 +887,11 @@ pse_status pse_create(const pse_params *p, void *stream, pse_ctx **out) {
   const size_t lzbytes = c->acc_dbl ? sizeof(LzState<double>) : sizeof(LzState<float>);
   c->lz = al.dev(lzbytes);
   c->lz_h = al.host(lzbytes);
+  c->lz_nodes = (double2 *)al.dev(sizeof(double2) * kRootNodes);
   // partial sums: one per block of the widest reduction (256-particle
   // blocks, or one per LDS target block of edge 1 cell)
   const size_t nparts = std::max<size_t>(std::max<size_t>(kRedBlock, (n + 255) / 256), (size_t)c->ncell);
   c->partials = al.dev(A * (nparts + kRedBlock));  // + the alpha partial sums of a Lanczos step
-  c->counter = (unsigned *)al.dev(sizeof(unsigned));
   const size_t M3 = (size_t)p->grid * p->grid * p->grid;
   c->grid = al.dev(3 * T * M3);
   c->rgrid = al.dev(4 * T * M3);
@@ -935,7 +935,11 @@ pse_status pse_create(const pse_params *p, void *stream, pse_ctx **out) {
     fg_build_table(p->xi, p->a, p->rcut, d.mu0, serF, serG, tab.data());
     e = hipMemcpy(c->table, tab.data(), sizeof(float2) * kTableN, hipMemcpyHostToDevice);
   }
-  if (e == hipSuccess) e = hipMemset(c->counter, 0, sizeof(unsigned));
+  if (e == hipSuccess) {
+    double2 tw[kRootNodes];
+    lz_quadrature(tw);
+    e = hipMemcpy(c->lz_nodes, tw, sizeof tw, hipMemcpyHostToDevice);
+  }
   if (e == hipSuccess && c->pc_w) e = hipMemset(c->pc_w, 0, sizeof(uint16_t) * kWTotal);
   if (e != hipSuccess) {
     free_ctx(c);
@@ -1027,7 +1031,8 @@ pse_status pse_full_sample(pse_ctx *c, const void *z, void *y, pse_stats *stats)
 pse_status pse_real_matvec(pse_ctx *c, const void *v, void *w) {
   if (!c || !v || !w) return PSE_ERR_INVALID_ARG;
   if (!c->have_pos) return PSE_ERR_NO_POSITIONS;
-  DISPATCH(c, (real_matvec_impl<T, A>(c, v, w)));
+  if (c->dbl) return real_matvec_impl<double>(c, v, w);
+  return real_matvec_impl<float>(c, v, w);
 }
 
 pse_status pse_real_sample(pse_ctx *c, const void *z, void *y, pse_stats *stats) {
@@ -1046,7 +1051,8 @@ pse_status pse_wave_sample(pse_ctx *c, const void *W, void *y) {
 pse_status pse_wave_apply(pse_ctx *c, const void *F, void *u) {
   if (!c || !F || !u) return PSE_ERR_INVALID_ARG;
   if (!c->have_pos) return PSE_ERR_NO_POSITIONS;
-  DISPATCH(c, (wave_apply_impl<T, A>(c, F, u, false)));
+  if (c->dbl) return wave_apply_impl<double>(c, F, u, false);
+  return wave_apply_impl<float>(c, F, u, false);
 }
 
 pse_status pse_autotune(pse_ctx *c, int32_t *choice) {
@@ -1299,6 +1305,7 @@ template <typename A> static pse_status lzb_setup(pse_batch *b) {
   std::vector<std::vector<int2>> pm;
   std::vector<LzGroup> gr;
   std::vector<int2> vm;
+  std::vector<int> big, small;
   int iters = 0;
   for (int r = 0; r < R; ++r) {
     pse_ctx *c = b->ctx[r];
@@ -1313,11 +1320,10 @@ template <typename A> static pse_status lzb_setup(pse_batch *b) {
     q.cnt = c->nbr_cnt;
     q.tab = c->table;
     q.ovf = c->flags + 7;
-    q.z = (const float4 *)c->vbuf[0];
     q.t = (float4 *)c->vbuf[2];
-    q.w = (float4 *)c->vbuf[3];
     q.V = (float4 *)c->V;
     q.st = (LzState<A> *)c->lz;
+    q.nodes = c->lz_nodes;
     q.partials = (A *)c->partials;
     // the fully batched replicas' M_r F runs in the batched plain product
     const bool fr = !b->is_full.empty() && b->is_full[r] && batch_forces(b, r) && b->g_dt > 0;
@@ -1345,11 +1351,14 @@ template <typename A> static pse_status lzb_setup(pse_batch *b) {
     for (int blk = 0; blk < c->lds_blocks; ++blk) pm[g].push_back(make_int2(k, blk));
     const size_t smem = (sizeof(float4) + sizeof(float2)) * (size_t)c->hcap;
     if (smem > gr[g].smem) gr[g].smem = smem;
-    for (int v = 0; v < (c->n + 255) / 256; ++v) vm.push_back(make_int2(k, v));
+    if (c->n > kLzStepMax)
+      for (int v = 0; v < (c->n + 255) / 256; ++v) vm.push_back(make_int2(k, v));
+    (c->n > kLzStepMax ? big : small).push_back(k);
     iters = std::max(iters, c->graph_iters);
   }
   if (reps.empty()) return PSE_OK;
-  size_t nmap = vm.size();
+  const size_t nlist = (big.size() + small.size() + 1) / 2;  // int2 entries holding the two lists
+  size_t nmap = vm.size() + nlist;
   for (auto &x : pm) nmap += x.size();
   if (hipMalloc(&z.reps, sizeof(LzRep<A>) * reps.size()) != hipSuccess ||
       hipMalloc((void **)&z.maps, sizeof(int2) * nmap) != hipSuccess)
@@ -1361,23 +1370,30 @@ template <typename A> static pse_status lzb_setup(pse_batch *b) {
     gr[g].nblk = (int)pm[g].size();
     all.insert(all.end(), pm[g].begin(), pm[g].end());
   }
-  z.vmap = z.maps + all.size();
+  z.vm.vmap = z.maps + all.size();
+  z.vm.nv = (int)vm.size();
   all.insert(all.end(), vm.begin(), vm.end());
+  z.vm.big = (const int *)(z.maps + all.size());
+  z.vm.small = z.vm.big + big.size();
+  z.vm.nbig = (int)big.size();
+  z.vm.nsmall = (int)small.size();
+  std::vector<int> list(big);
+  list.insert(list.end(), small.begin(), small.end());
+  list.resize(2 * nlist, 0);
+  for (size_t i = 0; i < nlist; ++i) all.push_back(make_int2(list[2 * i], list[2 * i + 1]));
   if (hipMemcpy(z.reps, reps.data(), sizeof(LzRep<A>) * reps.size(), hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(z.maps, all.data(), sizeof(int2) * nmap, hipMemcpyHostToDevice) != hipSuccess)
     return PSE_ERR_HIP;
   z.groups = gr;
   z.nrep = (int)reps.size();
-  z.nv = (int)vm.size();
   z.iters = iters;
   return PSE_OK;
 }
 
 template <typename A> static void lzb_launch(pse_batch *b) {
   const pse_batch::LzBatch &z = b->lzb[sizeof(A) == 8 ? 1 : 0];
-  for (int m = 0; m < z.iters; ++m)
-    launch_lz_batch_iter<A>(b->gstream, (const LzRep<A> *)z.reps, z.nrep, z.groups.data(), (int)z.groups.size(),
-                            z.vmap, z.nv, m);
+  if (z.nrep)
+    launch_lz_batch<A>(b->gstream, (const LzRep<A> *)z.reps, z.groups.data(), (int)z.groups.size(), z.vm, z.iters);
 }
 
 // The batched neighbour build of a captured step: every replica on the LDS
@@ -1456,11 +1472,9 @@ static pse_status full_setup(pse_batch *b) {
   for (int a = 0; a < 2; ++a) {
     pse_batch::FullBatch &f = b->full[a];
     std::vector<SampRep> reps;
-    std::vector<int2> mz, mp, mt, mc, mf;
+    std::vector<int2> mz, mp, mt, mc;
     for (int r = 0; r < R; ++r) {
       pse_ctx *c = b->ctx[r];
-      // 4n vector scalars in at most kRedBlock blocks of 256: the Krylov
-      // start's partial sums are laid out as in a single-system launch
       if (!b->is_full[r] || (c->acc_dbl ? 1 : 0) != a) continue;
       if (!(in_lz[r] && in_nb[r] && in_wv[r])) return PSE_ERR_INVALID_ARG;  // the candidate test and the batched sets disagree
       const int k = (int)reps.size(), n = c->n;
@@ -1482,11 +1496,9 @@ static pse_status full_setup(pse_batch *b) {
       q.ncell = c->ncell;
       q.n = n;
       q.rng = c->rng_dev;
-      q.z = (float4 *)c->vbuf[0];
       q.partials = c->partials;
       q.st = c->lz;
-      q.V = (const float4 *)c->V;
-      q.yr = (float4 *)c->vbuf[1];
+      q.V = (float4 *)c->V;
       q.wave = (const float4 *)c->vbuf[4];
       q.out = (float *)b->g_disp[r];
       q.cr = (float)std::sqrt(2.0 * c->p.kT * b->g_dt);
@@ -1500,10 +1512,9 @@ static pse_status full_setup(pse_batch *b) {
       for (int q2 = 0; q2 < (n + 255) / 256; ++q2) mp.push_back(make_int2(k, q2));
       for (int q2 = 0; q2 < (c->ncell + kScanTile - 1) / kScanTile; ++q2) mt.push_back(make_int2(k, q2));
       for (int q2 = 0; q2 < (c->ncell + 3) / 4; ++q2) mc.push_back(make_int2(k, q2));
-      for (int q2 = 0; q2 < (4 * n + 255) / 256; ++q2) mf.push_back(make_int2(k, q2));
     }
     if (reps.empty()) continue;
-    const size_t nmap = mz.size() + mp.size() + mt.size() + mc.size() + mf.size();
+    const size_t nmap = mz.size() + mp.size() + mt.size() + mc.size();
     if (hipMalloc((void **)&f.reps, sizeof(SampRep) * reps.size()) != hipSuccess ||
         hipMalloc((void **)&f.maps, sizeof(int2) * nmap) != hipSuccess)
       return PSE_ERR_OOM;
@@ -1518,7 +1529,6 @@ static pse_status full_setup(pse_batch *b) {
     put(mp, f.m.part, f.m.npart);
     put(mt, f.m.tile, f.m.ntile);
     put(mc, f.m.cell, f.m.ncell);
-    put(mf, f.m.flat, f.m.nflat);
     f.m.nrep = (int)reps.size();
     if (hipMemcpy(f.reps, reps.data(), sizeof(SampRep) * reps.size(), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(f.maps, all.data(), sizeof(int2) * nmap, hipMemcpyHostToDevice) != hipSuccess)
@@ -2056,7 +2066,8 @@ pse_status pse_mlp_adam(void *w_master, void *w_bf16, const void *dw, void *m, v
 pse_status pse_mobility_apply(pse_ctx *c, const void *F, void *u) {
   if (!c || !F || !u) return PSE_ERR_INVALID_ARG;
   if (!c->have_pos) return PSE_ERR_NO_POSITIONS;
-  DISPATCH(c, (wave_apply_impl<T, A>(c, F, u, true)));
+  if (c->dbl) return wave_apply_impl<double>(c, F, u, true);
+  return wave_apply_impl<float>(c, F, u, true);
 }
 
 }  // extern "C"

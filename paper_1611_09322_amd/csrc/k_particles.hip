@@ -1,6 +1,7 @@
 // Particle-side kernels: wrapping and linked-cell binning, the sorted order,
 // the near-field neighbour list, the real-space product w = M_r v
 // (eq. Mreal, Appendix A) and the Lanczos square-root iteration (Sec. II B.1).
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 #include <unordered_set>
@@ -428,19 +429,16 @@ __global__ void k_nbr_build(const typename vec4<T>::type *__restrict__ pos, cons
 
 // --------------------------------------------------- near-field product
 // One thread per sorted particle s:
-//   out_s = scale * ( self * v_s + sum_{t in nbr(s)} mu0 [F v_t + (G-F)(d.v_t) d / r^2] )
-// with v = src (times `scale`).  In the Lanczos variant the scale is the
-// device-side 1/beta, the thread also stores the basis vector V_m = scale*src
-// and the block reduces V_m . out toward alpha_m (last block finishes it).
-template <typename T, typename A, typename FG, bool LZ>
+//   out_s = self * v_s + sum_{t in nbr(s)} mu0 [F v_t + (G-F)(d.v_t) d / r^2]
+// with v = src.  A Lanczos iteration passes `done`, the flag of its state:
+// once set the product is skipped (null: always formed).
+template <typename T, typename FG>
 __device__ __forceinline__ void spmv_body(const typename vec4<T>::type *__restrict__ pos, const int *__restrict__ nbr,
                                           const int *__restrict__ cnt, int n, T L, T invL, const FG &fg, T self_r,
-                                          const typename vec4<T>::type *__restrict__ src, T scale,
-                                          typename vec4<T>::type *__restrict__ out,
-                                          typename vec4<T>::type *__restrict__ vm_out, A &dot) {
+                                          const typename vec4<T>::type *__restrict__ src,
+                                          typename vec4<T>::type *__restrict__ out) {
   using T4 = typename vec4<T>::type;
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  dot = A(0);
   if (s >= n) return;
   const T4 p = pos[s];
   const T4 v = src[s];
@@ -471,97 +469,34 @@ __device__ __forceinline__ void spmv_body(const typename vec4<T>::type *__restri
     az += Fm * w.z + pr * dz;
   }
   T4 o;
-  o.x = ax * scale;
-  o.y = ay * scale;
-  o.z = az * scale;
+  o.x = ax;
+  o.y = ay;
+  o.z = az;
   o.w = T(0);
   out[s] = o;
-  if (LZ) {
-    T4 u;
-    u.x = v.x * scale;
-    u.y = v.y * scale;
-    u.z = v.z * scale;
-    u.w = T(0);
-    vm_out[s] = u;
-    dot = (A)u.x * (A)o.x + (A)u.y * (A)o.y + (A)u.z * (A)o.z;
-  }
 }
 
-template <typename T, typename A, bool LZ>
 __global__ __launch_bounds__(256) void k_spmv_table(const float4 *__restrict__ pos, const int *__restrict__ nbr,
                                                     const int *__restrict__ cnt, int n, float L, float invL,
                                                     const float2 *__restrict__ tab_g, float inv_dr, float self_r,
-                                                    const float4 *__restrict__ src, float scale, float4 *__restrict__ out,
-                                                    float4 *__restrict__ vm_out, LzState<A> *st, A *partials,
-                                                    unsigned *counter) {
+                                                    const float4 *__restrict__ src, float4 *__restrict__ out,
+                                                    const int *__restrict__ done) {
   __shared__ float2 tab[kTableN];
-  __shared__ A sh[16];
-  __shared__ int last;
-  if (LZ) {
-    if (st->done) return;
-    scale = (float)st->inv_beta;
-  }
+  if (done && *done) return;
   for (int i = threadIdx.x; i < kTableN; i += blockDim.x) tab[i] = tab_g[i];
   __syncthreads();
   FGTable fg{tab, inv_dr};
-  A dot;
-  spmv_body<float, A, FGTable, LZ>(pos, nbr, cnt, n, L, invL, fg, self_r, src, scale, out, vm_out, dot);
-  if (!LZ) return;
-  A bs = block_sum(dot, sh);
-  if (threadIdx.x == 0) {
-    partials[blockIdx.x] = bs;
-    __threadfence();
-    const unsigned prev = atomicAdd(counter, 1u);
-    last = (prev == gridDim.x - 1);
-  }
-  __syncthreads();
-  if (last) {
-    __threadfence();
-    A v = 0;
-    for (int i = threadIdx.x; i < (int)gridDim.x; i += blockDim.x) v += partials[i];
-    v = block_sum(v, sh);
-    if (threadIdx.x == 0) {
-      st->alpha[st->m] = v;
-      *counter = 0u;
-    }
-  }
+  spmv_body<float, FGTable>(pos, nbr, cnt, n, L, invL, fg, self_r, src, out);
 }
 
-template <bool LZ>
 __global__ __launch_bounds__(256) void k_spmv_exact(const double4 *__restrict__ pos, const int *__restrict__ nbr,
                                                     const int *__restrict__ cnt, int n, double L, double invL,
                                                     const double *__restrict__ ser, double xi, double a, double mu0,
                                                     double small_r2, double self_r, const double4 *__restrict__ src,
-                                                    double scale, double4 *__restrict__ out, double4 *__restrict__ vm_out,
-                                                    LzState<double> *st, double *partials, unsigned *counter) {
-  __shared__ double sh[16];
-  __shared__ int last;
-  if (LZ) {
-    if (st->done) return;
-    scale = st->inv_beta;
-  }
+                                                    double4 *__restrict__ out, const int *__restrict__ done) {
+  if (done && *done) return;
   FGExact fg{ser, xi, a, mu0, small_r2};
-  double dot;
-  spmv_body<double, double, FGExact, LZ>(pos, nbr, cnt, n, L, invL, fg, self_r, src, scale, out, vm_out, dot);
-  if (!LZ) return;
-  double bs = block_sum(dot, sh);
-  if (threadIdx.x == 0) {
-    partials[blockIdx.x] = bs;
-    __threadfence();
-    const unsigned prev = atomicAdd(counter, 1u);
-    last = (prev == gridDim.x - 1);
-  }
-  __syncthreads();
-  if (last) {
-    __threadfence();
-    double v = 0;
-    for (int i = threadIdx.x; i < (int)gridDim.x; i += blockDim.x) v += partials[i];
-    v = block_sum(v, sh);
-    if (threadIdx.x == 0) {
-      st->alpha[st->m] = v;
-      *counter = 0u;
-    }
-  }
+  spmv_body<double, FGExact>(pos, nbr, cnt, n, L, invL, fg, self_r, src, out);
 }
 
 // ------------------------------------------- LDS-staged near-field kernels
@@ -1045,20 +980,18 @@ __global__ __launch_bounds__(kFeatNT) void k_feat_lds(const float4 *__restrict__
 // workgroups share a compute unit: one stages its halo while the other
 // computes.  With UNWRAP the staged positions are the images nearest the
 // block centre.
-// With LZ (a Lanczos step) the epilogue scales by 1 / beta_m and stores the
-// basis vector v_m; alpha_m = <v_m, out> is formed by the update step.
-// With PC (Lanczos on A = P M_r P^T): src holds u = P^T r, and the
-// epilogue forms out = P (M_r u) / beta and v_m = r / beta (r from rsrc);
+// A Lanczos iteration passes `done`, the flag of its state: once set the
+// product is skipped (null: always formed).  With PC (Lanczos on
+// A = P M_r P^T): src holds P^T u and the epilogue forms out = P M_r src;
 // Pm holds the rows of P_i as (x, y, z, 0).
-template <int B, bool UNWRAP, typename A, bool LZ, bool PC, int G>
+template <int B, bool UNWRAP, bool PC, int G>
 __device__ __forceinline__ void spmv_lds_block(const float4 *__restrict__ pos, const float4 *__restrict__ src,
                                                const int *__restrict__ cell_start, int nc, float cs, int n, int hcap,
                                                float L, float invL, const uint16_t *__restrict__ nbr,
                                                const int *__restrict__ cnt, const float2 *__restrict__ tab,
-                                               float inv_dr, float self_r, float scale, float4 *__restrict__ out,
-                                               float4 *__restrict__ vm_out, const LzState<A> *st,
-                                               int *__restrict__ ovf, const float4 *__restrict__ Pm,
-                                               const float4 *__restrict__ rsrc, int blk) {
+                                               float inv_dr, float self_r, float4 *__restrict__ out,
+                                               const int *__restrict__ done, int *__restrict__ ovf,
+                                               const float4 *__restrict__ Pm, int blk) {
   constexpr int NH = Halo<B>::NH;
   static_assert(G >= 2 && G <= 4, "lanes per target");
   constexpr int GPW = 64 / G;               // groups per wavefront (lane 63 idle at G = 3)
@@ -1067,10 +1000,7 @@ __device__ __forceinline__ void spmv_lds_block(const float4 *__restrict__ pos, c
   float2 *hB = (float2 *)(smem + hcap);     // (v_y, v_z)
   __shared__ float2 tabs[kTableN];
   __shared__ HaloTab<B> ht;
-  if (LZ) {
-    if (st->done) return;
-    scale = (float)st->inv_beta;
-  }
+  if (done && *done) return;
   for (int k = threadIdx.x; k < kTableN; k += blockDim.x) tabs[k] = tab[k];
   halo_setup<B>(cell_start, nc, ht, blk);
   // a halo past the capacity stages nothing and computes no target
@@ -1194,190 +1124,108 @@ __device__ __forceinline__ void spmv_lds_block(const float4 *__restrict__ pos, c
       sz += tz;
     }
     if (act && g == 0) {
-      const float vx = pa.w, vy = pb.x, vz = pb.y;
-      float4 u4;
+      sx += self_r * pa.w;
+      sy += self_r * pb.x;
+      sz += self_r * pb.y;
       if (PC) {
-        const float tx = sx + self_r * vx, ty = sy + self_r * vy, tz = sz + self_r * vz;
+        const float tx = sx, ty = sy, tz = sz;
         const float4 p0 = Pm[3 * (size_t)s], p1 = Pm[3 * (size_t)s + 1], p2 = Pm[3 * (size_t)s + 2];
-        sx = (p0.x * tx + p0.y * ty + p0.z * tz) * scale;
-        sy = (p1.x * tx + p1.y * ty + p1.z * tz) * scale;
-        sz = (p2.x * tx + p2.y * ty + p2.z * tz) * scale;
-        const float4 r = rsrc[s];
-        u4 = make_float4(r.x * scale, r.y * scale, r.z * scale, 0.0f);
-      } else {
-        sx = (sx + self_r * vx) * scale;
-        sy = (sy + self_r * vy) * scale;
-        sz = (sz + self_r * vz) * scale;
-        u4 = make_float4(vx * scale, vy * scale, vz * scale, 0.0f);
+        sx = p0.x * tx + p0.y * ty + p0.z * tz;
+        sy = p1.x * tx + p1.y * ty + p1.z * tz;
+        sz = p2.x * tx + p2.y * ty + p2.z * tz;
       }
       out[s] = make_float4(sx, sy, sz, 0.0f);
-      if (LZ) vm_out[s] = u4;
     }
   }
 }
 
-template <int B, bool UNWRAP, typename A, bool LZ, bool PC = false, int G = 3>
+template <int B, bool UNWRAP, bool PC = false, int G = 3>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_spmv_lds(
     const float4 *__restrict__ pos, const float4 *__restrict__ src, const int *__restrict__ cell_start, int nc, float cs,
     int n, int hcap, float L, float invL, const uint16_t *__restrict__ nbr, const int *__restrict__ cnt,
-    const float2 *__restrict__ tab, float inv_dr, float self_r, float scale, float4 *__restrict__ out,
-    float4 *__restrict__ vm_out, const LzState<A> *st, int *__restrict__ ovf, const float4 *__restrict__ Pm = nullptr,
-    const float4 *__restrict__ rsrc = nullptr) {
-  spmv_lds_block<B, UNWRAP, A, LZ, PC, G>(pos, src, cell_start, nc, cs, n, hcap, L, invL, nbr, cnt, tab, inv_dr,
-                                          self_r, scale, out, vm_out, st, ovf, Pm, rsrc,
-                                          xcd_block(blockIdx.x, gridDim.x));
+    const float2 *__restrict__ tab, float inv_dr, float self_r, float4 *__restrict__ out,
+    const int *__restrict__ done, int *__restrict__ ovf, const float4 *__restrict__ Pm = nullptr) {
+  spmv_lds_block<B, UNWRAP, PC, G>(pos, src, cell_start, nc, cs, n, hcap, L, invL, nbr, cnt, tab, inv_dr, self_r, out,
+                                   done, ovf, Pm, xcd_block(blockIdx.x, gridDim.x));
 }
 
 // ------------------------------------------------------------- Lanczos
-// Block partial sums of |z|^2 (sorted order vector of length 3n).
+// Iteration m on the basis of unnormalised vectors (LzState):
+//   t = M_r u_m                                       (the product)
+//   alpha_m = <v_m, M_r v_m> = rs_m^2 <u_m, t>
+//   u_{m+1} = 2^-e (rs_m t - alpha_m v_m - beta_m v_{m-1}),  beta_{m+1} = 2^e |u_{m+1}|
+// and the check of iteration m: the square root of T_{m+1} and the stopping
+// rule.  Systems of at most kLzStepMax particles take one launch of one
+// workgroup for all of it (k_lz_step); larger ones the pair k_lz_alpha,
+// k_lz_update.  The next product needs none of the scalars, and the next
+// vector work only beta, so there the check of iteration m is queued as one
+// more workgroup of iteration m + 1's k_lz_alpha, and only the last
+// iteration's is a launch of its own.  Iteration m + 1 is then speculative:
+// what it writes (the next basis slot, alpha, beta) is not read once the
+// state is done.  A captured step, which queues more iterations than it
+// needs, checks before the next product instead (no speculation).
+__device__ __forceinline__ float dot3(float acc, const float4 &a, const float4 &b) {
+  return acc + (a.x * b.x + a.y * b.y + a.z * b.z);
+}
+__device__ __forceinline__ double dot3(double acc, const float4 &a, const float4 &b) {
+  return acc + ((double)a.x * (double)b.x + (double)a.y * (double)b.y + (double)a.z * (double)b.z);
+}
+__device__ __forceinline__ double dot3(double acc, const double4 &a, const double4 &b) {
+  return acc + (a.x * b.x + a.y * b.y + a.z * b.z);
+}
+
+// The even exponent e of alpha (0 where alpha is no positive number).
+template <typename A> __device__ __forceinline__ int lz_exponent(A alpha) {
+  const int e = alpha > A(0) && isfinite(alpha) ? ilogb(alpha) : 0;
+  return e - (e & 1);
+}
+
+// State before iteration 0 from z2 = |z|^2 (one thread).
+template <typename A> __device__ __forceinline__ void lz_begin(LzState<A> *st, A z2) {
+  const A b0 = sqrt(z2);
+  st->beta[0] = b0;
+  st->rs[0] = b0 > A(0) ? A(1) / b0 : A(0);
+  st->m = 0;
+  st->rel_change = A(1);
+  st->converged = b0 == A(0);
+  st->nonfinite = !isfinite(b0);
+  st->done = b0 == A(0) || !isfinite(b0);
+}
+
+// beta_{m+1} and rs_{m+1} from x2 = |u_{m+1}|^2 (one thread).
+template <typename A> __device__ __forceinline__ void lz_set_beta(LzState<A> *st, int m, A x2) {
+  const A nrm = sqrt(x2);
+  st->beta[m + 1] = ldexp(nrm, lz_exponent(st->alpha[m]));
+  st->rs[m + 1] = nrm > A(0) ? A(1) / nrm : A(0);
+}
+
+// u_{m+1} at one particle: c1 t - c2 u_m - c3 u_{m-1}, (x, y, z, 0).
+template <typename T4, typename T>
+__device__ __forceinline__ T4 lz_next(const T4 &t, const T4 &u, const T4 *__restrict__ uprev, int i, T c1, T c2, T c3) {
+  T4 x;
+  x.x = c1 * t.x - c2 * u.x;
+  x.y = c1 * t.y - c2 * u.y;
+  x.z = c1 * t.z - c2 * u.z;
+  if (uprev) {
+    const T4 q = uprev[i];
+    x.x -= c3 * q.x;
+    x.y -= c3 * q.y;
+    x.z -= c3 * q.z;
+  }
+  x.w = T(0);
+  return x;
+}
+
+// c1, c2, c3 of iteration m for alpha_m = al.
 template <typename T, typename A>
-__global__ void k_norm2_partial(const T *__restrict__ z, int len, A *__restrict__ partials) {
-  __shared__ A sh[16];
-  A v = 0;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < len; i += gridDim.x * blockDim.x) v += (A)z[i] * (A)z[i];
-  v = block_sum(v, sh);
-  if (threadIdx.x == 0) partials[blockIdx.x] = v;
-}
-
-template <typename A>
-__device__ __forceinline__ void lz_init_body(const A *__restrict__ partials, int nparts, LzState<A> *st) {
-  __shared__ A sh[16];
-  A v = 0;
-  for (int i = threadIdx.x; i < nparts; i += blockDim.x) v += partials[i];
-  v = block_sum(v, sh);
-  if (threadIdx.x == 0) {
-    const A b0 = sqrt(v);
-    st->beta[0] = b0;
-    st->m = 0;
-    st->rel_change = A(1);
-    st->converged = 0;
-    st->nonfinite = !isfinite(b0);
-    st->done = (b0 == A(0)) || !isfinite(b0);
-    if (b0 == A(0)) st->converged = 1;
-    st->inv_beta = b0 > A(0) ? A(1) / b0 : A(0);
-  }
-}
-
-template <typename A>
-__global__ void k_lz_init(const A *__restrict__ partials, int nparts, LzState<A> *st) {
-  lz_init_body<A>(partials, nparts, st);
-}
-
-// w = t - alpha_m v_m - beta_m v_{m-1}, one particle (x, y, z, 0) per
-// step; block partials of |w|^2.
-// alpha_m = <v_m, t> of the step.  k_lz_alpha_part writes block partial
-// sums; lz_alpha (inside the update kernels) adds them in a fixed order in
-// every block, and block 0 stores alpha_m.  Computed here rather than in
-// the LDS product's epilogue: without the reduction the product needs no
-// register spills (64 VGPRs), which costs far more than this extra pass
-// over two vectors.
-template <typename T, typename A>
-__global__ void k_lz_alpha_part(const typename vec4<T>::type *__restrict__ t,
-                                const typename vec4<T>::type *__restrict__ vm, int n, const LzState<A> *st,
-                                A *__restrict__ partials) {
-  __shared__ A sh[16];
-  if (st->done) return;
-  A v = 0;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    const auto a = t[i], b = vm[i];
-    v += (A)a.x * (A)b.x + (A)a.y * (A)b.y + (A)a.z * (A)b.z;
-  }
-  v = block_sum(v, sh);
-  if (threadIdx.x == 0) partials[blockIdx.x] = v;
-}
-
-template <typename A> __device__ A lz_alpha(LzState<A> *st, const A *apart, int napart, A *sh, bool store) {
-  __shared__ A alpha_s;
-  if (!apart) return st->alpha[st->m];
-  A v = 0;
-  for (int i = threadIdx.x; i < napart; i += blockDim.x) v += apart[i];
-  v = block_sum(v, sh);
-  if (threadIdx.x == 0) {
-    alpha_s = v;
-    if (store) st->alpha[st->m] = v;
-  }
-  __syncthreads();
-  return alpha_s;
-}
-
-template <typename T, typename A>
-__global__ void k_lz_update(const typename vec4<T>::type *__restrict__ t, const typename vec4<T>::type *__restrict__ vm,
-                            const typename vec4<T>::type *__restrict__ vprev, typename vec4<T>::type *__restrict__ w,
-                            int n, LzState<A> *st, A *__restrict__ partials, const A *__restrict__ apart = nullptr,
-                            int napart = 0) {
-  __shared__ A sh[16];
-  if (st->done) return;
-  const int m = st->m;
-  const T al = (T)lz_alpha(st, apart, napart, sh, blockIdx.x == 0);
-  const T be = m > 0 ? (T)st->beta[m] : T(0);
-  A v = 0;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    const auto a = t[i], b = vm[i];
-    typename vec4<T>::type x;
-    x.x = a.x - al * b.x;
-    x.y = a.y - al * b.y;
-    x.z = a.z - al * b.z;
-    if (m > 0) {
-      const auto c = vprev[i];
-      x.x -= be * c.x;
-      x.y -= be * c.y;
-      x.z -= be * c.z;
-    }
-    x.w = T(0);
-    w[i] = x;
-    v += (A)x.x * (A)x.x + (A)x.y * (A)x.y + (A)x.z * (A)x.z;
-  }
-  v = block_sum(v, sh);
-  if (threadIdx.x == 0) partials[blockIdx.x] = v;
-}
-
-// Preconditioned variant, per particle: w as above, and u = P^T w, the
-// source of the next product (P rows as (x, y, z, 0), 12 values each).
-template <typename T, typename A>
-__global__ void k_lz_update_pc(const typename vec4<T>::type *__restrict__ t,
-                               const typename vec4<T>::type *__restrict__ vm,
-                               const typename vec4<T>::type *__restrict__ vprev, typename vec4<T>::type *__restrict__ w,
-                               const T *__restrict__ P, typename vec4<T>::type *__restrict__ u, int n,
-                               LzState<A> *st, A *__restrict__ partials, const A *__restrict__ apart = nullptr,
-                               int napart = 0) {
-  __shared__ A sh[16];
-  if (st->done) return;
-  const int m = st->m;
-  const T al = (T)lz_alpha(st, apart, napart, sh, blockIdx.x == 0);
-  const T be = m > 0 ? (T)st->beta[m] : T(0);
-  A v = 0;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    const auto a = t[i], b = vm[i];
-    typename vec4<T>::type x;
-    x.x = a.x - al * b.x;
-    x.y = a.y - al * b.y;
-    x.z = a.z - al * b.z;
-    if (m > 0) {
-      const auto c = vprev[i];
-      x.x -= be * c.x;
-      x.y -= be * c.y;
-      x.z -= be * c.z;
-    }
-    x.w = T(0);
-    w[i] = x;
-    v += (A)x.x * (A)x.x + (A)x.y * (A)x.y + (A)x.z * (A)x.z;
-    const auto *pr = (const typename vec4<T>::type *)(P + (size_t)i * 12);  // rows of P_i
-    const auto r0 = pr[0], r1 = pr[1], r2 = pr[2];
-    typename vec4<T>::type o;
-    o.x = r0.x * x.x + r1.x * x.y + r2.x * x.z;
-    o.y = r0.y * x.x + r1.y * x.y + r2.y * x.z;
-    o.z = r0.z * x.x + r1.z * x.y + r2.z * x.z;
-    o.w = T(0);
-    u[i] = o;
-  }
-  v = block_sum(v, sh);
-  if (threadIdx.x == 0) partials[blockIdx.x] = v;
+__device__ __forceinline__ void lz_coef(const LzState<A> *st, int m, A al, T &c1, T &c2, T &c3) {
+  const int e = -lz_exponent(al);
+  c1 = (T)ldexp(st->rs[m], e);
+  c2 = (T)ldexp(al * st->rs[m], e);
+  c3 = m > 0 ? (T)ldexp(st->beta[m] * st->rs[m - 1], e) : T(0);
 }
 
 // Value of v in lane i (wave-uniform i) as a scalar.
-__device__ __forceinline__ float lane_value(float v, int i) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i));
-}
 __device__ __forceinline__ double lane_value(double v, int i) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), i),
                           __builtin_amdgcn_readlane(__double2loint(v), i));
@@ -1386,13 +1234,6 @@ __device__ __forceinline__ double lane_value(double v, int i) {
 // r = sqrt(x) and ri = 1 / sqrt(x) for normal x > 0: the hardware estimate
 // of 1 / sqrt(x), refined by the coupled Newton iteration g -> sqrt(x),
 // h -> 1 / (2 sqrt(x)) to within about an ulp.
-__device__ __forceinline__ void sqrt_pair(float x, float &r, float &ri) {
-  const float y = __builtin_amdgcn_rsqf(x);
-  float g = x * y, h = 0.5f * y;
-  const float d = fmaf(-h, g, 0.5f);
-  r = fmaf(g, d, g);
-  ri = 2.0f * fmaf(h, d, h);
-}
 __device__ __forceinline__ void sqrt_pair(double x, double &r, double &ri) {
   const double y = __builtin_amdgcn_rsq(x);
   double g = x * y, h = 0.5 * y;
@@ -1406,25 +1247,84 @@ __device__ __forceinline__ void sqrt_pair(double x, double &r, double &ri) {
   ri = 2.0 * h;
 }
 
-// s = T^{1/2} e_1 for the n x n tridiagonal T (diag d, off-diagonal e with
-// e[i] coupling i, i+1), by implicit QL with Wilkinson-type shifts.  One
-// wavefront: lane j holds d[j], e[j]; lane k owns row k of the eigenvector
-// matrix Q (stored column-major in LDS).  Returns s_k in lane k.
-// A serial chain of rotations bounds it, so each rotation is kept short:
+// 1 / x by the hardware estimate and two Newton steps (about an ulp).
+__device__ __forceinline__ double rcp_newton(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+
+// s = T^{1/2} e_1 for the n x n tridiagonal T (lane j holds the diagonal d[j]
+// and e[j], which couples j and j + 1), by the quadrature
+//   lambda^{1/2} = sum_j w_j lambda / (lambda + t_j),   lambda in [1e-13, 1]
+// (lz_quadrature; relative error 2e-15 there): lane j solves
+// (T + t_j) x_j = T e_1 and s = sum_j w_j x_j.  T is scaled by an even power of
+// two so that its Gershgorin bound lies in (1/4, 1].  Eliminating from the last
+// row up leaves one stored factor per row: with pivots D_i, r_i = 1 / D_i,
+//   x_0 = (D_0 - t) r_0,  x_1 = e_0 t r_0 r_1,  x_i = -e_{i-1} r_i x_{i-1}.
+// A step of the elimination is one reciprocal and two FMAs for all nodes at
+// once: about a microsecond at five rows, where the eigen-decomposition's
+// chain of rotations took 10 (22 at eight rows).  False when some pivot
+// is not positive (T indefinite to rounding, or not finite): the
+// caller then takes the eigen-decomposition, which clamps.  X: 64 n values.
+__device__ __forceinline__ bool tridiag_root_quadrature(int n, double d, double e, const double2 *__restrict__ nodes,
+                                                        double *X, double &s) {
+  const int lane = threadIdx.x & 63;
+  const double2 tw = nodes[lane];
+  const double el = __shfl_up(e, 1, 64), g = fabs(d) + fabs(e) + (lane ? fabs(el) : 0.0);
+  double bound = 0.0;
+  for (int j = 0; j < n; ++j) bound = fmax(bound, lane_value(g, j));
+  if (!(bound > 0.0) || !isfinite(bound)) return false;
+  int ex = ilogb(bound) + 1;
+  ex += ex & 1;
+  d = ldexp(d, -ex);
+  e = ldexp(e, -ex);
+  double D = lane_value(d, n - 1), r = 0.0;
+  bool pos = true;
+  for (int i = n - 1; i > 0; --i) {
+    const double Dt = D + tw.x, ei = lane_value(e, i - 1);
+    pos = pos && Dt > 0.0;
+    r = rcp_newton(Dt);
+    X[i * 64 + lane] = r;
+    D = fma(-ei * ei, r, lane_value(d, i - 1));
+  }
+  pos = pos && D + tw.x > 0.0;
+  if (!__all(pos)) return false;
+  const double r0 = rcp_newton(D + tw.x);
+  X[lane] = tw.y * D * r0;
+  double x = lane_value(e, 0) * (tw.y * tw.x * r0) * r;  // r = r_1 here
+  for (int i = 1; i < n; ++i) {
+    if (i > 1) x *= -lane_value(e, i - 1) * X[i * 64 + lane];
+    X[i * 64 + lane] = x;
+  }
+  // lane k sums row k over the nodes (rotated columns: no bank conflicts)
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
+  if (lane < n) {
+    for (int j = 0; j < 64; j += 4)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) a[u] += X[lane * 64 + ((j + u + lane) & 63)];
+  }
+  s = ldexp((a[0] + a[1]) + (a[2] + a[3]), ex / 2);
+  return true;
+}
+
+// The same by implicit QL with Wilkinson-type shifts, negative eigenvalues
+// taken as 0.  Lane k owns row k of the eigenvector matrix Q (stored
+// column-major in LDS).  Returns s_k in lane k.
+// double serial chain of rotations bounds it, so each rotation is kept short:
 // uniform values are read from their lane as scalars instead of through LDS
 // permutes, one reciprocal square root gives r, 1/r and with them the sine
 // and cosine (no hypot, no divisions), the deflation test looks at every
 // lane at once, and the updated column of Q stays in a register for the
 // next rotation.  T is scaled by a power of two to diagonal entries of order
 // 1, which keeps f^2 + g^2 in range.
-template <typename A>
-__device__ A tridiag_sqrt_e1(int n, A d, A e, A *Q, int &ok) {
+__device__ double tridiag_root_ql(int n, double d, double e, double *Q, int &ok) {
   const int lane = threadIdx.x & 63;
-  const A eps = sizeof(A) == 8 ? A(2.2e-16) : A(1.2e-7), tiny = sizeof(A) == 8 ? A(1e-290) : A(1e-35);
-  for (int j = 0; j < n; ++j) Q[j * 64 + lane] = (lane == j) ? A(1) : A(0);
+  const double eps = 2.2e-16, tiny = 1e-290;
+  for (int j = 0; j < n; ++j) Q[j * 64 + lane] = (lane == j) ? 1.0 : 0.0;
   ok = 1;
-  const A d0 = lane_value(d, 0);
-  int ex = d0 > A(0) && isfinite(d0) ? ilogb(d0) : 0;
+  const double d0 = lane_value(d, 0);
+  int ex = d0 > 0.0 && isfinite(d0) ? ilogb(d0) : 0;
   ex -= ex & 1;  // even: the square root's scale is a power of two too
   d = ldexp(d, -ex);
   e = ldexp(e, -ex);
@@ -1432,7 +1332,7 @@ __device__ A tridiag_sqrt_e1(int n, A d, A e, A *Q, int &ok) {
     int iter = 0;
     while (true) {
       // the first negligible off-diagonal entry at or after l
-      const A ad = fabs(d), an = __shfl_down(ad, 1, 64);
+      const double ad = fabs(d), an = __shfl_down(ad, 1, 64);
       const bool cut = lane >= n - 1 || fabs(e) <= eps * (ad + an);
       const unsigned long long cuts = __ballot(cut) >> l;
       const int mm = l + (cuts ? __ffsll((long long)cuts) - 1 : 0);
@@ -1441,35 +1341,35 @@ __device__ A tridiag_sqrt_e1(int n, A d, A e, A *Q, int &ok) {
         ok = 0;
         break;
       }
-      const A dl = lane_value(d, l), el = lane_value(e, l);
-      A g = (lane_value(d, l + 1) - dl) / (A(2) * el);
-      A r = sqrt(g * g + A(1));
+      const double dl = lane_value(d, l), el = lane_value(e, l);
+      double g = (lane_value(d, l + 1) - dl) / (2.0 * el);
+      double r = sqrt(g * g + 1.0);
       g = lane_value(d, mm) - dl + el / (g + copysign(r, g));
-      A s = 1, c = 1, p = 0;
+      double s = 1, c = 1, p = 0;
       bool early = false;
-      A q1 = Q[mm * 64 + lane], dn = lane_value(d, mm);
+      double q1 = Q[mm * 64 + lane], dn = lane_value(d, mm);
       for (int i = mm - 1; i >= l; --i) {
-        const A qi = Q[i * 64 + lane];
-        const A ei = lane_value(e, i), di = lane_value(d, i);
-        const A f = s * ei, b = c * ei;
-        const A h2 = f * f + g * g;
+        const double qi = Q[i * 64 + lane];
+        const double ei = lane_value(e, i), di = lane_value(d, i);
+        const double f = s * ei, b = c * ei;
+        const double h2 = f * f + g * g;
         if (h2 < tiny) {
           if (lane == i + 1) {
-            e = A(0);
+            e = 0.0;
             d = dn - p;
           }
-          if (lane == mm) e = A(0);
+          if (lane == mm) e = 0.0;
           early = true;
           Q[(i + 1) * 64 + lane] = q1;
           break;
         }
-        A ri;
+        double ri;
         sqrt_pair(h2, r, ri);
         if (lane == i + 1) e = r;
         s = f * ri;
         c = g * ri;
         g = dn - p;
-        r = (di - g) * s + A(2) * c * b;
+        r = (di - g) * s + 2.0 * c * b;
         p = s * r;
         if (lane == i + 1) d = g + p;
         g = c * r - b;
@@ -1483,73 +1383,254 @@ __device__ A tridiag_sqrt_e1(int n, A d, A e, A *Q, int &ok) {
         d = dn - p;
         e = g;
       }
-      if (lane == mm) e = A(0);
+      if (lane == mm) e = 0.0;
     }
     if (!ok) break;
   }
   __builtin_amdgcn_wave_barrier();
-  const A root = sqrt(d > A(0) ? d : A(0));
-  A acc = 0;
+  const double root = sqrt(d > 0.0 ? d : 0.0);
+  double acc = 0;
   for (int j = 0; j < n; ++j) acc += Q[j * 64 + lane] * lane_value(root, j) * Q[j * 64];
   return ldexp(acc, ex / 2);
 }
 
-// After iteration m: beta_{m+1} = |w|, s = T_{m+1}^{1/2} e_1, convergence test
-// |s_{m+1} - s_m| <= tol |s_{m+1}| (successive iterates; V orthonormal), and
-// the scale 1/beta_{m+1} of the next Lanczos vector.  One wavefront.
+// After iteration m: beta_{m+1} (from the partial sums of |u_{m+1}|^2, or set
+// already by k_lz_step when nparts is 0), s = T_{m+1}^{1/2} e_1, and the
+// convergence test |s_{m+1} - s_m| <= tol |s_{m+1}| (successive iterates; V
+// orthonormal), in FP64 for every Lanczos scalar type.  The first wavefront
+// of a workgroup, all of whose threads call it.
 template <typename A>
-__device__ __forceinline__ void lz_check_body(const A *__restrict__ partials, int nparts, LzState<A> *st, A tol,
-                                              int max_iter) {
-  __shared__ A Q[kMaxIter * 64];
-  if (st->done) return;
+__device__ __forceinline__ void lz_check_body(const A *__restrict__ partials, int nparts, LzState<A> *st, int m, A tol,
+                                              int max_iter, const double2 *__restrict__ nodes) {
+  __shared__ double Q[kMaxIter * 64];
+  if (threadIdx.x >= 64 || st->done) return;
   const int lane = threadIdx.x;
-  // eight interleaved sums keep eight loads in flight (fixed order)
-  A vs[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  int i = lane;
-  for (; i + 7 * 64 < nparts; i += 8 * 64) {
+  A bb;
+  if (nparts > 0) {
+    // eight interleaved sums keep eight loads in flight (fixed order)
+    A vs[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    int i = lane;
+    for (; i + 7 * 64 < nparts; i += 8 * 64) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) vs[u] += partials[i + u * 64];
+      for (int u = 0; u < 8; ++u) vs[u] += partials[i + u * 64];
+    }
+    for (; i < nparts; i += 64) vs[0] += partials[i];
+    A v = ((vs[0] + vs[1]) + (vs[2] + vs[3])) + ((vs[4] + vs[5]) + (vs[6] + vs[7]));
+    v = wave_sum(v);
+    if (lane == 0) lz_set_beta(st, m, v);
+    bb = ldexp(sqrt(v), lz_exponent(st->alpha[m]));
+  } else {
+    bb = st->beta[m + 1];
   }
-  for (; i < nparts; i += 64) vs[0] += partials[i];
-  A v = ((vs[0] + vs[1]) + (vs[2] + vs[3])) + ((vs[4] + vs[5]) + (vs[6] + vs[7]));
-  v = wave_sum(v);
-  const A bb = sqrt(v);
-  const int m = st->m;
   const int nn = m + 1;
-  A d = lane < nn ? st->alpha[lane] : A(0);
-  A e = lane < nn - 1 ? st->beta[lane + 1] : A(0);
-  int ok;
-  const A sk = tridiag_sqrt_e1<A>(nn, d, e, Q, ok);
-  const A sold = (lane < m) ? st->s[lane] : A(0);
-  const A dif = lane < nn ? (sk - sold) : A(0);
-  A num = 0, den = 0, scale2 = 0;
+  const double d = lane < nn ? (double)st->alpha[lane] : 0.0;
+  const double e = lane < nn - 1 ? (double)st->beta[lane + 1] : 0.0;
+  int ok = 1;
+  double sk = 0.0;
+  if (!tridiag_root_quadrature(nn, d, e, nodes, Q, sk)) sk = tridiag_root_ql(nn, d, e, Q, ok);
+  const double sold = lane < m ? (double)st->s[lane] : 0.0;
+  const double dif = lane < nn ? sk - sold : 0.0;
+  double num = 0.0, den = 0.0, scale2 = 0.0;
   for (int j = 0; j < nn; ++j) {
-    const A dj = lane_value(dif, j), sj = lane_value(sk, j), aj = lane_value(d, j);
+    const double dj = lane_value(dif, j), sj = lane_value(sk, j), aj = lane_value(d, j);
     num += dj * dj;
     den += sj * sj;
     scale2 += aj * aj;
   }
-  const A rel = den > A(0) ? sqrt(num / den) : A(0);
-  const A bdn = (sizeof(A) == 8 ? A(1e-11) : A(1e-6)) * sqrt(scale2 + bb * bb);
+  const double rel = den > 0.0 ? sqrt(num / den) : 0.0;
+  const double bdn = (sizeof(A) == 8 ? 1e-11 : 1e-6) * sqrt(scale2 + (double)bb * (double)bb);
   const bool finite = isfinite(bb) && isfinite(den) && ok;
-  if (lane < nn) st->s[lane] = sk;
-  __builtin_amdgcn_wave_barrier();
+  if (lane < nn) st->s[lane] = (A)sk;
   if (lane == 0) {
-    st->beta[nn] = bb;
-    st->rel_change = m > 0 ? rel : A(1);
+    st->rel_change = m > 0 ? (A)rel : A(1);
     st->m = nn;
-    const bool conv = (m > 0 && rel <= tol) || (bb <= bdn);
+    const bool conv = (m > 0 && rel <= (double)tol) || ((double)bb <= bdn);
     st->converged = conv && finite;
     st->nonfinite = !finite;
     st->done = conv || !finite || nn >= max_iter;
-    st->inv_beta = bb > A(0) ? A(1) / bb : A(0);
   }
 }
 
 template <typename A>
-__global__ __launch_bounds__(64) void k_lz_check(const A *__restrict__ partials, int nparts, LzState<A> *st, A tol,
-                                                 int max_iter) {
-  lz_check_body<A>(partials, nparts, st, tol, max_iter);
+__global__ __launch_bounds__(64) void k_lz_check(const A *__restrict__ partials, int nparts, LzState<A> *st, int m,
+                                                 A tol, int max_iter, const double2 *__restrict__ nodes) {
+  lz_check_body<A>(partials, nparts, st, m, tol, max_iter, nodes);
+}
+
+// Sum of nparts partial sums in a fixed order, valid in every thread of
+// the workgroup.
+template <typename A> __device__ A lz_parts_sum(const A *parts, int nparts, A *sh) {
+  __shared__ A all;
+  A v = 0;
+  for (int i = threadIdx.x; i < nparts; i += blockDim.x) v += parts[i];
+  v = block_sum(v, sh);
+  if (threadIdx.x == 0) all = v;
+  __syncthreads();
+  return all;
+}
+
+// Block partial sums of |z|^2 (sorted order).
+template <typename T, typename A>
+__global__ __launch_bounds__(256) void k_lz_norm(const typename vec4<T>::type *__restrict__ z, int n,
+                                                 A *__restrict__ partials) {
+  __shared__ A sh[16];
+  A v = 0;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    const auto a = z[i];
+    v = dot3(v, a, a);
+  }
+  v = block_sum(v, sh);
+  if (threadIdx.x == 0) partials[blockIdx.x] = v;
+}
+
+// Block partial sums of <u_m, t>.  Computed here rather than in the LDS
+// product's epilogue: without the reduction the product needs no register
+// spills (64 VGPRs), which costs far more than this extra pass over two
+// vectors.  The workgroup past the nparts partial sums, if launched, starts
+// the state (m = 0, from the partial sums of |z|^2) or checks iteration m - 1.
+template <typename T, typename A>
+__device__ __forceinline__ void lz_alpha_block(const typename vec4<T>::type *__restrict__ t,
+                                               const typename vec4<T>::type *__restrict__ u, int n, LzState<A> *st,
+                                               bool test, A *__restrict__ apart, int blk, int nparts) {
+  __shared__ A sh[16];
+  if (test && st->done) return;
+  A v = 0;
+#pragma unroll 4
+  for (int i = blk * blockDim.x + threadIdx.x; i < n; i += nparts * blockDim.x) v = dot3(v, t[i], u[i]);
+  v = block_sum(v, sh);
+  if (threadIdx.x == 0) apart[blk] = v;
+}
+template <typename A>
+__device__ __forceinline__ void lz_side_block(const A *__restrict__ partials, int nparts, LzState<A> *st, int m, A tol,
+                                              int max_iter, const double2 *__restrict__ nodes) {
+  __shared__ A sh[16];
+  if (m == 0) {
+    const A z2 = lz_parts_sum(partials, nparts, sh);
+    if (threadIdx.x == 0) lz_begin(st, z2);
+  } else {
+    lz_check_body<A>(partials, nparts, st, m - 1, tol, max_iter, nodes);
+  }
+}
+
+template <typename T, typename A>
+__global__ __launch_bounds__(256) void k_lz_alpha(const typename vec4<T>::type *__restrict__ t,
+                                                  const typename vec4<T>::type *__restrict__ u, int n, LzState<A> *st,
+                                                  int m, A *__restrict__ partials, int nparts, A tol, int max_iter,
+                                                  const double2 *__restrict__ nodes) {
+  // (beside a check, which may set `done` meanwhile, the flag is not tested:
+  // the sums of a finished process are not used)
+  if ((int)blockIdx.x < nparts)
+    lz_alpha_block<T, A>(t, u, n, st, (int)gridDim.x == nparts, partials + kRedBlock, blockIdx.x, nparts);
+  else
+    lz_side_block<A>(partials, nparts, st, m, tol, max_iter, nodes);
+}
+
+// alpha_m from its partial sums (every workgroup; block 0 stores it),
+// u_{m+1} into the next basis slot and the block partial sums of its square.
+// With P (rows as (x, y, z, 0), 12 values each) also up = P^T u_{m+1}, the
+// source of the next preconditioned product.
+template <typename T, typename A>
+__device__ __forceinline__ void lz_update_block(const typename vec4<T>::type *__restrict__ t,
+                                                typename vec4<T>::type *__restrict__ V, int n, LzState<A> *st, int m,
+                                                A *__restrict__ partials, int blk, int nparts,
+                                                const T *__restrict__ P, typename vec4<T>::type *__restrict__ up) {
+  using T4 = typename vec4<T>::type;
+  __shared__ A sh[16];
+  if (st->done) return;
+  const A rs = st->rs[m];
+  const A al = lz_parts_sum(partials + kRedBlock, nparts, sh) * rs * rs;
+  if (blk == 0 && threadIdx.x == 0) st->alpha[m] = al;
+  T c1, c2, c3;
+  lz_coef<T, A>(st, m, al, c1, c2, c3);
+  const T4 *u = V + (size_t)m * n, *uprev = m > 0 ? u - n : nullptr;
+  T4 *un = V + (size_t)(m + 1) * n;
+  A v = 0;
+#pragma unroll 2
+  for (int i = blk * blockDim.x + threadIdx.x; i < n; i += nparts * blockDim.x) {
+    const T4 x = lz_next<T4, T>(t[i], u[i], uprev, i, c1, c2, c3);
+    un[i] = x;
+    v = dot3(v, x, x);
+    if (P) {
+      const T4 *pr = (const T4 *)(P + (size_t)i * 12);  // rows of P_i
+      const T4 r0 = pr[0], r1 = pr[1], r2 = pr[2];
+      T4 o;
+      o.x = r0.x * x.x + r1.x * x.y + r2.x * x.z;
+      o.y = r0.y * x.x + r1.y * x.y + r2.y * x.z;
+      o.z = r0.z * x.x + r1.z * x.y + r2.z * x.z;
+      o.w = T(0);
+      up[i] = o;
+    }
+  }
+  v = block_sum(v, sh);
+  if (threadIdx.x == 0) partials[blk] = v;
+}
+
+template <typename T, typename A>
+__global__ __launch_bounds__(256) void k_lz_update(const typename vec4<T>::type *__restrict__ t,
+                                                   typename vec4<T>::type *__restrict__ V, int n, LzState<A> *st, int m,
+                                                   A *__restrict__ partials, int nparts, const T *__restrict__ P,
+                                                   typename vec4<T>::type *__restrict__ up) {
+  lz_update_block<T, A>(t, V, n, st, m, partials, blockIdx.x, nparts, P, up);
+}
+
+// Vector work and check of iteration m in one workgroup of 1024 lanes: 64 n
+// bytes (FP32 storage) through one compute unit against two or three launches
+// whose time is launch and reduction latency (4 to 5 us each).  The bound
+// kLzStepMax is where the two meet: 7 us at 1000 particles, 12.7 at 8000,
+// against 10 to 14.
+template <typename T, typename A>
+__device__ __forceinline__ void lz_step_block(const typename vec4<T>::type *__restrict__ t,
+                                              typename vec4<T>::type *__restrict__ V, int n, LzState<A> *st, int m,
+                                              A tol, int max_iter, const double2 *__restrict__ nodes) {
+  using T4 = typename vec4<T>::type;
+  __shared__ A sh[16];
+  __shared__ A al_s;
+  __shared__ int stop;
+  if (threadIdx.x == 0) stop = 0;
+  if (m > 0 && st->done) return;
+  const T4 *u = V + (size_t)m * n, *uprev = m > 0 ? u - n : nullptr;
+  T4 *un = V + (size_t)(m + 1) * n;
+  if (m == 0) {
+    A z2 = 0;
+#pragma unroll 4
+    for (int i = threadIdx.x; i < n; i += 1024) z2 = dot3(z2, u[i], u[i]);
+    z2 = block_sum(z2, sh);
+    if (threadIdx.x == 0) {
+      lz_begin(st, z2);
+      stop = st->done;
+    }
+  }
+  A v = 0;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < n; i += 1024) v = dot3(v, t[i], u[i]);
+  v = block_sum(v, sh);
+  if (threadIdx.x == 0) {
+    const A al = v * st->rs[m] * st->rs[m];
+    st->alpha[m] = al;
+    al_s = al;
+  }
+  __syncthreads();
+  if (stop) return;
+  T c1, c2, c3;
+  lz_coef<T, A>(st, m, al_s, c1, c2, c3);
+  v = 0;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < n; i += 1024) {
+    const T4 x = lz_next<T4, T>(t[i], u[i], uprev, i, c1, c2, c3);
+    un[i] = x;
+    v = dot3(v, x, x);
+  }
+  v = block_sum(v, sh);
+  if (threadIdx.x == 0) lz_set_beta(st, m, v);
+  __syncthreads();
+  lz_check_body<A>(nullptr, 0, st, m, tol, max_iter, nodes);
+}
+
+template <typename T, typename A>
+__global__ __launch_bounds__(1024) void k_lz_step(const typename vec4<T>::type *__restrict__ t,
+                                                  typename vec4<T>::type *__restrict__ V, int n, LzState<A> *st, int m,
+                                                  A tol, int max_iter, const double2 *__restrict__ nodes) {
+  lz_step_block<T, A>(t, V, n, st, m, tol, max_iter, nodes);
 }
 
 // ------------------------------------------------- batched Krylov loop
@@ -1560,14 +1641,16 @@ __global__ __launch_bounds__(64) void k_lz_check(const A *__restrict__ partials,
 // product's blocks of B^3 cells, and the vector kernels' blocks of 256
 // particles (n <= kRedBlock 256 per system, so that each thread owns at most
 // one particle, as in the single-system kernels).
+__device__ __forceinline__ int lz_parts(int n) { return min(kRedBlock, (n + 255) / 256); }
+
 template <int B, bool UNWRAP, typename A, int G>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_spmv_lds_batch(
     const LzRep<A> *__restrict__ reps, const int2 *__restrict__ pmap, int m) {
   const int2 rb = pmap[blockIdx.x];
   const LzRep<A> &r = reps[rb.x];
-  spmv_lds_block<B, UNWRAP, A, true, false, G>(r.pos, m == 0 ? r.z : r.w, r.cell_start, r.nc, r.cs, r.n, r.hcap,
-                                               r.L, r.invL, r.nbr, r.cnt, r.tab, r.inv_dr, r.self_r, 1.0f, r.t,
-                                               r.V + (size_t)m * r.n, r.st, r.ovf, nullptr, nullptr, rb.y);
+  spmv_lds_block<B, UNWRAP, false, G>(r.pos, r.V + (size_t)m * r.n, r.cell_start, r.nc, r.cs, r.n, r.hcap, r.L, r.invL,
+                                      r.nbr, r.cnt, r.tab, r.inv_dr, r.self_r, r.t, m > 0 ? &r.st->done : nullptr,
+                                      r.ovf, nullptr, rb.y);
 }
 
 // M_r F of the systems whose record carries forces (the others' blocks exit)
@@ -1577,93 +1660,77 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
   const int2 rb = pmap[blockIdx.x];
   const LzRep<A> &r = reps[rb.x];
   if (!r.fs) return;
-  spmv_lds_block<B, UNWRAP, A, false, false, G>(r.pos, r.fs, r.cell_start, r.nc, r.cs, r.n, r.hcap, r.L, r.invL,
-                                                r.nbr, r.cnt, r.tab, r.inv_dr, r.self_r, 1.0f, r.ur, nullptr, nullptr,
-                                                r.ovf, nullptr, nullptr, rb.y);
+  spmv_lds_block<B, UNWRAP, false, G>(r.pos, r.fs, r.cell_start, r.nc, r.cs, r.n, r.hcap, r.L, r.invL, r.nbr, r.cnt,
+                                      r.tab, r.inv_dr, r.self_r, r.ur, nullptr, r.ovf, nullptr, rb.y);
 }
 
 template <typename A>
-__global__ __launch_bounds__(256) void k_lz_alpha_batch(const LzRep<A> *__restrict__ reps,
-                                                        const int2 *__restrict__ vmap, int m) {
-  __shared__ A sh[16];
-  const int2 rb = vmap[blockIdx.x];
-  const LzRep<A> &r = reps[rb.x];
-  if (r.st->done) return;
-  const float4 *vm = r.V + (size_t)m * r.n;
-  A *part = r.partials + kRedBlock;
-  A v = 0;
-  const int i = rb.y * 256 + (int)threadIdx.x;
-  if (i < r.n) {
-    const float4 a = r.t[i], b = vm[i];
-    v += (A)a.x * (A)b.x + (A)a.y * (A)b.y + (A)a.z * (A)b.z;
+__global__ __launch_bounds__(256) void k_lz_alpha_batch(const LzRep<A> *__restrict__ reps, LzVecMaps vm, int m) {
+  if ((int)blockIdx.x < vm.nv) {
+    const int2 rb = vm.vmap[blockIdx.x];
+    const LzRep<A> &r = reps[rb.x];
+    lz_alpha_block<float, A>(r.t, r.V + (size_t)m * r.n, r.n, r.st, m > 0, r.partials + kRedBlock, rb.y, lz_parts(r.n));
+  } else {
+    const LzRep<A> &r = reps[vm.big[blockIdx.x - vm.nv]];
+    lz_side_block<A>(r.partials, lz_parts(r.n), r.st, 0, r.tol, r.maxit, r.nodes);
   }
-  v = block_sum(v, sh);
-  if (threadIdx.x == 0) part[rb.y] = v;
-  if (rb.y == 0)  // the blocks past the system's particles hold 0, as a single-system launch writes them
-    for (int k = (r.n + 255) / 256 + (int)threadIdx.x; k < kRedBlock; k += 256) part[k] = A(0);
 }
 
 template <typename A>
-__global__ __launch_bounds__(256) void k_lz_update_batch(const LzRep<A> *__restrict__ reps,
-                                                         const int2 *__restrict__ vmap, int m) {
-  __shared__ A sh[16];
-  const int2 rb = vmap[blockIdx.x];
+__global__ __launch_bounds__(256) void k_lz_update_batch(const LzRep<A> *__restrict__ reps, LzVecMaps vm, int m) {
+  const int2 rb = vm.vmap[blockIdx.x];
   const LzRep<A> &r = reps[rb.x];
-  LzState<A> *st = r.st;
-  if (st->done) return;
-  const int mm = st->m;
-  const float al = (float)lz_alpha(st, r.partials + kRedBlock, kRedBlock, sh, rb.y == 0);
-  const float be = mm > 0 ? (float)st->beta[mm] : 0.0f;
-  const float4 *vm = r.V + (size_t)m * r.n;
-  const float4 *vprev = m > 0 ? r.V + (size_t)(m - 1) * r.n : r.V;
-  A v = 0;
-  const int i = rb.y * 256 + (int)threadIdx.x;
-  if (i < r.n) {
-    const float4 a = r.t[i], b = vm[i];
-    float4 x;
-    x.x = a.x - al * b.x;
-    x.y = a.y - al * b.y;
-    x.z = a.z - al * b.z;
-    if (mm > 0) {
-      const float4 c = vprev[i];
-      x.x -= be * c.x;
-      x.y -= be * c.y;
-      x.z -= be * c.z;
-    }
-    x.w = 0.0f;
-    r.w[i] = x;
-    v += (A)x.x * (A)x.x + (A)x.y * (A)x.y + (A)x.z * (A)x.z;
-  }
-  v = block_sum(v, sh);
-  if (threadIdx.x == 0) r.partials[rb.y] = v;
-  if (rb.y == 0)
-    for (int k = (r.n + 255) / 256 + (int)threadIdx.x; k < kRedBlock; k += 256) r.partials[k] = A(0);
+  lz_update_block<float, A>(r.t, r.V, r.n, r.st, m, r.partials, rb.y, lz_parts(r.n), nullptr, nullptr);
 }
 
-// one wavefront per system
+// the systems of at most kLzStepMax particles
 template <typename A>
-__global__ __launch_bounds__(64) void k_lz_check_batch(const LzRep<A> *__restrict__ reps) {
-  const LzRep<A> &r = reps[blockIdx.x];
-  lz_check_body<A>(r.partials, kRedBlock, r.st, r.tol, r.maxit);
+__global__ __launch_bounds__(1024) void k_lz_step_batch(const LzRep<A> *__restrict__ reps, LzVecMaps vm, int m) {
+  const LzRep<A> &r = reps[vm.small[blockIdx.x]];
+  lz_step_block<float, A>(r.t, r.V, r.n, r.st, m, r.tol, r.maxit, r.nodes);
 }
 
-// y = beta_0 sum_{j < m} V_j s_j  (sorted order, length 3n)
-// one element of y from the coefficients sc[0 .. m)
-template <typename T, typename A>
-__device__ __forceinline__ T lz_combine_at(const T *__restrict__ V, size_t ld, const A *sc, int m, int i) {
-  A acc = 0;
-  for (int j = 0; j < m; ++j) acc += sc[j] * (A)V[(size_t)j * ld + i];
-  return (T)acc;
+// the checks of the larger systems: one wavefront each
+template <typename A>
+__global__ __launch_bounds__(64) void k_lz_check_batch(const LzRep<A> *__restrict__ reps, LzVecMaps vm, int m) {
+  const LzRep<A> &r = reps[vm.big[blockIdx.x]];
+  lz_check_body<A>(r.partials, lz_parts(r.n), r.st, m, r.tol, r.maxit, r.nodes);
 }
 
-template <typename T, typename A>
-__global__ void k_lz_combine(const T *__restrict__ V, size_t ld, int len, const LzState<A> *st, T *__restrict__ y) {
-  __shared__ A sc[kMaxIter];
+// y = beta_0 sum_{j < m} s_j v_j: the coefficients beta_0 s_j rs_j of the basis
+// vectors into sc (all threads), and one particle of y (sorted order).
+template <typename A> __device__ __forceinline__ int lz_combine_coef(const LzState<A> *st, A *sc) {
   const int m = st->m;
-  if (threadIdx.x < (unsigned)m) sc[threadIdx.x] = st->beta[0] * st->s[threadIdx.x];
+  if (threadIdx.x < (unsigned)m) sc[threadIdx.x] = st->beta[0] * st->s[threadIdx.x] * st->rs[threadIdx.x];
   __syncthreads();
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < len; i += gridDim.x * blockDim.x)
-    y[i] = lz_combine_at<T, A>(V, ld, sc, m, i);
+  return m;
+}
+template <typename T, typename A>
+__device__ __forceinline__ typename vec4<T>::type lz_combine_at(const typename vec4<T>::type *__restrict__ V, int n,
+                                                                const A *sc, int m, int i) {
+  A x = 0, y = 0, z = 0;
+#pragma unroll 4
+  for (int j = 0; j < m; ++j) {
+    const auto v = V[(size_t)j * n + i];
+    x += sc[j] * (A)v.x;
+    y += sc[j] * (A)v.y;
+    z += sc[j] * (A)v.z;
+  }
+  typename vec4<T>::type o;
+  o.x = (T)x;
+  o.y = (T)y;
+  o.z = (T)z;
+  o.w = T(0);
+  return o;
+}
+
+template <typename T, typename A>
+__global__ __launch_bounds__(256) void k_lz_combine(const typename vec4<T>::type *__restrict__ V, int n,
+                                                    const LzState<A> *st, typename vec4<T>::type *__restrict__ y) {
+  __shared__ A sc[kMaxIter];
+  const int m = lz_combine_coef<A>(st, sc);
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) y[i] = lz_combine_at<T, A>(V, n, sc, m, i);
 }
 
 // ------------------------------------------------------------- vectors
@@ -1713,21 +1780,19 @@ template <typename T> __global__ void k_advance(T *__restrict__ x, const T *__re
   if (i < len) x[i] += dx[i];
 }
 
-// out[perm[s]] = cr * yr[s] + dt * ur[s] + wv[s]   (null terms omitted;
-// sorted inputs are (x, y, z, 0), the output is caller-order n x 3)
+// out[perm[s]] = cr * y + dt * ur[s] + wv[s]   (y the particle's Krylov
+// sample; null terms omitted; sorted inputs are (x, y, z, 0), the output is
+// caller-order n x 3)
 template <typename T>
-__device__ __forceinline__ void finalize_at(const int *__restrict__ perm, const typename vec4<T>::type *__restrict__ yr,
-                                            T cr, const typename vec4<T>::type *__restrict__ ur, T dt,
-                                            const typename vec4<T>::type *__restrict__ wv, T *__restrict__ out, int n,
-                                            int s) {
-  if (s >= n) return;
+__device__ __forceinline__ void finalize_at(const int *__restrict__ perm, const typename vec4<T>::type *yr, T cr,
+                                            const typename vec4<T>::type *__restrict__ ur, T dt,
+                                            const typename vec4<T>::type *__restrict__ wv, T *__restrict__ out, int s) {
   const int i = perm[s];
   T x = 0, y = 0, z = 0;
   if (yr) {
-    const auto a = yr[s];
-    x += cr * a.x;
-    y += cr * a.y;
-    z += cr * a.z;
+    x += cr * yr->x;
+    y += cr * yr->y;
+    z += cr * yr->z;
   }
   if (ur) {
     const auto a = ur[s];
@@ -1747,10 +1812,30 @@ __device__ __forceinline__ void finalize_at(const int *__restrict__ perm, const 
 }
 
 template <typename T>
-__global__ void k_finalize(const int *__restrict__ perm, const typename vec4<T>::type *__restrict__ yr, T cr,
-                           const typename vec4<T>::type *__restrict__ ur, T dt,
-                           const typename vec4<T>::type *__restrict__ wv, T *__restrict__ out, int n) {
-  finalize_at<T>(perm, yr, cr, ur, dt, wv, out, n, blockIdx.x * blockDim.x + threadIdx.x);
+__global__ __launch_bounds__(256) void k_finalize(const int *__restrict__ perm,
+                                                  const typename vec4<T>::type *__restrict__ yr, T cr,
+                                                  const typename vec4<T>::type *__restrict__ ur, T dt,
+                                                  const typename vec4<T>::type *__restrict__ wv, T *__restrict__ out,
+                                                  int n) {
+  const int s = blockIdx.x * blockDim.x + threadIdx.x;
+  if (s < n) finalize_at<T>(perm, yr ? yr + s : nullptr, cr, ur, dt, wv, out, s);
+}
+
+// the same with y formed here from the basis: one pass less over a vector
+// than a combination of its own (write and read 32 n bytes)
+template <typename T, typename A>
+__global__ __launch_bounds__(256) void k_finalize_krylov(const int *__restrict__ perm,
+                                                         const typename vec4<T>::type *__restrict__ V,
+                                                         const LzState<A> *st, T cr,
+                                                         const typename vec4<T>::type *__restrict__ ur, T dt,
+                                                         const typename vec4<T>::type *__restrict__ wv,
+                                                         T *__restrict__ out, int n) {
+  __shared__ A sc[kMaxIter];
+  const int m = lz_combine_coef<A>(st, sc);
+  const int s = blockIdx.x * blockDim.x + threadIdx.x;
+  if (s >= n) return;
+  const auto y = lz_combine_at<T, A>(V, n, sc, m, s);
+  finalize_at<T>(perm, &y, cr, ur, dt, wv, out, s);
 }
 
 // ------------------------------------------------ Philox noise for z1
@@ -2005,9 +2090,8 @@ void launch_feat_lds(pse_ctx *c) {
   });
 }
 
-template <typename A, bool LZ, bool PC = false>
-static void spmv_lds(pse_ctx *c, const float4 *src, float4 *out, float4 *vm_out, LzState<A> *st,
-                     const float4 *rsrc = nullptr) {
+template <bool PC = false>
+static void spmv_lds(pse_ctx *c, const float4 *src, float4 *out, const int *done = nullptr) {
   const size_t smem = (sizeof(float4) + sizeof(float2)) * (size_t)c->hcap;
   const float L = (float)c->d.L, invL = (float)(1.0 / c->d.L);
   const auto *nb = (const uint16_t *)c->nbr;
@@ -2017,15 +2101,15 @@ static void spmv_lds(pse_ctx *c, const float4 *src, float4 *out, float4 *vm_out,
     allow_lds(kernel, smem);
     kernel<<<c->lds_blocks, 1024, smem, c->stream>>>((const float4 *)c->pos_s, src, c->cell_start, c->d.nc,
                                                       (float)c->d.cs, c->n, c->hcap, L, invL, nb, c->nbr_cnt,
-                                                      c->table, inv_dr, self_r, 1.0f, out, vm_out, st,
-                                                      c->flags + 7, (const float4 *)c->pc_P, rsrc);
+                                                      c->table, inv_dr, self_r, out, done, c->flags + 7,
+                                                      (const float4 *)c->pc_P);
   };
   auto pick = [&](auto g) {
     constexpr int G = decltype(g)::value;
     with_block_edge(c->lds_B, [&](auto b) {
       constexpr int BE = decltype(b)::value;
-      if (unwrap) go(k_spmv_lds<BE, true, A, LZ, PC, G>);
-      else go(k_spmv_lds<BE, false, A, LZ, PC, G>);
+      if (unwrap) go(k_spmv_lds<BE, true, PC, G>);
+      else go(k_spmv_lds<BE, false, PC, G>);
     });
   };
   // lanes per target: 3 built in (the best measured at phi = 0.3 with
@@ -2035,14 +2119,9 @@ static void spmv_lds(pse_ctx *c, const float4 *src, float4 *out, float4 *vm_out,
   else pick(std::integral_constant<int, 3>{});
 }
 
-// The fused Lanczos product (5 of the 6 product launches of a sample) is
-// timed: the Krylov state is initialised from the sorted positions as the
-// start vector (finite, nonzero), so every trial is iteration 0 and writes
-// alpha_0, the basis slot 0 and vbuf[5], scratch that every sample
-// re-initialises or rewrites.
-template <typename A> static pse_status autotune_spmv_impl(pse_ctx *c) {
-  launch_lz_init<float, A>(c, c->pos_s);
-  auto *st = (LzState<A> *)c->lz;
+// The product is timed on the sorted positions as its source (finite) into
+// vbuf[5], scratch that every sample rewrites.
+static pse_status autotune_spmv_impl(pse_ctx *c) {
   hipEvent_t e0, e1;
   if (hipEventCreate(&e0) != hipSuccess) return PSE_ERR_HIP;
   if (hipEventCreate(&e1) != hipSuccess) {
@@ -2054,9 +2133,7 @@ template <typename A> static pse_status autotune_spmv_impl(pse_ctx *c) {
   float tbest = 1e30f, t3 = 1e30f;
   for (int g : {3, 2, 4}) {
     c->tune_spmv_lanes = g;
-    auto launch = [&] {
-      spmv_lds<A, true>(c, (const float4 *)c->pos_s, (float4 *)c->vbuf[5], (float4 *)c->V, st);
-    };
+    auto launch = [&] { spmv_lds(c, (const float4 *)c->pos_s, (float4 *)c->vbuf[5]); };
     launch();  // warm-up
     float t = 1e30f;
     for (int rep = 0; rep < 3; ++rep) {
@@ -2088,168 +2165,125 @@ pse_status autotune_spmv(pse_ctx *c, int32_t *lanes) {
   if (c->dbl || !c->lds_B) return PSE_OK;
   const uint32_t mask = c->prof_mask;
   c->prof_mask = 0;  // the trial launches are not stage time
-  const pse_status st = c->acc_dbl ? autotune_spmv_impl<double>(c) : autotune_spmv_impl<float>(c);
+  const pse_status st = autotune_spmv_impl(c);
   c->prof_mask = mask;
   if (lanes) *lanes = c->tune_spmv_lanes ? c->tune_spmv_lanes : 3;
   return st;
 }
 
-template <typename T, typename A>
-void launch_spmv(pse_ctx *c, const void *src, void *out, bool lz, void *vm_out) {
-  const int n = c->n;
-  const int nb = nblk(n, 256);
-  (void)lz;
-  (void)vm_out;
+template <typename T> static void spmv(pse_ctx *c, const void *src, void *out, const int *done) {
+  const int n = c->n, nb = nblk(n, 256);
   ProfScope ps(c, PSE_STAGE_SPMV);
-  if constexpr (sizeof(T) == 4) {
-    if (c->lds_B) {
-      spmv_lds<A, false>(c, (const float4 *)src, (float4 *)out, nullptr, nullptr);
-      return;
-    }
-  }
   if constexpr (sizeof(T) == 8) {
-    k_spmv_exact<false><<<nb, 256, 0, c->stream>>>(
-        (const double4 *)c->pos_s, c->nbr, c->nbr_cnt, n, c->d.L, 1.0 / c->d.L, c->series, c->p.xi, c->p.a, c->d.mu0,
-        c->small_r2, c->d.self_r, (const double4 *)src, 1.0, (double4 *)out, nullptr, nullptr, nullptr, nullptr);
-  } else {
-    k_spmv_table<float, A, false><<<nb, 256, 0, c->stream>>>(
-        (const float4 *)c->pos_s, c->nbr, c->nbr_cnt, n, (float)c->d.L, (float)(1.0 / c->d.L), c->table,
-        (float)(kTableK / c->p.rcut), (float)c->d.self_r, (const float4 *)src, 1.0f, (float4 *)out, nullptr, nullptr,
-        nullptr, nullptr);
-  }
-}
-
-// Sorted particle vectors are (x, y, z, 0): the reductions and updates run
-// over the flat 4n scalars (the zero lanes stay zero).
-template <typename T, typename A>
-void launch_lz_init(pse_ctx *c, const void *z) {
-  const int len = 4 * c->n;
-  ProfScope ps(c, PSE_STAGE_LANCZOS);
-  k_norm2_partial<T, A><<<kRedBlock, 256, 0, c->stream>>>((const T *)z, len, (A *)c->partials);
-  k_lz_init<A><<<1, 256, 0, c->stream>>>((const A *)c->partials, kRedBlock, (LzState<A> *)c->lz);
-}
-
-// One Lanczos iteration: SpMV (+alpha), update (+|w|^2 partials), check.
-// src = z (m = 0) or the previous residual w.
-template <typename T, typename A>
-void launch_lz_iter(pse_ctx *c, int m, const void *z) {
-  using T4 = typename vec4<T>::type;
-  const int n = c->n, len = 4 * n;
-  T4 *V = (T4 *)c->V;
-  T4 *t = (T4 *)c->vbuf[2];
-  T4 *w = (T4 *)c->vbuf[3];
-  const T4 *src = m == 0 ? (const T4 *)z : w;
-  const int nb = nblk(n, 256);
-  auto *st = (LzState<A> *)c->lz;
-  prof_begin(c, PSE_STAGE_SPMV);
-  if constexpr (sizeof(T) == 8) {
-    k_spmv_exact<true><<<nb, 256, 0, c->stream>>>((const double4 *)c->pos_s, c->nbr, c->nbr_cnt, n, c->d.L,
-                                                   1.0 / c->d.L, c->series, c->p.xi, c->p.a, c->d.mu0, c->small_r2,
-                                                   c->d.self_r, src, 1.0, t, V + (size_t)m * n, st,
-                                                   (double *)c->partials, c->counter);
+    k_spmv_exact<<<nb, 256, 0, c->stream>>>((const double4 *)c->pos_s, c->nbr, c->nbr_cnt, n, c->d.L, 1.0 / c->d.L,
+                                            c->series, c->p.xi, c->p.a, c->d.mu0, c->small_r2, c->d.self_r,
+                                            (const double4 *)src, (double4 *)out, done);
   } else if (c->lds_B) {
-    spmv_lds<A, true>(c, src, t, V + (size_t)m * n, st);
+    spmv_lds(c, (const float4 *)src, (float4 *)out, done);
   } else {
-    k_spmv_table<float, A, true><<<nb, 256, 0, c->stream>>>(
-        (const float4 *)c->pos_s, c->nbr, c->nbr_cnt, n, (float)c->d.L, (float)(1.0 / c->d.L), c->table,
-        (float)(kTableK / c->p.rcut), (float)c->d.self_r, src, 1.0f, t, V + (size_t)m * n, st, (A *)c->partials,
-        c->counter);
+    k_spmv_table<<<nb, 256, 0, c->stream>>>((const float4 *)c->pos_s, c->nbr, c->nbr_cnt, n, (float)c->d.L,
+                                            (float)(1.0 / c->d.L), c->table, (float)(kTableK / c->p.rcut),
+                                            (float)c->d.self_r, (const float4 *)src, (float4 *)out, done);
   }
-  prof_end(c, PSE_STAGE_SPMV);
-  const T4 *vprev = m > 0 ? V + (size_t)(m - 1) * n : V;
+}
+template <typename T> void launch_spmv(pse_ctx *c, const void *src, void *out) { spmv<T>(c, src, out, nullptr); }
+
+// Iteration m; with `check` that of iteration m - 1 goes with it (the systems
+// above kLzStepMax and the preconditioned ones; k_lz_step holds its own).
+template <typename T, typename A> static void lz_iter(pse_ctx *c, int m, bool pc, bool check) {
+  using T4 = typename vec4<T>::type;
+  const int n = c->n, nparts = std::min(kRedBlock, nblk(n, 256));
+  T4 *V = (T4 *)c->V, *t = (T4 *)c->vbuf[2];
+  auto *st = (LzState<A> *)c->lz;
+  const A tol = (A)c->p.lanczos_tol;
+  const int *done = m > 0 ? &st->done : nullptr;
+  if (pc) {
+    // t = P M_r P^T u_m; P^T u_m comes from the previous update (m > 0)
+    T4 *up = (T4 *)c->vbuf[8], *tp = (T4 *)c->vbuf[9];
+    if (m == 0) {
+      ProfScope ps(c, PSE_STAGE_PRECOND);
+      launch_pc_pre<T>(c, V, up);
+    }
+    bool fused = false;
+    if constexpr (sizeof(T) == 4) {
+      if (c->lds_B) {
+        ProfScope ps(c, PSE_STAGE_SPMV);
+        spmv_lds<true>(c, (const float4 *)up, (float4 *)t, done);
+        fused = true;
+      }
+    }
+    if (!fused) {
+      spmv<T>(c, up, tp, done);
+      ProfScope ps(c, PSE_STAGE_PRECOND);
+      launch_pc_post<T>(c, tp, t);
+    }
+  } else {
+    spmv<T>(c, V + (size_t)m * n, t, done);
+  }
   ProfScope ps(c, PSE_STAGE_LANCZOS);
-  if (sizeof(T) == 4 && c->lds_B) {
-    // the LDS product leaves alpha_m to its own pass
-    A *ap = (A *)c->partials + kRedBlock;
-    k_lz_alpha_part<T, A><<<kRedBlock, 256, 0, c->stream>>>(t, V + (size_t)m * n, n, st, ap);
-    k_lz_update<T, A><<<kRedBlock, 256, 0, c->stream>>>(t, V + (size_t)m * n, vprev, w, n, st, (A *)c->partials,
-                                                        ap, kRedBlock);
-  } else {
-    k_lz_update<T, A><<<kRedBlock, 256, 0, c->stream>>>(t, V + (size_t)m * n, vprev, w, n, st, (A *)c->partials);
+  A *part = (A *)c->partials;
+  if (!pc && n <= kLzStepMax) {
+    k_lz_step<T, A><<<1, 1024, 0, c->stream>>>(t, V, n, st, m, tol, c->lz_maxit, c->lz_nodes);
+    return;
   }
-  k_lz_check<A><<<1, 64, 0, c->stream>>>((const A *)c->partials, kRedBlock, st, (A)c->p.lanczos_tol,
-                                         c->lz_maxit);
+  k_lz_alpha<T, A><<<nparts + (m == 0 || check ? 1 : 0), 256, 0, c->stream>>>(t, V + (size_t)m * n, n, st, m, part,
+                                                                             nparts, tol, c->lz_maxit, c->lz_nodes);
+  k_lz_update<T, A><<<nparts, 256, 0, c->stream>>>(t, V, n, st, m, part, nparts, pc ? (const T *)c->pc_P : nullptr,
+                                                   pc ? (T4 *)c->vbuf[8] : nullptr);
 }
 
-// Lanczos step on A = P M_r P^T: u = P^T r, t' = M_r u, then the basis
-// vector, A v_m and alpha_m from t' (k_pc_post), then the usual update and
-// check.  The product runs unconditionally; the other kernels skip once the
-// iteration is done.
-template <typename T, typename A>
-void launch_lz_iter_pc(pse_ctx *c, int m, const void *z) {
-  using T4 = typename vec4<T>::type;
-  T4 *V = (T4 *)c->V;
-  T4 *t = (T4 *)c->vbuf[2];
-  T4 *w = (T4 *)c->vbuf[3];
-  T4 *u = (T4 *)c->vbuf[8];
-  T4 *tp = (T4 *)c->vbuf[9];
-  const T4 *src = m == 0 ? (const T4 *)z : w;
-  if constexpr (sizeof(T) == 4) {
-    if (c->lds_B) {
-      // u = P^T r comes from the previous update (from z at m = 0); P and
-      // alpha_m are applied in the product's epilogue
-      if (m == 0) {
-        ProfScope ps(c, PSE_STAGE_PRECOND);
-        launch_pc_pre<T, A>(c, src, u);
-      }
-      {
-        ProfScope ps(c, PSE_STAGE_SPMV);
-        spmv_lds<A, true, true>(c, (const float4 *)u, (float4 *)t, (float4 *)(V + (size_t)m * c->n),
-                                (LzState<A> *)c->lz, (const float4 *)src);
-      }
-      ProfScope ps(c, PSE_STAGE_LANCZOS);
-      const T4 *vprev = m > 0 ? V + (size_t)(m - 1) * c->n : V;
-      A *ap = (A *)c->partials + kRedBlock;
-      k_lz_alpha_part<T, A><<<kRedBlock, 256, 0, c->stream>>>(t, V + (size_t)m * c->n, c->n, (LzState<A> *)c->lz, ap);
-      k_lz_update_pc<T, A><<<kRedBlock, 256, 0, c->stream>>>(t, V + (size_t)m * c->n, vprev, w, (const T *)c->pc_P,
-                                                             u, c->n, (LzState<A> *)c->lz, (A *)c->partials, ap,
-                                                             kRedBlock);
-      k_lz_check<A><<<1, 64, 0, c->stream>>>((const A *)c->partials, kRedBlock, (LzState<A> *)c->lz,
-                                             (A)c->p.lanczos_tol, c->lz_maxit);
-      return;
+template <typename T, typename A> void launch_lz_norm(pse_ctx *c, bool pc) {
+  if (!pc && c->n <= kLzStepMax) return;
+  ProfScope ps(c, PSE_STAGE_LANCZOS);
+  k_lz_norm<T, A><<<std::min(kRedBlock, nblk(c->n, 256)), 256, 0, c->stream>>>((const typename vec4<T>::type *)c->V,
+                                                                              c->n, (A *)c->partials);
+}
+
+template <typename T, typename A> void launch_lz_iters(pse_ctx *c, int m0, int k, bool pc) {
+  const int nparts = std::min(kRedBlock, nblk(c->n, 256));
+  const bool step = !pc && c->n <= kLzStepMax;
+  if (m0 == 0) launch_lz_norm<T, A>(c, pc);
+  for (int m = m0; m < m0 + k; ++m) {
+    lz_iter<T, A>(c, m, pc, m > m0 && !c->graph);
+    if (step || (!c->graph && m + 1 < m0 + k)) continue;
+    ProfScope ps(c, PSE_STAGE_LANCZOS);
+    k_lz_check<A><<<1, 64, 0, c->stream>>>((const A *)c->partials, nparts, (LzState<A> *)c->lz, m,
+                                           (A)c->p.lanczos_tol, c->lz_maxit, c->lz_nodes);
+  }
+}
+
+// The batched Krylov loop: per iteration the product of every group of
+// systems sharing a block edge, halo form and lanes per target, then the
+// vector work and the checks of all systems.
+template <typename A>
+void launch_lz_batch(hipStream_t s, const LzRep<A> *reps, const LzGroup *groups, int ngroups,
+                     const LzVecMaps &vm, int iters) {
+  for (int m = 0; m < iters; ++m) {
+    for (int g = 0; g < ngroups; ++g) {
+      const LzGroup &gr = groups[g];
+      with_block_edge(gr.B, [&](auto b) {
+        constexpr int BE = decltype(b)::value;
+        auto go = [&](auto kernel) {
+          allow_lds(kernel, gr.smem);
+          kernel<<<gr.nblk, 1024, gr.smem, s>>>(reps, gr.pmap, m);
+        };
+        auto pick = [&](auto gl) {
+          constexpr int GL = decltype(gl)::value;
+          if (gr.unwrap) go(k_spmv_lds_batch<BE, true, A, GL>);
+          else go(k_spmv_lds_batch<BE, false, A, GL>);
+        };
+        if (gr.G == 2) pick(std::integral_constant<int, 2>{});
+        else if (gr.G == 4) pick(std::integral_constant<int, 4>{});
+        else pick(std::integral_constant<int, 3>{});
+      });
+    }
+    if (vm.nsmall) k_lz_step_batch<A><<<vm.nsmall, 1024, 0, s>>>(reps, vm, m);
+    if (vm.nbig) {
+      k_lz_alpha_batch<A><<<vm.nv + (m == 0 ? vm.nbig : 0), 256, 0, s>>>(reps, vm, m);
+      k_lz_update_batch<A><<<vm.nv, 256, 0, s>>>(reps, vm, m);
+      k_lz_check_batch<A><<<vm.nbig, 64, 0, s>>>(reps, vm, m);
     }
   }
-  {
-    ProfScope ps(c, PSE_STAGE_PRECOND);
-    launch_pc_pre<T, A>(c, src, u);
-  }
-  launch_spmv<T, A>(c, u, tp, false, nullptr);
-  ProfScope ps(c, PSE_STAGE_LANCZOS);
-  launch_pc_post<T, A>(c, tp, src, t, V + (size_t)m * c->n);
-  const T4 *vprev = m > 0 ? V + (size_t)(m - 1) * c->n : V;
-  k_lz_update<T, A><<<kRedBlock, 256, 0, c->stream>>>(t, V + (size_t)m * c->n, vprev, w, c->n, (LzState<A> *)c->lz,
-                                                      (A *)c->partials);
-  k_lz_check<A><<<1, 64, 0, c->stream>>>((const A *)c->partials, kRedBlock, (LzState<A> *)c->lz,
-                                         (A)c->p.lanczos_tol, c->lz_maxit);
-}
-
-// One iteration of the batched Krylov loop: the product of every group of
-// systems sharing a block edge, halo form and lanes per target, then the
-// vector kernels and the checks of all systems.
-template <typename A>
-void launch_lz_batch_iter(hipStream_t s, const LzRep<A> *reps, int nrep, const LzGroup *groups, int ngroups,
-                          const int2 *vmap, int nvblk, int m) {
-  for (int g = 0; g < ngroups; ++g) {
-    const LzGroup &gr = groups[g];
-    with_block_edge(gr.B, [&](auto b) {
-      constexpr int BE = decltype(b)::value;
-      auto go = [&](auto kernel) {
-        allow_lds(kernel, gr.smem);
-        kernel<<<gr.nblk, 1024, gr.smem, s>>>(reps, gr.pmap, m);
-      };
-      auto pick = [&](auto gl) {
-        constexpr int GL = decltype(gl)::value;
-        if (gr.unwrap) go(k_spmv_lds_batch<BE, true, A, GL>);
-        else go(k_spmv_lds_batch<BE, false, A, GL>);
-      };
-      if (gr.G == 2) pick(std::integral_constant<int, 2>{});
-      else if (gr.G == 4) pick(std::integral_constant<int, 4>{});
-      else pick(std::integral_constant<int, 3>{});
-    });
-  }
-  k_lz_alpha_batch<A><<<nvblk, 256, 0, s>>>(reps, vmap, m);
-  k_lz_update_batch<A><<<nvblk, 256, 0, s>>>(reps, vmap, m);
-  k_lz_check_batch<A><<<nrep, 64, 0, s>>>(reps);
 }
 __global__ void k_batch_status(const RepStatusSrc *__restrict__ src, int nrep, RepStatus *__restrict__ out) {
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
@@ -2322,45 +2356,35 @@ __global__ __launch_bounds__(256) void k_cell_sort_batch(const SampRep *__restri
 __global__ __launch_bounds__(256) void k_noise_batch(const SampRep *__restrict__ reps, const int2 *__restrict__ map) {
   const int2 rb = map[blockIdx.x];
   const SampRep &r = reps[rb.x];
-  real_noise_at<float>(r.perm, r.n, 0ull, 0ull, r.z, r.rng, rb.y * 256 + (int)threadIdx.x);
+  real_noise_at<float>(r.perm, r.n, 0ull, 0ull, r.V, r.rng, rb.y * 256 + (int)threadIdx.x);
 }
+// partial sums of |z|^2 (the systems whose vector work is one workgroup sum
+// it themselves)
 template <typename A>
-__global__ __launch_bounds__(256) void k_norm2_batch(const SampRep *__restrict__ reps, const int2 *__restrict__ map) {
+__global__ __launch_bounds__(256) void k_lz_norm_batch(const SampRep *__restrict__ reps, const int2 *__restrict__ map) {
   __shared__ A sh[16];
   const int2 rb = map[blockIdx.x];
   const SampRep &r = reps[rb.x];
-  const float *zf = (const float *)r.z;
-  A *part = (A *)r.partials;
-  const int len = 4 * r.n, i = rb.y * 256 + (int)threadIdx.x;
+  if (r.n <= kLzStepMax) return;
+  const int i = rb.y * 256 + (int)threadIdx.x;
   A v = 0;
-  if (i < len) v += (A)zf[i] * (A)zf[i];
+  if (i < r.n) {
+    const float4 a = r.V[i];
+    v = dot3(v, a, a);
+  }
   v = block_sum(v, sh);
-  if (threadIdx.x == 0) part[rb.y] = v;
-  if (rb.y == 0)
-    for (int k = (len + 255) / 256 + (int)threadIdx.x; k < kRedBlock; k += 256) part[k] = A(0);
+  if (threadIdx.x == 0) ((A *)r.partials)[rb.y] = v;
 }
 template <typename A>
-__global__ __launch_bounds__(256) void k_lz_init_batch(const SampRep *__restrict__ reps) {
-  const SampRep &r = reps[blockIdx.x];
-  lz_init_body<A>((const A *)r.partials, kRedBlock, (LzState<A> *)r.st);
-}
-template <typename A>
-__global__ __launch_bounds__(256) void k_combine_batch(const SampRep *__restrict__ reps, const int2 *__restrict__ map) {
+__global__ __launch_bounds__(256) void k_finalize_batch(const SampRep *__restrict__ reps, const int2 *__restrict__ map) {
   __shared__ A sc[kMaxIter];
   const int2 rb = map[blockIdx.x];
   const SampRep &r = reps[rb.x];
-  const LzState<A> *st = (const LzState<A> *)r.st;
-  const int m = st->m;
-  if (threadIdx.x < (unsigned)m) sc[threadIdx.x] = st->beta[0] * st->s[threadIdx.x];
-  __syncthreads();
-  const int len = 4 * r.n, i = rb.y * 256 + (int)threadIdx.x;
-  if (i < len) ((float *)r.yr)[i] = lz_combine_at<float, A>((const float *)r.V, (size_t)len, sc, m, i);
-}
-__global__ __launch_bounds__(256) void k_finalize_batch(const SampRep *__restrict__ reps, const int2 *__restrict__ map) {
-  const int2 rb = map[blockIdx.x];
-  const SampRep &r = reps[rb.x];
-  finalize_at<float>(r.perm, r.yr, r.cr, r.f_in ? r.ur : nullptr, r.dt, r.wave, r.out, r.n,
-                     rb.y * 256 + (int)threadIdx.x);
+  const int m = lz_combine_coef<A>((const LzState<A> *)r.st, sc);
+  const int s = rb.y * 256 + (int)threadIdx.x;
+  if (s >= r.n) return;
+  const float4 y = lz_combine_at<float, A>(r.V, r.n, sc, m, s);
+  finalize_at<float>(r.perm, &y, r.cr, r.f_in ? r.ur : nullptr, r.dt, r.wave, r.out, s);
 }
 __global__ __launch_bounds__(256) void k_gather_forces_batch(const SampRep *__restrict__ reps,
                                                              const int2 *__restrict__ map) {
@@ -2390,12 +2414,10 @@ void launch_samp_batch_forces(hipStream_t s, const SampRep *reps, const SampMaps
 }
 template <typename A> void launch_samp_batch_start(hipStream_t s, const SampRep *reps, const SampMaps &m) {
   k_noise_batch<<<m.npart, 256, 0, s>>>(reps, m.part);
-  k_norm2_batch<A><<<m.nflat, 256, 0, s>>>(reps, m.flat);
-  k_lz_init_batch<A><<<m.nrep, 256, 0, s>>>(reps);
+  k_lz_norm_batch<A><<<m.npart, 256, 0, s>>>(reps, m.part);
 }
 template <typename A> void launch_samp_batch_end(hipStream_t s, const SampRep *reps, const SampMaps &m) {
-  k_combine_batch<A><<<m.nflat, 256, 0, s>>>(reps, m.flat);
-  k_finalize_batch<<<m.npart, 256, 0, s>>>(reps, m.part);
+  k_finalize_batch<A><<<m.npart, 256, 0, s>>>(reps, m.part);
 }
 template void launch_samp_batch_start<float>(hipStream_t, const SampRep *, const SampMaps &);
 template void launch_samp_batch_start<double>(hipStream_t, const SampRep *, const SampMaps &);
@@ -2426,18 +2448,15 @@ void launch_lz_batch_plain(hipStream_t s, const LzRep<A> *reps, const LzGroup *g
 template void launch_lz_batch_plain<float>(hipStream_t, const LzRep<float> *, const LzGroup *, int);
 template void launch_lz_batch_plain<double>(hipStream_t, const LzRep<double> *, const LzGroup *, int);
 
-template void launch_lz_batch_iter<float>(hipStream_t, const LzRep<float> *, int, const LzGroup *, int, const int2 *,
-                                          int, int);
-template void launch_lz_batch_iter<double>(hipStream_t, const LzRep<double> *, int, const LzGroup *, int,
-                                           const int2 *, int, int);
-
+template void launch_lz_batch<float>(hipStream_t, const LzRep<float> *, const LzGroup *, int, const LzVecMaps &, int);
+template void launch_lz_batch<double>(hipStream_t, const LzRep<double> *, const LzGroup *, int, const LzVecMaps &,
+                                      int);
 
 template <typename T, typename A>
 void launch_lz_combine(pse_ctx *c, void *y) {
-  const int len = 4 * c->n;
+  using T4 = typename vec4<T>::type;
   ProfScope ps(c, PSE_STAGE_LANCZOS);
-  k_lz_combine<T, A><<<nblk(len, 256) < 2048 ? nblk(len, 256) : 2048, 256, 0, c->stream>>>(
-      (const T *)c->V, (size_t)len, len, (const LzState<A> *)c->lz, (T *)y);
+  k_lz_combine<T, A><<<nblk(c->n, 256), 256, 0, c->stream>>>((const T4 *)c->V, c->n, (const LzState<A> *)c->lz, (T4 *)y);
 }
 
 template <typename T>
@@ -2465,6 +2484,15 @@ void launch_finalize(pse_ctx *c, const void *yr, double cr, const void *ur, doub
                                                         (const T4 *)wv, (T *)out, c->n);
 }
 
+template <typename T, typename A>
+void launch_finalize_krylov(pse_ctx *c, double cr, const void *ur, double dt, const void *wv, void *out) {
+  using T4 = typename vec4<T>::type;
+  ProfScope ps(c, PSE_STAGE_OTHER);
+  k_finalize_krylov<T, A><<<nblk(c->n, 256), 256, 0, c->stream>>>(c->perm, (const T4 *)c->V, (const LzState<A> *)c->lz,
+                                                                  (T)cr, (const T4 *)ur, (T)dt, (const T4 *)wv,
+                                                                  (T *)out, c->n);
+}
+
 template <typename T>
 void launch_real_noise(pse_ctx *c, void *z_sorted, uint64_t seed, uint64_t sample) {
   ProfScope ps(c, PSE_STAGE_NOISE);
@@ -2475,6 +2503,7 @@ void launch_real_noise(pse_ctx *c, void *z_sorted, uint64_t seed, uint64_t sampl
 #define INST_T(T)                                                                                  \
   template void launch_bin<T>(pse_ctx *, const void *);                                            \
   template void launch_nbr<T>(pse_ctx *);                                                          \
+  template void launch_spmv<T>(pse_ctx *, const void *, void *);                                   \
   template void launch_gather3<T>(pse_ctx *, const void *, void *);                                \
   template void launch_gather3_add<T>(pse_ctx *, const void *, const void *, void *);              \
   template void launch_advance<T>(pse_ctx *, void *, const void *);                                \
@@ -2483,11 +2512,10 @@ void launch_real_noise(pse_ctx *c, void *z_sorted, uint64_t seed, uint64_t sampl
 INST_T(float)
 INST_T(double)
 #define INST_TA(T, A)                                                           \
-  template void launch_spmv<T, A>(pse_ctx *, const void *, void *, bool, void *); \
-  template void launch_lz_init<T, A>(pse_ctx *, const void *);                  \
-  template void launch_lz_iter<T, A>(pse_ctx *, int, const void *);             \
-  template void launch_lz_iter_pc<T, A>(pse_ctx *, int, const void *);          \
-  template void launch_lz_combine<T, A>(pse_ctx *, void *);
+  template void launch_lz_norm<T, A>(pse_ctx *, bool);                          \
+  template void launch_lz_iters<T, A>(pse_ctx *, int, int, bool);                \
+  template void launch_lz_combine<T, A>(pse_ctx *, void *);                     \
+  template void launch_finalize_krylov<T, A>(pse_ctx *, double, const void *, double, const void *, void *);
 INST_TA(float, float)
 INST_TA(float, double)
 INST_TA(double, double)

@@ -492,11 +492,10 @@ __global__ void k_pc_blocks(const float *__restrict__ y, int n, T *__restrict__ 
 }
 
 // ------------------------------------------- preconditioned Lanczos steps
-// u = P^T src (sorted order), skipped once the iteration is done.
-template <typename T, typename A>
+// u = P^T src (sorted order).
+template <typename T>
 __global__ void k_pc_pre(const typename vec4<T>::type *__restrict__ src, const T *__restrict__ P, int n,
-                         typename vec4<T>::type *__restrict__ u, const LzState<A> *st) {
-  if (st->done) return;
+                         typename vec4<T>::type *__restrict__ u) {
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= n) return;
   const auto v = src[s];
@@ -510,67 +509,14 @@ __global__ void k_pc_pre(const typename vec4<T>::type *__restrict__ src, const T
   u[s] = o;
 }
 
-// From t' = M_r P^T src: v_m = src / beta (stored as basis vector m),
-// out = P t' / beta, and alpha_m = <v_m, out> reduced in a fixed order with
-// the last workgroup finishing (the same contract as the fused product).
-template <typename T, typename A>
-__global__ __launch_bounds__(256) void k_pc_post(const typename vec4<T>::type *__restrict__ tp,
-                                                 const typename vec4<T>::type *__restrict__ src,
-                                                 const T *__restrict__ P, int n,
-                                                 typename vec4<T>::type *__restrict__ out,
-                                                 typename vec4<T>::type *__restrict__ vm_out, LzState<A> *st,
-                                                 A *partials, unsigned *counter) {
-  __shared__ A sh[16];
-  __shared__ int last;
-  if (st->done) return;
-  const T sc = (T)st->inv_beta;
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  A dot = A(0);
-  if (s < n) {
-    const auto t = tp[s];
-    const auto v = src[s];
-    const auto *pr = (const typename vec4<T>::type *)(P + (size_t)s * 12);  // rows of P_s
-    const auto r0 = pr[0], r1 = pr[1], r2 = pr[2];
-    typename vec4<T>::type o, u;
-    o.x = (r0.x * t.x + r0.y * t.y + r0.z * t.z) * sc;
-    o.y = (r1.x * t.x + r1.y * t.y + r1.z * t.z) * sc;
-    o.z = (r2.x * t.x + r2.y * t.y + r2.z * t.z) * sc;
-    o.w = T(0);
-    u.x = v.x * sc;
-    u.y = v.y * sc;
-    u.z = v.z * sc;
-    u.w = T(0);
-    out[s] = o;
-    vm_out[s] = u;
-    dot = (A)u.x * (A)o.x + (A)u.y * (A)o.y + (A)u.z * (A)o.z;
-  }
-  const A bs = block_sum(dot, sh);
-  if (threadIdx.x == 0) {
-    partials[blockIdx.x] = bs;
-    __threadfence();
-    const unsigned prev = atomicAdd(counter, 1u);
-    last = (prev == gridDim.x - 1);
-  }
-  __syncthreads();
-  if (last) {
-    __threadfence();
-    A v = 0;
-    for (int i = threadIdx.x; i < (int)gridDim.x; i += blockDim.x) v += partials[i];
-    v = block_sum(v, sh);
-    if (threadIdx.x == 0) {
-      st->alpha[st->m] = v;
-      *counter = 0u;
-    }
-  }
-}
-
-// y = P^{-1} y in place (sorted order).
+// y = Q x (sorted order; x and y may be the same array).
 template <typename T>
-__global__ void k_pc_apply(const T *__restrict__ Q, int n, typename vec4<T>::type *__restrict__ y) {
+__global__ void k_pc_apply(const T *__restrict__ Q, int n, const typename vec4<T>::type *x,
+                           typename vec4<T>::type *y) {
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= n) return;
-  const auto v = y[s];
-  const auto *qr = (const typename vec4<T>::type *)(Q + (size_t)s * 12);  // rows of P_s^-1
+  const auto v = x[s];
+  const auto *qr = (const typename vec4<T>::type *)(Q + (size_t)s * 12);  // rows of Q_s
   const auto r0 = qr[0], r1 = qr[1], r2 = qr[2];
   typename vec4<T>::type o;
   o.x = r0.x * v.x + r0.y * v.y + r0.z * v.z;
@@ -694,23 +640,20 @@ template <typename T> void launch_pc_blocks(pse_ctx *c) {
                                                        (T *)c->pc_Pinv, c->flags);
 }
 
-template <typename T, typename A> void launch_pc_pre(pse_ctx *c, const void *src, void *u) {
-  k_pc_pre<T, A><<<nblk(c->n, 256), 256, 0, c->stream>>>((const typename vec4<T>::type *)src, (const T *)c->pc_P,
-                                                         c->n, (typename vec4<T>::type *)u,
-                                                         (const LzState<A> *)c->lz);
+template <typename T> void launch_pc_pre(pse_ctx *c, const void *src, void *u) {
+  k_pc_pre<T><<<nblk(c->n, 256), 256, 0, c->stream>>>((const typename vec4<T>::type *)src, (const T *)c->pc_P, c->n,
+                                                      (typename vec4<T>::type *)u);
 }
 
-template <typename T, typename A>
-void launch_pc_post(pse_ctx *c, const void *tp, const void *src, void *out, void *vm_out) {
+template <typename T> void launch_pc_post(pse_ctx *c, const void *tp, void *out) {
   using T4 = typename vec4<T>::type;
-  k_pc_post<T, A><<<nblk(c->n, 256), 256, 0, c->stream>>>((const T4 *)tp, (const T4 *)src, (const T *)c->pc_P, c->n,
-                                                          (T4 *)out, (T4 *)vm_out, (LzState<A> *)c->lz,
-                                                          (A *)c->partials, c->counter);
+  k_pc_apply<T><<<nblk(c->n, 256), 256, 0, c->stream>>>((const T *)c->pc_P, c->n, (const T4 *)tp, (T4 *)out);
 }
 
 template <typename T> void launch_pc_apply_inv(pse_ctx *c, void *y) {
+  using T4 = typename vec4<T>::type;
   ProfScope ps(c, PSE_STAGE_PRECOND);
-  k_pc_apply<T><<<nblk(c->n, 256), 256, 0, c->stream>>>((const T *)c->pc_Pinv, c->n, (typename vec4<T>::type *)y);
+  k_pc_apply<T><<<nblk(c->n, 256), 256, 0, c->stream>>>((const T *)c->pc_Pinv, c->n, (const T4 *)y, (T4 *)y);
 }
 
 void launch_unsort_features(pse_ctx *c, void *out) {
@@ -728,11 +671,9 @@ template void launch_pc_apply_inv<float>(pse_ctx *, void *);
 template void launch_pc_apply_inv<double>(pse_ctx *, void *);
 template void launch_unsort_blocks<float>(pse_ctx *, float *);
 template void launch_unsort_blocks<double>(pse_ctx *, float *);
-#define PSE_PC_INST(T, A)                                                          \
-  template void launch_pc_pre<T, A>(pse_ctx *, const void *, void *);              \
-  template void launch_pc_post<T, A>(pse_ctx *, const void *, const void *, void *, void *);
-PSE_PC_INST(float, float)
-PSE_PC_INST(float, double)
-PSE_PC_INST(double, double)
+template void launch_pc_pre<float>(pse_ctx *, const void *, void *);
+template void launch_pc_pre<double>(pse_ctx *, const void *, void *);
+template void launch_pc_post<float>(pse_ctx *, const void *, void *);
+template void launch_pc_post<double>(pse_ctx *, const void *, void *);
 
 }  // namespace pse

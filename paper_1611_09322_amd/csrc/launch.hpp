@@ -28,17 +28,26 @@ void launch_nbr_lds(pse_ctx *c);
 // the LDS neighbour build of every system of the groups in one launch per group
 void launch_nbr_batch(hipStream_t s, const NbrRep *reps, const NbrGroup *groups, int ngroups);
 void launch_feat_lds(pse_ctx *c);  // preconditioner features from the list and the staged halo
-template <typename T, typename A> void launch_spmv(pse_ctx *c, const void *src, void *out, bool lz, void *vm_out);
-template <typename T, typename A> void launch_lz_init(pse_ctx *c, const void *z);
-template <typename T, typename A> void launch_lz_iter(pse_ctx *c, int m, const void *z);
+template <typename T> void launch_spmv(pse_ctx *c, const void *src, void *out);
+// The Krylov loop on the start vector in the basis' first slot: iterations
+// [m0, m0 + k) and their checks.  pc: on P M_r P^T.
+template <typename T, typename A> void launch_lz_iters(pse_ctx *c, int m0, int k, bool pc);
+// the partial sums of |z|^2 that iteration 0 starts from, where it needs them
+// (part of launch_lz_iters)
+template <typename T, typename A> void launch_lz_norm(pse_ctx *c, bool pc);
 template <typename T, typename A> void launch_lz_combine(pse_ctx *c, void *y);
 template <typename T> void launch_gather3(pse_ctx *c, const void *in, void *out);
 // out (sorted) = gather(in, caller order; may be null) + add (sorted; may be null)
 template <typename T> void launch_gather3_add(pse_ctx *c, const void *in, const void *add, void *out);
 // x += dx over 3n scalars (caller order)
 template <typename T> void launch_advance(pse_ctx *c, void *x, const void *dx);
+// out = cr y + dt ur + wv in caller order (null or absent terms omitted): y
+// the Krylov iterate, formed here from the basis (krylov), or the sorted
+// vector yr
 template <typename T>
 void launch_finalize(pse_ctx *c, const void *yr, double cr, const void *ur, double dt, const void *wv, void *out);
+template <typename T, typename A>
+void launch_finalize_krylov(pse_ctx *c, double cr, const void *ur, double dt, const void *wv, void *out);
 template <typename T> void launch_real_noise(pse_ctx *c, void *z, uint64_t seed, uint64_t sample);
 
 // full-mobility Krylov sample (k_full.hip); alpha, beta live in device memory
@@ -62,18 +71,17 @@ pse_status launch_mlp_bwd_static(const uint16_t *w, const uint16_t *x, const uin
 void launch_mlp_adam(float *wm, uint16_t *wb, const float *g, float *m, float *v, float lr, int t, hipStream_t stream);
 void launch_mlp_loss(const float *y, const float *t, int n, float *dy, float *loss, hipStream_t stream);
 template <typename T> void launch_pc_blocks(pse_ctx *c);           // features -> MLP -> P, P^-1 (fallbacks in flags[6])
-template <typename T, typename A> void launch_pc_pre(pse_ctx *c, const void *src, void *u);  // u = P^T src
-template <typename T, typename A>
-void launch_pc_post(pse_ctx *c, const void *tp, const void *src, void *out, void *vm_out);
-template <typename T> void launch_pc_apply_inv(pse_ctx *c, void *y);  // y = P^-1 y
+template <typename T> void launch_pc_pre(pse_ctx *c, const void *src, void *u);   // u = P^T src
+template <typename T> void launch_pc_post(pse_ctx *c, const void *tp, void *out);  // out = P tp
+template <typename T> void launch_pc_apply_inv(pse_ctx *c, void *y);               // y = P^-1 y
 void launch_unsort_features(pse_ctx *c, void *out);
 template <typename T> void launch_unsort_blocks(pse_ctx *c, float *out);
-template <typename T, typename A> void launch_lz_iter_pc(pse_ctx *c, int m, const void *z);
-// iteration m of the Lanczos process on nrep systems at once (FP32 storage,
-// LDS product, no preconditioner): bit-identical to launch_lz_iter per system
+// iterations [0, iters) of the Lanczos process on many systems at once (FP32
+// storage, LDS product, no preconditioner): bit-identical to launch_lz_iters
+// per system
 template <typename A>
-void launch_lz_batch_iter(hipStream_t s, const LzRep<A> *reps, int nrep, const LzGroup *groups, int ngroups,
-                          const int2 *vmap, int nvblk, int m);
+void launch_lz_batch(hipStream_t s, const LzRep<A> *reps, const LzGroup *groups, int ngroups,
+                     const LzVecMaps &vm, int iters);
 // the wave-space part without forces of every system of the groups
 // (bit-identical to each system's own launches)
 void launch_wave_batch(hipStream_t s, const WaveGroup *groups, int ngroups);

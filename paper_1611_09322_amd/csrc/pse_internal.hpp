@@ -91,18 +91,25 @@ __host__ __device__ __forceinline__ float bf16_to_f32(uint16_t h) {
   return x;
 }
 
-// Lanczos state kept in device memory (A = accumulation precision).
+// Lanczos state kept in device memory (A = accumulation precision).  The
+// basis holds unnormalised vectors u_j (u_0 = z): v_j = rs[j] u_j, and
+// |u_{m+1}| = beta_{m+1} 2^-e with e the even exponent of alpha_m, so that
+// the vectors stay of order 1 in any units.
 template <typename A> struct LzState {
   A alpha[kMaxIter];
   A beta[kMaxIter + 1];  // beta[0] = |z|, beta[m+1] couples v_m and v_{m+1}
+  A rs[kMaxIter + 1];    // 1 / |u_j|
   A s[kMaxIter];         // T_m^{1/2} e_1 of the latest iterate
   A rel_change;          // |s_m - s_{m-1}| / |s_m|
-  A inv_beta;            // scale of the next Lanczos vector
-  int m;                 // completed iterations
+  int m;                 // completed and checked iterations
   int done;              // 1: converged (or broke down / max_iter reached)
   int converged;         // 1: tolerance met or invariant subspace
   int nonfinite;
 };
+
+// Up to this many particles one workgroup does the vector work and check of a
+// Lanczos iteration (k_lz_step).
+constexpr int kLzStepMax = 4096;
 
 // One system whose whole captured step runs in batched launches (FP32
 // storage, LDS path, Philox noise, no forces, no preconditioner): the
@@ -114,11 +121,9 @@ struct SampRep {
   float L, invL, inv_cs;
   int nc, ncell, n;
   const uint64_t *rng;  // (seed, counter) of the Philox noise
-  float4 *z;            // real-space noise, sorted
+  float4 *V;            // Krylov basis; its first vector is the real-space noise, sorted
   void *partials;       // A [kRedBlock]
   void *st;             // LzState<A>
-  const float4 *V;      // Krylov basis
-  float4 *yr;           // Krylov sample, sorted
   const float4 *wave;   // wave-space part, sorted
   float *out;           // displacement, caller order n x 3
   float cr;             // sqrt(2 kT dt)
@@ -129,10 +134,10 @@ struct SampRep {
 };
 // Workgroup maps (system, block) of the batched launches: zero (blocks of
 // 256 over ncell + 8), part (256 particles), tile (scan tiles), cell (4
-// cells), flat (256 of the 4n vector scalars).
+// cells).
 struct SampMaps {
-  const int2 *zero, *part, *tile, *cell, *flat;
-  int nzero, npart, ntile, ncell, nflat, nrep;
+  const int2 *zero, *part, *tile, *cell;
+  int nzero, npart, ntile, ncell, nrep;
 };
 
 // One system of a batched neighbour build (LDS path, no repulsion), and the
@@ -163,12 +168,12 @@ template <typename A> struct LzRep {
   const int *cnt;           // entries per target
   const float2 *tab;        // (mu0 F, mu0 (G - F)) table
   int *ovf;                 // halo overflow flag
-  const float4 *z;          // start vector
-  float4 *t, *w, *V;        // product, residual, basis [maxit][n]
+  float4 *t, *V;            // product, basis [maxit + 1][n]
   const float4 *fs;         // forces (sorted) of the batched M_r F, or null
   float4 *ur;               // M_r F
   LzState<A> *st;
-  A *partials;              // [0, kRedBlock): |w|^2; [kRedBlock, 2 kRedBlock): alpha_m
+  const double2 *nodes;     // quadrature of the tridiagonal root
+  A *partials;              // [0, kRedBlock): |u|^2; [kRedBlock, 2 kRedBlock): alpha_m
   float cs, L, invL, inv_dr, self_r;
   int nc, n, hcap, maxit;
   A tol;
@@ -181,6 +186,14 @@ struct LzGroup {
   int B, G, unwrap, nblk;
   size_t smem;
   const int2 *pmap;
+};
+// The vector work of a batched Krylov loop: vmap lists (system, block of 256
+// particles) of the systems above kLzStepMax, big those systems, small the
+// others (one workgroup each).
+struct LzVecMaps {
+  const int2 *vmap;
+  const int *big, *small;
+  int nv, nbig, nsmall;
 };
 
 // What the host reads back from each replica after a captured batch step:
@@ -284,6 +297,10 @@ bool precond_targets(const double *x, int n, double L, double a, double xi, doub
 bool fft_size_supported(int M);
 // s = T^{1/2} e_1 of an m x m symmetric tridiagonal (lanczos_host.cpp)
 bool tridiag_sqrt_e1_host(int m, const double *d, const double *e, double *s);
+// nodes of lambda^{1/2} = sum_j w_j lambda / (lambda + t_j) on [1e-13, 1]
+// (lanczos_host.cpp)
+constexpr int kRootNodes = 64;
+void lz_quadrature(double2 *tw);
 
 }  // namespace pse
 
@@ -334,8 +351,8 @@ struct pse_ctx {
   void *V = nullptr;        // T4 [(kMaxIter+1) n] Lanczos basis
   void *lz = nullptr;       // LzState<A>
   void *lz_h = nullptr;     // pinned copy
+  double2 *lz_nodes = nullptr;  // [64] quadrature (t_j, w_j) of the tridiagonal root
   void *partials = nullptr; // A [max blocks]
-  unsigned *counter = nullptr;
   float2 *table = nullptr;  // F/G table nodes (FP32 modes)
   double *series = nullptr; // [2*kSeriesTerms] series coefficients (device)
   double series_h[2 * pse::kSeriesTerms];

@@ -48,3 +48,27 @@ def test_root_over_iterations_and_units(gpu_lib, boxes, precision, tol, eta, n):
     assert st.converged == 1
     check(y.double().cpu().numpy(), ref, bar, f"root n={n} {precision} eta={eta:g} iters {st.lanczos_iters}")
     s.close()
+
+
+# around the bound up to which one workgroup does an iteration's vector work
+# (4096 particles)
+@pytest.mark.parametrize("n", [4095, 4096, 4097])
+@pytest.mark.parametrize("precision", ["mixed", "fp32", "fp64"])
+def test_vector_work_by_size(gpu_lib, n, precision):
+    """M_r^{1/2} applied twice is M_r: both products of one context, so the
+    bar is the Krylov tolerance's and the storage type's alone."""
+    L = (4 * np.pi * n / 0.6) ** (1 / 3)  # phi = 0.2
+    x = synth.uniform_positions(n, L, seed=5)
+    tol = 1e-10 if precision == "fp64" else 1e-5
+    s = gpu_lib.Sampler(n, L, xi=0.7, rcut=4.5, grid=64, support=6, tol=tol, precision=precision)
+    s.set_positions(torch.as_tensor(x, dtype=s.dtype, device="cuda"))
+    z = torch.as_tensor(synth.normals(12, (n, 3)), dtype=s.dtype, device="cuda")
+    y, st = s.real_sample(z)
+    assert st.converged == 1
+    again, _ = s.real_sample(y.clone())
+    ref = s.real_matvec(z)
+    # two roots: each 3 tol (see above) and the storage type's rounding
+    bar = 6 * tol + (1e-12 if precision == "fp64" else 2 * FP32_NEAR_BAR_DENSE)
+    check(again.double().cpu().numpy(), ref.double().cpu().numpy(), bar,
+          f"root twice n={n} {precision} iters {st.lanczos_iters}")
+    s.close()
