@@ -51,7 +51,7 @@ inline size_t asize(const pse_ctx *c) { return c->acc_dbl ? 8 : 4; }
 
 void free_ctx(pse_ctx *c) {
   if (!c) return;
-  void *dev[] = {c->pos_w, c->pos_s, c->perm, c->cell_of, c->cell_count, c->cell_start, c->nbr, c->nbr_cnt,
+  void *dev[] = {c->pos_w, c->pos_s, c->perm, c->cell_of, c->cell_count, c->cell_start, c->nbr, c->nbr_cnt, c->nbr_coef,
                  c->flags, c->V, c->lz, c->lz_nodes, c->partials, c->table, c->series, c->grid, c->rgrid, c->grid2, c->tw_M,
                  c->tw_H, c->pc_w, c->pc_feat, c->pc_y, c->pc_P, c->pc_Pinv, c->pc_user, c->fl_V, c->fl_ab,
                  c->fl_coef};
@@ -99,6 +99,28 @@ int nbr_capacity(const pse_ctx *c) {
   if (cap > c->n) cap = c->n;
   if (cap < 8) cap = 8;
   return (cap + 7) & ~7;
+}
+
+// The list (and FP64 pair coefficients) at a capacity.  Products fall back to
+// evaluating the coefficients where they find no memory.
+bool alloc_list(pse_ctx *c, int cap) {
+  if (c->nbr) (void)hipFree(c->nbr);
+  if (c->nbr_coef) (void)hipFree(c->nbr_coef);
+  c->nbr = nullptr;
+  c->nbr_coef = nullptr;
+  c->nbr_cap = 0;
+  const size_t slots = (size_t)cap * c->n;
+  if (hipMalloc((void **)&c->nbr, sizeof(int) * slots) != hipSuccess) {
+    c->nbr = nullptr;
+    (void)hipGetLastError();
+    return false;
+  }
+  c->nbr_cap = cap;
+  if (c->dbl && hipMalloc((void **)&c->nbr_coef, sizeof(double2) * slots) != hipSuccess) {
+    c->nbr_coef = nullptr;
+    (void)hipGetLastError();
+  }
+  return true;
 }
 
 WaveCoef wave_coef(const pse_ctx *c, double det_scale, double sto_scale, uint64_t seed, uint64_t counter) {
@@ -459,14 +481,7 @@ pse_status set_positions_impl(pse_ctx *c, const void *pos) {
   if (c->flags_h[1] > c->nbr_cap) {
     const int cap = (c->flags_h[1] + 32 + 7) & ~7;
     c->graph_stale = true;  // a captured graph holds the old list
-    (void)hipFree(c->nbr);
-    c->nbr = nullptr;
-    if (hipMalloc(&c->nbr, sizeof(int) * (size_t)cap * c->n) != hipSuccess) {
-      c->nbr = nullptr;
-      c->nbr_cap = 0;
-      return PSE_ERR_OOM;
-    }
-    c->nbr_cap = cap;
+    if (!alloc_list(c, cap)) return PSE_ERR_OOM;
     if (hipMemsetAsync(c->flags, 0, sizeof(int) * 8, c->stream) != hipSuccess) return PSE_ERR_HIP;
     st = build_neighbors<T>(c);
     if (st != PSE_OK) return st;
@@ -875,8 +890,7 @@ pse_status pse_create(const pse_params *p, void *stream, pse_ctx **out) {
   c->cell_of = (int *)al.dev(sizeof(int) * 2 * n);  // cells, then slots
   c->cell_count = (int *)al.dev(sizeof(int) * 2 * c->ncell);
   c->cell_start = (int *)al.dev(sizeof(int) * (c->ncell + 1));
-  c->nbr_cap = nbr_capacity(c);
-  c->nbr = (int *)al.dev(sizeof(int) * (size_t)c->nbr_cap * n);
+  if (al.st == PSE_OK && !alloc_list(c, nbr_capacity(c))) al.st = PSE_ERR_OOM;
   c->nbr_cnt = (int *)al.dev(sizeof(int) * n);
 
   c->flags = (int *)al.dev(sizeof(int) * 8);
@@ -1639,13 +1653,7 @@ static pse_status batch_capture(pse_batch *b) {
     const int cap = ((int)std::ceil(c->flags_h[1] * (1.0 + b->g_headroom)) + 32 + 7) & ~7;
     if (cap > c->nbr_cap) {
       if (hipStreamSynchronize(c->stream) != hipSuccess) return PSE_ERR_HIP;
-      (void)hipFree(c->nbr);
-      c->nbr = nullptr;
-      if (hipMalloc(&c->nbr, sizeof(int) * (size_t)cap * c->n) != hipSuccess) {
-        c->nbr_cap = 0;
-        return PSE_ERR_OOM;
-      }
-      c->nbr_cap = cap;
+      if (!alloc_list(c, cap)) return PSE_ERR_OOM;
     }
     int it = (c->last_iters < 2 ? 2 : c->last_iters) + b->g_extra;
     c->graph_iters = it > c->lz_maxit ? c->lz_maxit : it;

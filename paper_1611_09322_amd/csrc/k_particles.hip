@@ -344,37 +344,156 @@ template <typename T> struct FeatAcc {
   }
 };
 
-// Near-field neighbour list (ELL layout nbr[k * n + s], sorted indices):
-// every t != s with minimum-image distance <= rc, scanning the 27 adjacent
-// cells (fewer when a side has < 3 cells, so no cell is visited twice).
-// With FEAT the learned-preconditioner features of s are accumulated from
-// the same hits (fg gives mu0 F and mu0 (G - F); FeatAcc).
+// Global near-field list (FP64, and FP32 boxes without an LDS block): row s
+// holds the sorted indices nbr[s cap + k], k < cnt[s], of every t != s with
+// minimum-image distance <= rc, in the order of the adjacent cells (fewer
+// than 27 when a side has < 3 cells, so no cell is visited twice).
 // With REP the overlap repulsion f_s = sum_{t: r < 2a} krep (2a - r) d / r
 // (d = x_s - x_t) goes to frep[s].
-template <typename T, bool FEAT, typename FG, bool REP = false>
-__global__ void k_nbr_build(const typename vec4<T>::type *__restrict__ pos, const int *__restrict__ start, int n,
-                            int nc, T L, T invL, T inv_cs, T rc2, int *__restrict__ nbr, int *__restrict__ cnt_out,
-                            int cap, int *__restrict__ flags, FG fg, T inv_mu0, T fself, T a, T inv_rc,
-                            uint16_t *__restrict__ feat, T krep, typename vec4<T>::type *__restrict__ frep) {
+//
+// The adjacent cells of one (x, y) column: a run of consecutive z cells,
+// split in two where it wraps.
+struct CellRun {
+  int a1, n1, a2, n;  // first particle and length of the first part, first of the second, total
+  __device__ __forceinline__ int at(int i) const { return i < n1 ? a1 + i : a2 + (i - n1); }
+};
+__device__ __forceinline__ CellRun cell_run(const int *__restrict__ start, int nc, int ax, int ay, int z0, int nz) {
+  const int base = (ax * nc + ay) * nc, zl = (z0 + nc) % nc, z1 = zl + nz - 1;
+  CellRun r;
+  r.a1 = start[base + zl];
+  r.n1 = start[base + min(z1, nc - 1) + 1] - r.a1;
+  r.a2 = start[base];
+  r.n = r.n1 + (z1 >= nc ? start[base + z1 - nc + 1] - r.a2 : 0);
+  return r;
+}
+
+// flags[1], flags[5]: largest count; flags[2..3]: total.  One set of atomics
+// per workgroup: every wavefront hitting the same words serialises at the L2
+// (about 12 ns each; testing the maxima with a load first is slower still, the
+// loads queue behind the atomics: 212 -> 470 us with 4096 workgroups).
+__device__ __forceinline__ void nbr_stats(unsigned long long mine, int mx, int *__restrict__ flags) {
+  __shared__ unsigned long long wtot[16];
+  __shared__ int wmx[16];
+  const unsigned long long tot = wave_sum(mine);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) mx = max(mx, __shfl_xor(mx, off, 64));
+  const int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) {
+    wtot[wave] = tot;
+    wmx[wave] = mx;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    unsigned long long t = 0;
+    int m = 0;
+    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
+      t += wtot[w];
+      m = max(m, wmx[w]);
+    }
+    if (t) atomicAdd((unsigned long long *)(flags + 2), t);
+    atomicMax(&flags[1], m);
+    atomicMax(&flags[5], m);
+  }
+}
+
+// 16 lanes per target scan its candidates, 16 at a time; the hits are
+// compacted with a ballot into consecutive entries of the row.  (One lane per
+// target took 150 us for 1000 particles, a serial scan on 16 wavefronts.)
+constexpr int kRowLanes = 16;
+template <typename T, bool REP>
+__global__ __launch_bounds__(256) void k_nbr_rows(const typename vec4<T>::type *__restrict__ pos,
+                                                  const int *__restrict__ start, int n, int nc, T L, T invL, T inv_cs,
+                                                  T rc2, int *__restrict__ nbr, int *__restrict__ cnt_out, int cap,
+                                                  int *__restrict__ flags, T a, T krep,
+                                                  typename vec4<T>::type *__restrict__ frep) {
+  constexpr int RL = kRowLanes;
+  const int sub = threadIdx.x % RL, grp0 = ((threadIdx.x & 63) / RL) * RL;  // first lane of the group
+  const int lo = nc >= 3 ? -1 : 0, nz = nc >= 3 ? 3 : (nc >= 2 ? 2 : 1);
+  const int rows = gridDim.x * (256 / RL);
+  unsigned long long mine = 0;
+  int mx = 0;
+  // a wavefront's groups leave the loop together (ballots below)
+  for (int s0 = (blockIdx.x * 256 + (threadIdx.x & ~63)) / RL; s0 < n; s0 += rows) {
+    const int s = s0 + grp0 / RL;
+    const bool act = s < n;
+    const auto p = pos[act ? s : n - 1];
+    const int cx = min((int)(p.x * inv_cs), nc - 1), cy = min((int)(p.y * inv_cs), nc - 1),
+              cz = min((int)(p.z * inv_cs), nc - 1);
+    int cnt = 0;
+    T fx = T(0), fy = T(0), fz = T(0);
+    for (int dx = 0; dx < nz; ++dx)
+      for (int dy = 0; dy < nz; ++dy) {
+        const CellRun r = cell_run(start, nc, (cx + lo + dx + nc) % nc, (cy + lo + dy + nc) % nc, cz + lo, nz);
+        const int tot = act ? r.n : 0;
+        for (int c0 = 0; __any(c0 < tot); c0 += RL) {
+          const int ci = c0 + sub, t = ci < tot ? r.at(ci) : s;
+          const bool cand = ci < tot && t != s;
+          const auto q = pos[cand ? t : (act ? s : n - 1)];
+          const T ddx = min_image(p.x - q.x, L, invL);
+          const T ddy = min_image(p.y - q.y, L, invL);
+          const T ddz = min_image(p.z - q.z, L, invL);
+          const T r2 = ddx * ddx + ddy * ddy + ddz * ddz;
+          if (REP && cand && r2 < T(4) * a * a && r2 > T(0)) {
+            const T rr = sqrt(r2), m = krep * (T(2) * a - rr) / rr;
+            fx += m * ddx;
+            fy += m * ddy;
+            fz += m * ddz;
+          }
+          const bool hit = cand && r2 <= rc2;
+          const unsigned gm = (unsigned)(__ballot(hit) >> grp0) & ((1u << RL) - 1u);
+          const int slot = cnt + __popc(gm & ((1u << sub) - 1u));
+          if (hit && slot < cap) nbr[(size_t)s * cap + slot] = t;
+          cnt += __popc(gm);
+        }
+      }
+    if (REP) {
+#pragma unroll
+      for (int off = RL / 2; off > 0; off >>= 1) {
+        fx += __shfl_xor(fx, off, 64);
+        fy += __shfl_xor(fy, off, 64);
+        fz += __shfl_xor(fz, off, 64);
+      }
+    }
+    if (act && sub == 0) {
+      if (REP) {
+        typename vec4<T>::type f;
+        f.x = fx;
+        f.y = fy;
+        f.z = fz;
+        f.w = T(0);
+        frep[s] = f;
+      }
+      cnt_out[s] = min(cnt, cap);  // entries stored; flags[1] carries the capacity needed
+      mine += (unsigned long long)cnt;
+      mx = max(mx, cnt);
+    }
+  }
+  nbr_stats(mine, mx, flags);
+}
+
+// The same list with the learned-preconditioner features of s accumulated
+// from its hits (fg gives mu0 F and mu0 (G - F); FeatAcc): one lane per
+// target, which holds the 24 sums.
+template <typename T, typename FG, bool REP>
+__global__ void k_nbr_feat(const typename vec4<T>::type *__restrict__ pos, const int *__restrict__ start, int n,
+                           int nc, T L, T invL, T inv_cs, T rc2, int *__restrict__ nbr, int *__restrict__ cnt_out,
+                           int cap, int *__restrict__ flags, FG fg, T inv_mu0, T fself, T a,
+                           uint16_t *__restrict__ feat, T krep, typename vec4<T>::type *__restrict__ frep) {
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
   int cnt = 0;
   if (s < n) {
-  FeatAcc<T> acc;
-  if (FEAT) acc.init(fself);
-  T fx = T(0), fy = T(0), fz = T(0);
-  const auto p = pos[s];
-  const int cx = min((int)(p.x * inv_cs), nc - 1);
-  const int cy = min((int)(p.y * inv_cs), nc - 1);
-  const int cz = min((int)(p.z * inv_cs), nc - 1);
-  const int lo = nc >= 3 ? -1 : 0, hi = nc >= 2 ? 1 : 0;
-  for (int dx = lo; dx <= hi; ++dx) {
-    const int ax = (cx + dx + nc) % nc;
-    for (int dy = lo; dy <= hi; ++dy) {
-      const int ay = (cy + dy + nc) % nc;
-      for (int dz = lo; dz <= hi; ++dz) {
-        const int c = (ax * nc + ay) * nc + (cz + dz + nc) % nc;
-        const int e = start[c + 1];
-        for (int t = start[c]; t < e; ++t) {
+    FeatAcc<T> acc;
+    acc.init(fself);
+    T fx = T(0), fy = T(0), fz = T(0);
+    const auto p = pos[s];
+    const int cx = min((int)(p.x * inv_cs), nc - 1), cy = min((int)(p.y * inv_cs), nc - 1),
+              cz = min((int)(p.z * inv_cs), nc - 1);
+    const int lo = nc >= 3 ? -1 : 0, nz = nc >= 3 ? 3 : (nc >= 2 ? 2 : 1);
+    for (int dx = 0; dx < nz; ++dx)
+      for (int dy = 0; dy < nz; ++dy) {
+        const CellRun run = cell_run(start, nc, (cx + lo + dx + nc) % nc, (cy + lo + dy + nc) % nc, cz + lo, nz);
+        for (int k = 0; k < run.n; ++k) {
+          const int t = run.at(k);
           if (t == s) continue;
           const auto q = pos[t];
           const T ddx = min_image(p.x - q.x, L, invL);
@@ -388,9 +507,9 @@ __global__ void k_nbr_build(const typename vec4<T>::type *__restrict__ pos, cons
             fz += m * ddz;
           }
           if (r2 <= rc2) {
-            if (cnt < cap) nbr[(size_t)cnt * n + s] = t;
+            if (cnt < cap) nbr[(size_t)s * cap + cnt] = t;
             ++cnt;
-            if (FEAT && r2 < T(20.25) * a * a) {  // near shell r < 4.5a
+            if (r2 < T(20.25) * a * a) {  // near shell r < 4.5a
               T Fm = fself / inv_mu0, Dm = T(0), r = T(0), ir = T(0);
               if (r2 > T(1e-24)) {
                 r = sqrt(r2);
@@ -402,82 +521,114 @@ __global__ void k_nbr_build(const typename vec4<T>::type *__restrict__ pos, cons
           }
         }
       }
+    acc.store(feat + (size_t)s * kNFeat, cnt);
+    if (REP) {
+      typename vec4<T>::type f;
+      f.x = fx;
+      f.y = fy;
+      f.z = fz;
+      f.w = T(0);
+      frep[s] = f;
     }
+    cnt_out[s] = min(cnt, cap);  // entries stored; flags[1] carries the capacity needed
   }
-  if (FEAT) acc.store(feat + (size_t)s * kNFeat, cnt);
-  if (REP) {
-    typename vec4<T>::type f;
-    f.x = fx;
-    f.y = fy;
-    f.z = fz;
-    f.w = T(0);
-    frep[s] = f;
-  }
-  cnt_out[s] = min(cnt, cap);  // entries stored; flags[1] carries the capacity needed
-  }
-  // total ordered pairs and the largest count: one set of atomics per wavefront
-  const unsigned long long tot = wave_sum((unsigned long long)cnt);
-  int mx = cnt;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) mx = max(mx, __shfl_xor(mx, off, 64));
-  if ((threadIdx.x & 63) == 0) {
-    if (tot) atomicAdd((unsigned long long *)(flags + 2), tot);
-    atomicMax(&flags[1], mx);  // capacity needed
-    atomicMax(&flags[5], mx);  // largest neighbour count
-  }
+  nbr_stats((unsigned long long)cnt, cnt, flags);
 }
 
 // --------------------------------------------------- near-field product
-// One thread per sorted particle s:
-//   out_s = self * v_s + sum_{t in nbr(s)} mu0 [F v_t + (G-F)(d.v_t) d / r^2]
-// with v = src.  A Lanczos iteration passes `done`, the flag of its state:
-// once set the product is skipped (null: always formed).
+// mu0 F and mu0 (G - F) / r^2 of one pair (the coincident limit is isotropic).
 template <typename T, typename FG>
-__device__ __forceinline__ void spmv_body(const typename vec4<T>::type *__restrict__ pos, const int *__restrict__ nbr,
-                                          const int *__restrict__ cnt, int n, T L, T invL, const FG &fg, T self_r,
-                                          const typename vec4<T>::type *__restrict__ src,
-                                          typename vec4<T>::type *__restrict__ out) {
-  using T4 = typename vec4<T>::type;
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= n) return;
-  const T4 p = pos[s];
-  const T4 v = src[s];
-  T ax = self_r * v.x, ay = self_r * v.y, az = self_r * v.z;
-  const int c = cnt[s];
-  const int *nb = nbr + s;
-#pragma unroll 4
-  for (int k = 0; k < c; ++k) {
-    const int t = nb[(size_t)k * n];
-    const T4 q = pos[t];
-    const T4 w = src[t];
-    const T dx = min_image(p.x - q.x, L, invL);
-    const T dy = min_image(p.y - q.y, L, invL);
-    const T dz = min_image(p.z - q.z, L, invL);
-    const T r2 = dx * dx + dy * dy + dz * dz;
-    T Fm, Dm, rinv;
-    if (r2 > T(1e-24)) {
-      rinv = T(1) / sqrt(r2);
-      fg.eval(r2, rinv, Fm, Dm);
-    } else {  // coincident spheres: the r -> 0 limit is isotropic
-      Fm = self_r;
-      Dm = T(0);
-      rinv = T(0);
-    }
-    const T pr = Dm * rinv * rinv * (dx * w.x + dy * w.y + dz * w.z);
-    ax += Fm * w.x + pr * dx;
-    ay += Fm * w.y + pr * dy;
-    az += Fm * w.z + pr * dz;
+__device__ __forceinline__ void pair_coef(T r2, const FG &fg, T self_r, T &Fm, T &Dr) {
+  if (r2 > T(1e-24)) {
+    const T rinv = T(1) / sqrt(r2);
+    T Dm;
+    fg.eval(r2, rinv, Fm, Dm);
+    Dr = Dm * rinv * rinv;
+  } else {
+    Fm = self_r;
+    Dr = T(0);
   }
-  T4 o;
-  o.x = ax;
-  o.y = ay;
-  o.z = az;
-  o.w = T(0);
-  out[s] = o;
+}
+
+// FP64: both coefficients of every list entry, evaluated once per
+// configuration.  The closed forms take six transcendental functions a pair;
+// evaluated inside every product they were 112 us of the 116 us a product of
+// 1000 particles took, 7 products a sample.
+__global__ __launch_bounds__(256) void k_pair_coef(const double4 *__restrict__ pos, const int *__restrict__ nbr,
+                                                   const int *__restrict__ cnt, int n, int cap, double L, double invL,
+                                                   FGExact fg, double self_r, double2 *__restrict__ coef) {
+  // consecutive lanes take consecutive entries of a row; grid.y splits long rows
+  const int sub = threadIdx.x % kRowLanes, s = (blockIdx.x * 256 + threadIdx.x) / kRowLanes;
+  if (s >= n) return;
+  const int c = cnt[s];
+  const double4 p = pos[s];
+  for (int k = blockIdx.y * kRowLanes + sub; k < c; k += gridDim.y * kRowLanes) {
+    const size_t e = (size_t)s * cap + k;
+    const double4 q = pos[nbr[e]];
+    const double dx = min_image(p.x - q.x, L, invL), dy = min_image(p.y - q.y, L, invL),
+                 dz = min_image(p.z - q.z, L, invL);
+    double2 o;
+    pair_coef(dx * dx + dy * dy + dz * dz, fg, self_r, o.x, o.y);
+    coef[e] = o;
+  }
+}
+
+// out_s = self * v_s + sum_{t in nbr(s)} mu0 [F v_t + (G-F)(d.v_t) d / r^2]
+// with v = src: kRowLanes lanes per row, partial sums combined by lane
+// shuffles.  A Lanczos iteration passes `done`, the flag of its state: once
+// set the product is skipped (null: always formed).  The pair coefficients come
+// from coef(entry, r^2, F, D).
+template <typename T, typename Coef>
+__device__ __forceinline__ void spmv_rows(const typename vec4<T>::type *__restrict__ pos, const int *__restrict__ nbr,
+                                          const int *__restrict__ cnt, int n, int cap, T L, T invL, T self_r,
+                                          const typename vec4<T>::type *__restrict__ src,
+                                          typename vec4<T>::type *__restrict__ out, Coef coef) {
+  using T4 = typename vec4<T>::type;
+  constexpr int RL = kRowLanes;
+  const int sub = threadIdx.x % RL, rows = gridDim.x * (blockDim.x / RL);
+  for (int s0 = (blockIdx.x * blockDim.x + (threadIdx.x & ~63)) / RL; s0 < n; s0 += rows) {
+    const int s = s0 + (threadIdx.x & 63) / RL;
+    T ax = T(0), ay = T(0), az = T(0);
+    if (s < n) {
+      const T4 p = pos[s];
+      const int c = cnt[s];
+#pragma unroll 2
+      for (int k = sub; k < c; k += RL) {
+        const size_t e = (size_t)s * cap + k;
+        const int t = nbr[e];
+        const T4 q = pos[t];
+        const T4 w = src[t];
+        const T dx = min_image(p.x - q.x, L, invL);
+        const T dy = min_image(p.y - q.y, L, invL);
+        const T dz = min_image(p.z - q.z, L, invL);
+        T F, Dr;
+        coef(e, dx * dx + dy * dy + dz * dz, F, Dr);
+        const T pr = Dr * (dx * w.x + dy * w.y + dz * w.z);
+        ax += F * w.x + pr * dx;
+        ay += F * w.y + pr * dy;
+        az += F * w.z + pr * dz;
+      }
+    }
+#pragma unroll
+    for (int off = RL / 2; off > 0; off >>= 1) {
+      ax += __shfl_xor(ax, off, 64);
+      ay += __shfl_xor(ay, off, 64);
+      az += __shfl_xor(az, off, 64);
+    }
+    if (s < n && sub == 0) {
+      const T4 v = src[s];
+      T4 o;
+      o.x = ax + self_r * v.x;
+      o.y = ay + self_r * v.y;
+      o.z = az + self_r * v.z;
+      o.w = T(0);
+      out[s] = o;
+    }
+  }
 }
 
 __global__ __launch_bounds__(256) void k_spmv_table(const float4 *__restrict__ pos, const int *__restrict__ nbr,
-                                                    const int *__restrict__ cnt, int n, float L, float invL,
+                                                    const int *__restrict__ cnt, int n, int cap, float L, float invL,
                                                     const float2 *__restrict__ tab_g, float inv_dr, float self_r,
                                                     const float4 *__restrict__ src, float4 *__restrict__ out,
                                                     const int *__restrict__ done) {
@@ -485,18 +636,32 @@ __global__ __launch_bounds__(256) void k_spmv_table(const float4 *__restrict__ p
   if (done && *done) return;
   for (int i = threadIdx.x; i < kTableN; i += blockDim.x) tab[i] = tab_g[i];
   __syncthreads();
-  FGTable fg{tab, inv_dr};
-  spmv_body<float, FGTable>(pos, nbr, cnt, n, L, invL, fg, self_r, src, out);
+  const FGTable fg{tab, inv_dr};
+  spmv_rows<float>(pos, nbr, cnt, n, cap, L, invL, self_r, src, out,
+                   [&](size_t, float r2, float &F, float &Dr) { pair_coef(r2, fg, self_r, F, Dr); });
 }
 
+__global__ __launch_bounds__(256) void k_spmv_coef(const double4 *__restrict__ pos, const int *__restrict__ nbr,
+                                                   const int *__restrict__ cnt, int n, int cap, double L, double invL,
+                                                   const double2 *__restrict__ coef, double self_r,
+                                                   const double4 *__restrict__ src, double4 *__restrict__ out,
+                                                   const int *__restrict__ done) {
+  if (done && *done) return;
+  spmv_rows<double>(pos, nbr, cnt, n, cap, L, invL, self_r, src, out, [&](size_t e, double, double &F, double &Dr) {
+    const double2 c = coef[e];
+    F = c.x;
+    Dr = c.y;
+  });
+}
+
+// where the coefficients found no memory (16 bytes per list slot)
 __global__ __launch_bounds__(256) void k_spmv_exact(const double4 *__restrict__ pos, const int *__restrict__ nbr,
-                                                    const int *__restrict__ cnt, int n, double L, double invL,
-                                                    const double *__restrict__ ser, double xi, double a, double mu0,
-                                                    double small_r2, double self_r, const double4 *__restrict__ src,
+                                                    const int *__restrict__ cnt, int n, int cap, double L, double invL,
+                                                    FGExact fg, double self_r, const double4 *__restrict__ src,
                                                     double4 *__restrict__ out, const int *__restrict__ done) {
   if (done && *done) return;
-  FGExact fg{ser, xi, a, mu0, small_r2};
-  spmv_body<double, FGExact>(pos, nbr, cnt, n, L, invL, fg, self_r, src, out);
+  spmv_rows<double>(pos, nbr, cnt, n, cap, L, invL, self_r, src, out,
+                    [&](size_t, double r2, double &F, double &Dr) { pair_coef(r2, fg, self_r, F, Dr); });
 }
 
 // ------------------------------------------- LDS-staged near-field kernels
@@ -799,30 +964,7 @@ __device__ __forceinline__ void nbr_lds_block(const float4 *__restrict__ pos, co
     mine += (unsigned long long)k;
     mx = max(mx, k);
   }
-  // one set of atomics per workgroup: every wavefront hitting the same
-  // flags serialises at the L2
-  const unsigned long long tot = wave_sum(mine);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) mx = max(mx, __shfl_xor(mx, off, 64));
-  __shared__ unsigned long long wtot[8];
-  __shared__ int wmx[8];
-  const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) {
-    wtot[wave] = tot;
-    wmx[wave] = mx;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned long long t = 0;
-    int m = 0;
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
-      t += wtot[w];
-      m = max(m, wmx[w]);
-    }
-    if (t) atomicAdd((unsigned long long *)(flags + 2), t);
-    atomicMax(&flags[1], m);
-    atomicMax(&flags[5], m);
-  }
+  nbr_stats(mine, mx, flags);
 }
 
 template <int B, bool UNWRAP, bool REP = false>
@@ -1961,6 +2103,10 @@ void launch_bin(pse_ctx *c, const void *pos) {
                                                            (T4 *)c->pos_s);
 }
 
+static FGExact fg_exact(const pse_ctx *c) { return FGExact{c->series, c->p.xi, c->p.a, c->d.mu0, c->small_r2}; }
+// workgroups of 256 lanes, kRowLanes per row, at most 8 per compute unit
+static int row_blocks(int n) { return std::min(nblk(n, 256 / kRowLanes), 2048); }
+
 template <typename T>
 void launch_nbr(pse_ctx *c) {
   using T4 = typename vec4<T>::type;
@@ -1968,22 +2114,33 @@ void launch_nbr(pse_ctx *c) {
   const T L = (T)c->d.L, invL = (T)(1.0 / c->d.L), inv_cs = (T)(1.0 / c->d.cs);
   const T rc2 = (T)(c->p.rcut * c->p.rcut);
   ProfScope ps(c, PSE_STAGE_NBR);
-  const T inv_mu0 = (T)(1.0 / c->d.mu0), fself = (T)(c->d.self_r / c->d.mu0), a = (T)c->p.a,
-          inv_rc = (T)(1.0 / c->p.rcut);
+  const T inv_mu0 = (T)(1.0 / c->d.mu0), fself = (T)(c->d.self_r / c->d.mu0), a = (T)c->p.a;
   const bool rep = c->rep_k > 0;
-  auto go = [&](auto kern, auto fg) {
-    kern<<<nblk(n, 128), 128, 0, c->stream>>>((const T4 *)c->pos_s, c->cell_start, n, c->d.nc, L, invL, inv_cs, rc2,
-                                              c->nbr, c->nbr_cnt, c->nbr_cap, c->flags, fg, inv_mu0, fself, a, inv_rc,
-                                              c->pc_feat, (T)c->rep_k, (T4 *)c->vbuf[kRepBuf]);
-  };
-  if constexpr (sizeof(T) == 8) {
-    const FGExact fg{c->series, c->p.xi, c->p.a, c->d.mu0, c->small_r2};
-    if (c->pc_on) rep ? go(k_nbr_build<double, true, FGExact, true>, fg) : go(k_nbr_build<double, true, FGExact>, fg);
-    else rep ? go(k_nbr_build<double, false, FGExact, true>, fg) : go(k_nbr_build<double, false, FGExact>, fg);
+  if (c->pc_on) {
+    auto go = [&](auto kern, auto fg) {
+      kern<<<nblk(n, 128), 128, 0, c->stream>>>((const T4 *)c->pos_s, c->cell_start, n, c->d.nc, L, invL, inv_cs, rc2,
+                                                c->nbr, c->nbr_cnt, c->nbr_cap, c->flags, fg, inv_mu0, fself, a,
+                                                c->pc_feat, (T)c->rep_k, (T4 *)c->vbuf[kRepBuf]);
+    };
+    auto both = [&](auto fg) {
+      using FG = decltype(fg);
+      rep ? go(k_nbr_feat<T, FG, true>, fg) : go(k_nbr_feat<T, FG, false>, fg);
+    };
+    if constexpr (sizeof(T) == 8) both(fg_exact(c));
+    else both(FGTable{c->table, (float)(kTableK / c->p.rcut)});
   } else {
-    const FGTable fg{c->table, (float)(kTableK / c->p.rcut)};
-    if (c->pc_on) rep ? go(k_nbr_build<float, true, FGTable, true>, fg) : go(k_nbr_build<float, true, FGTable>, fg);
-    else rep ? go(k_nbr_build<float, false, FGTable, true>, fg) : go(k_nbr_build<float, false, FGTable>, fg);
+    auto go = [&](auto kern) {
+      kern<<<row_blocks(n), 256, 0, c->stream>>>((const T4 *)c->pos_s, c->cell_start, n, c->d.nc, L, invL, inv_cs, rc2,
+                                                 c->nbr, c->nbr_cnt, c->nbr_cap, c->flags, a, (T)c->rep_k,
+                                                 (T4 *)c->vbuf[kRepBuf]);
+    };
+    rep ? go(k_nbr_rows<T, true>) : go(k_nbr_rows<T, false>);
+  }
+  if constexpr (sizeof(T) == 8) {
+    // small systems: rows split so that the evaluations fill the GPU
+    if (c->nbr_coef)
+      k_pair_coef<<<dim3(nblk(n, 256 / kRowLanes), n < 32768 ? 8 : 1), 256, 0, c->stream>>>(
+          (const double4 *)c->pos_s, c->nbr, c->nbr_cnt, n, c->nbr_cap, L, invL, fg_exact(c), c->d.self_r, c->nbr_coef);
   }
 }
 
@@ -2172,16 +2329,20 @@ pse_status autotune_spmv(pse_ctx *c, int32_t *lanes) {
 }
 
 template <typename T> static void spmv(pse_ctx *c, const void *src, void *out, const int *done) {
-  const int n = c->n, nb = nblk(n, 256);
+  const int n = c->n, nb = row_blocks(n), cap = c->nbr_cap;
   ProfScope ps(c, PSE_STAGE_SPMV);
   if constexpr (sizeof(T) == 8) {
-    k_spmv_exact<<<nb, 256, 0, c->stream>>>((const double4 *)c->pos_s, c->nbr, c->nbr_cnt, n, c->d.L, 1.0 / c->d.L,
-                                            c->series, c->p.xi, c->p.a, c->d.mu0, c->small_r2, c->d.self_r,
-                                            (const double4 *)src, (double4 *)out, done);
+    const double L = c->d.L, invL = 1.0 / L, self_r = c->d.self_r;
+    if (c->nbr_coef)
+      k_spmv_coef<<<nb, 256, 0, c->stream>>>((const double4 *)c->pos_s, c->nbr, c->nbr_cnt, n, cap, L, invL,
+                                             c->nbr_coef, self_r, (const double4 *)src, (double4 *)out, done);
+    else
+      k_spmv_exact<<<nb, 256, 0, c->stream>>>((const double4 *)c->pos_s, c->nbr, c->nbr_cnt, n, cap, L, invL,
+                                              fg_exact(c), self_r, (const double4 *)src, (double4 *)out, done);
   } else if (c->lds_B) {
     spmv_lds(c, (const float4 *)src, (float4 *)out, done);
   } else {
-    k_spmv_table<<<nb, 256, 0, c->stream>>>((const float4 *)c->pos_s, c->nbr, c->nbr_cnt, n, (float)c->d.L,
+    k_spmv_table<<<nb, 256, 0, c->stream>>>((const float4 *)c->pos_s, c->nbr, c->nbr_cnt, n, cap, (float)c->d.L,
                                             (float)(1.0 / c->d.L), c->table, (float)(kTableK / c->p.rcut),
                                             (float)c->d.self_r, (const float4 *)src, (float4 *)out, done);
   }

@@ -343,6 +343,7 @@ struct pse_ctx {
   int *nbr = nullptr;
   int *nbr_cnt = nullptr;
   int nbr_cap = 0;
+  double2 *nbr_coef = nullptr;  // FP64: (mu0 F, mu0 (G - F) / r^2) per list slot, or null without memory for it
   int *flags = nullptr;     // [0] nonfinite, [1] list slots needed, [2..3] pairs, [4] max halo,
                             // [5] max neighbours, [6] preconditioner fallbacks
   int *flags_h = nullptr;   // pinned copy

@@ -1,0 +1,58 @@
+"""Near-field list and product over box sizes and row lengths, against dense
+M_r of the oracle.
+
+Bars: 1e-12 in FP64 (sums of at most some hundred terms of order 1 at
+2.2e-16 each); in FP32 storage the table and coordinate bar of the parity
+tests for dense boxes.
+"""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import rpy
+from parity import FP32_NEAR_BAR_DENSE, check
+
+pytestmark = pytest.mark.gpu
+
+BAR = {"fp64": 1e-12, "fp32": FP32_NEAR_BAR_DENSE, "mixed": FP32_NEAR_BAR_DENSE}
+
+
+def dev(x, s):
+    return torch.as_tensor(np.ascontiguousarray(x), dtype=s.dtype, device="cuda")
+
+
+# cells per side 2 (no LDS block: rows of global indices), 3, 4, 5 and 6
+# (blocks of 1 to 4 cells, halos that wrap and halos that do not); rows
+# around the 16 entries one pass of a row's lanes takes
+@pytest.mark.parametrize("nc", [2, 3, 4, 5, 6])
+@pytest.mark.parametrize("n", [1, 2, 17, 40, 333])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_product_by_box_and_row_length(gpu_lib, precision, n, nc):
+    rc = 4.6
+    L = (nc + 0.05) * rc
+    x = synth.uniform_positions(n, L, seed=31 * n + nc)
+    x[0] = [L, -0.25 * L, 1.5 * L]  # on the face, below and above the box
+    s = gpu_lib.Sampler(n, L, xi=0.7, rcut=rc, grid=64, support=6, precision=precision)
+    s.set_positions(dev(x, s))
+    v = synth.normals(3, (n, 3))
+    ref = rpy.real_block_dense(x, L, 1.0, 1.0, 0.7, rc) @ v.ravel()
+    w = s.real_matvec(dev(v, s)).double().cpu().numpy()
+    check(w, ref, BAR[precision], f"M_r v n={n} cells {nc} {precision}")
+    s.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_rows_grow_past_their_capacity(gpu_lib, precision):
+    """All spheres within one cutoff of each other: rows far above the mean
+    density's estimate, so the list is reallocated and built again."""
+    n, L, rc = 300, 30.0, 4.6
+    x = synth.uniform_positions(n, L, seed=8)
+    s = gpu_lib.Sampler(n, L, xi=0.7, rcut=rc, grid=64, support=6, precision=precision)
+    s.set_positions(dev(x, s))
+    y = 13.0 + 2.6 * synth.uniform_positions(n, 1.0, seed=9)
+    s.set_positions(dev(y, s))
+    v = synth.normals(4, (n, 3))
+    ref = rpy.real_block_dense(y, L, 1.0, 1.0, 0.7, rc) @ v.ravel()
+    check(s.real_matvec(dev(v, s)).double().cpu().numpy(), ref, BAR[precision], f"clustered M_r v {precision}")
+    s.close()
