@@ -9,6 +9,7 @@
 // that are not finite, nearly singular or ill conditioned fall back to I.
 // Training kernels (the backward pass on the matrix cores, Adam) run off
 // the sampling path.
+#include <algorithm>
 #include <mutex>
 
 #include "launch.hpp"
@@ -163,6 +164,21 @@ __device__ __forceinline__ bf16x8 ld8(const uint16_t *p) {
   return as_bf16x8(*(const u32x4 *)p);
 }
 
+// Eight bf16 from global memory: one 16-byte load where every array starts on
+// a 16-byte boundary (A16; rows are multiples of 16 bytes), else one by one.
+template <bool A16> __device__ __forceinline__ u32x4 load8(const uint16_t *__restrict__ p) {
+  if constexpr (A16) return *(const u32x4 *)p;
+  u32x4 r;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r[i] = (uint32_t)p[2 * i] | ((uint32_t)p[2 * i + 1] << 16);
+  return r;
+}
+__device__ __forceinline__ uint16_t half_of(const u32x4 &v, int i) { return (uint16_t)(v[i >> 1] >> (16 * (i & 1))); }
+
+// At 6000 rows a wavefront has one chunk, so the kernel's time is the chain
+// stage, product, stage, ...: the staging loads are 16 bytes wide and all in
+// flight before the first is used (two-byte loads: 33 us a pass).
+template <bool A16>
 __global__ __launch_bounds__(64 * kBwdWaves) void k_mlp_bwd(const uint16_t *__restrict__ w,
                                                             const uint16_t *__restrict__ x,
                                                             const uint16_t *__restrict__ cache,
@@ -171,11 +187,22 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_mlp_bwd(const uint16_t *__re
   __shared__ __attribute__((aligned(16))) uint16_t w3T[64][32 + 8];  // W3^T (k, o), o >= 16 zero
   __shared__ __attribute__((aligned(16))) uint16_t w2s[64][64 + 8];  // W2 (j, k) as stored
   __shared__ __attribute__((aligned(16))) BwdLds L[kBwdWaves];
-  for (int e = threadIdx.x; e < 64 * 32; e += blockDim.x) {
-    const int k = e >> 5, o = e & 31;
-    w3T[k][o] = o < 16 ? w[kW3 + o * 64 + k] : (uint16_t)0;
+  {
+    constexpr int NT = 64 * kBwdWaves;
+    u32x4 a[64 * 8 / NT], b;  // W2: 8 pieces of 8 per row; W3 (16 rows of 64): 128 pieces
+    static_assert(NT == 128, "one piece of W3 per thread");
+#pragma unroll
+    for (int i = 0; i < 64 * 8 / NT; ++i) a[i] = load8<A16>(w + kW2 + 8 * (threadIdx.x + i * NT));
+    b = load8<A16>(w + kW3 + 8 * threadIdx.x);
+#pragma unroll
+    for (int i = 0; i < 64 * 8 / NT; ++i) {
+      const int e = threadIdx.x + i * NT;
+      *(u32x4 *)&w2s[e >> 3][8 * (e & 7)] = a[i];
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w3T[8 * (threadIdx.x & 7) + i][threadIdx.x >> 3] = half_of(b, i);
+    for (int e = threadIdx.x; e < 64 * 16; e += NT) w3T[e >> 4][16 + (e & 15)] = 0;
   }
-  for (int e = threadIdx.x; e < 64 * 64; e += blockDim.x) w2s[e >> 6][e & 63] = w[kW2 + e];
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r16 = lane & 15, g = lane >> 4;
@@ -193,30 +220,53 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_mlp_bwd(const uint16_t *__re
   float gb1[4] = {0.f, 0.f, 0.f, 0.f}, gb2[4] = {0.f, 0.f, 0.f, 0.f}, gb3 = 0.f;
   for (int p0 = gw * kBwdRows; p0 < n; p0 += nw * kBwdRows) {
     // ---- stage the chunk (rows past n are zero)
-    for (int e = lane; e < kBwdRows * 128; e += 64) {
-      const int p = e >> 7, c = e & 127;
-      const uint16_t v = p0 + p < n ? cache[(size_t)(p0 + p) * 2 * kNHid + c] : (uint16_t)0;
-      if (c < 64) S.h1T[c][p] = v;
-      else S.h2T[c - 64][p] = v;
+    // the activations: 16 pieces of 8 per row, x: 3, dy: 9 values
+    const u32x4 none = {0u, 0u, 0u, 0u};
+    u32x4 ca[8], xa[2];
+    float da[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int e = lane + 64 * i, p = e >> 4;
+      ca[i] = p0 + p < n ? load8<A16>(cache + (size_t)(p0 + p) * 2 * kNHid + 8 * (e & 15)) : none;
     }
-    for (int e = lane; e < kBwdRows * 32; e += 64) {
-      const int p = e >> 5, f = e & 31;
-      S.xT[f][p] = (f < kNFeat && p0 + p < n) ? x[(size_t)(p0 + p) * kNFeat + f] : (uint16_t)0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int e = lane + 64 * i, p = e / 3, q = e - 3 * p;
+      xa[i] = p < kBwdRows && p0 + p < n ? load8<A16>(x + (size_t)(p0 + p) * kNFeat + 8 * q) : none;
     }
-    for (int e = lane; e < kBwdRows * 32; e += 64) {
-      const int p = e >> 5, o = e & 31;
-      const float v = (o < kNOut && p0 + p < n) ? dy[(size_t)(p0 + p) * kNOut + o] : 0.f;
-      uint16_t a, b, c;
-      split3(v, &a, &b, &c);
-      S.dy[0][p][o] = a;
-      S.dy[1][p][o] = b;
-      S.dy[2][p][o] = c;
-      if (o < 16) {
-        S.dyT[0][o][p] = a;
-        S.dyT[1][o][p] = b;
-        S.dyT[2][o][p] = c;
-        S.dyf[p][o] = v;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int e = lane + 64 * i, p = e >> 4, o = e & 15;
+      da[i] = o < kNOut && p0 + p < n ? dy[(size_t)(p0 + p) * kNOut + o] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int e = lane + 64 * i, p = e >> 4, c = 8 * (e & 15);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        if (c < 64) S.h1T[c + u][p] = half_of(ca[i], u);
+        else S.h2T[c - 64 + u][p] = half_of(ca[i], u);
       }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int e = lane + 64 * i, p = e / 3, q = e - 3 * p;
+      if (p < kBwdRows)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) S.xT[8 * q + u][p] = half_of(xa[i], u);
+    }
+    for (int e = lane; e < kBwdRows * 8; e += 64) S.xT[24 + (e & 7)][e >> 3] = 0;  // features 24 .. 31
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int e = lane + 64 * i, p = e >> 4, o = e & 15;
+      uint16_t a, b, c;
+      split3(da[i], &a, &b, &c);
+      S.dy[0][p][o] = S.dyT[0][o][p] = a;
+      S.dy[1][p][o] = S.dyT[1][o][p] = b;
+      S.dy[2][p][o] = S.dyT[2][o][p] = c;
+      S.dyf[p][o] = da[i];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) S.dy[q][p][16 + o] = 0;
     }
     wave_sync();
     // ---- bias of the output layer: column sums of dy
@@ -362,36 +412,62 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_mlp_bwd(const uint16_t *__re
   if (lane < 16) out[kB3 + lane] = lane < kNOut ? gb3 : 0.f;
 }
 
-// Eight interleaved partial sums (slot q goes to sum q mod 8) keep eight
-// loads in flight; the order is fixed, so the result is deterministic.
-__global__ void k_mlp_reduce(const float *__restrict__ partial, int nparts, float *__restrict__ dw) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= kWTotal) return;
+// Sums of the slots: the four wavefronts of a workgroup take 64 entries and
+// every fourth slot each, eight loads in flight, combined in a fixed order
+// (deterministic).  One thread per entry left 29 workgroups with a chain of
+// all slots: 11 us at 188 slots.
+__global__ __launch_bounds__(256) void k_mlp_reduce(const float *__restrict__ partial, int nparts,
+                                                    float *__restrict__ dw) {
+  __shared__ float sh[4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, e = blockIdx.x * 64 + lane;
   float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  int q = 0;
-  for (; q + 8 <= nparts; q += 8) {
+  if (e < kWTotal) {
+    int q = wave;
+    for (; q + 4 * 7 < nparts; q += 4 * 8) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] += partial[(size_t)(q + u) * kWTotal + e];
+      for (int u = 0; u < 8; ++u) v[u] += partial[(size_t)(q + 4 * u) * kWTotal + e];
+    }
+    for (int u = 0; q < nparts; q += 4, ++u) v[u] += partial[(size_t)q * kWTotal + e];
   }
-  for (; q < nparts; ++q) v[q & 7] += partial[(size_t)q * kWTotal + e];
-  dw[e] = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+  sh[wave][lane] = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+  __syncthreads();
+  if (wave == 0 && e < kWTotal) dw[e] = (sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]);
 }
 
 // Squared-error training loss of the block network: dy = (2/n)(y - t) and
-// loss = sum |y - t|^2 / n over the n x 9 outputs; one workgroup, fixed
-// summation order (deterministic).
-__global__ __launch_bounds__(256) void k_mlp_loss(const float *__restrict__ y, const float *__restrict__ t, int n,
-                                                  float *__restrict__ dy, float *__restrict__ loss) {
+// loss = sum |y - t|^2 / n over the n x 9 outputs.  The call has no workspace
+// for partial sums, so one workgroup forms the loss in a fixed order
+// (deterministic) and the others dy; both take four values at a time where
+// the arrays start on 16-byte boundaries (A16).  A single workgroup of 256
+// lanes and single loads for everything took 60 us at 6000 rows.
+template <bool A16>
+__global__ __launch_bounds__(1024) void k_mlp_loss(const float *y, const float *t, int n, float *dy, float *loss) {
   __shared__ double sh[16];
-  const float sc = 2.0f / (float)n;
-  double acc = 0.0;
-  for (int e = threadIdx.x; e < n * kNOut; e += blockDim.x) {
-    const float r = y[e] - t[e];
-    dy[e] = sc * r;
-    acc += (double)r * (double)r;
+  const long len = (long)n * kNOut, n4 = A16 ? len / 4 : 0;
+  auto sq = [](float a, float b) {
+    const double r = (double)(a - b);
+    return r * r;
+  };
+  if (blockIdx.x == 0) {
+    if (!loss) return;
+    double acc = 0.0;
+#pragma unroll 4
+    for (long e = threadIdx.x; e < n4; e += 1024) {
+      const float4 a = ((const float4 *)y)[e], b = ((const float4 *)t)[e];
+      acc += (sq(a.x, b.x) + sq(a.y, b.y)) + (sq(a.z, b.z) + sq(a.w, b.w));
+    }
+    for (long e = 4 * n4 + threadIdx.x; e < len; e += 1024) acc += sq(y[e], t[e]);
+    acc = block_sum(acc, sh);
+    if (threadIdx.x == 0) *loss = (float)(acc / n);
+    return;
   }
-  acc = block_sum(acc, sh);
-  if (threadIdx.x == 0 && loss) *loss = (float)(acc / n);
+  const float sc = 2.0f / (float)n;
+  const long i = (long)(blockIdx.x - 1) * 1024 + threadIdx.x, step = (long)(gridDim.x - 1) * 1024;
+  for (long e = i; e < n4; e += step) {
+    const float4 a = ((const float4 *)y)[e], b = ((const float4 *)t)[e];
+    ((float4 *)dy)[e] = make_float4(sc * (a.x - b.x), sc * (a.y - b.y), sc * (a.z - b.z), sc * (a.w - b.w));
+  }
+  for (long e = 4 * n4 + i; e < len; e += step) dy[e] = sc * (y[e] - t[e]);
 }
 
 // Adam (Kingma and Ba) on the fp32 master weights; c1 = 1/(1 - b1^t),
@@ -571,8 +647,9 @@ int mlp_bwd_parts(int n) {
 void launch_mlp_bwd(const uint16_t *w, const uint16_t *x, const uint16_t *cache, const float *dy, int n, float *dw,
                     float *work, hipStream_t stream) {
   const int parts = mlp_bwd_parts(n);
-  k_mlp_bwd<<<parts / kBwdWaves, 64 * kBwdWaves, 0, stream>>>(w, x, cache, dy, n, work);
-  k_mlp_reduce<<<nblk(kWTotal, 256), 256, 0, stream>>>(work, parts, dw);
+  const bool a16 = (((uintptr_t)w | (uintptr_t)x | (uintptr_t)cache) & 15) == 0;
+  (a16 ? k_mlp_bwd<true> : k_mlp_bwd<false>)<<<parts / kBwdWaves, 64 * kBwdWaves, 0, stream>>>(w, x, cache, dy, n, work);
+  k_mlp_reduce<<<nblk(kWTotal, 64), 256, 0, stream>>>(work, parts, dw);
 }
 
 // ------------------------------------------ allocation-free backward pass
@@ -616,7 +693,15 @@ pse_status launch_mlp_bwd_static(const uint16_t *w, const uint16_t *x, const uin
 }
 
 void launch_mlp_loss(const float *y, const float *t, int n, float *dy, float *loss, hipStream_t stream) {
-  k_mlp_loss<<<1, 256, 0, stream>>>(y, t, n, dy, loss);
+  const bool a16 = (((uintptr_t)y | (uintptr_t)t | (uintptr_t)dy) & 15) == 0;
+  const long per = a16 ? 4096 : 1024;
+  const int blocks = 1 + (int)std::min(((long)n * kNOut + per - 1) / per, 1024L);
+  auto *kern = a16 ? k_mlp_loss<true> : k_mlp_loss<false>;
+  if (loss && (dy == y || dy == t)) {  // dy over its own input: the loss first
+    kern<<<1, 1024, 0, stream>>>(y, t, n, dy, loss);
+    loss = nullptr;
+  }
+  kern<<<blocks, 1024, 0, stream>>>(y, t, n, dy, loss);
 }
 
 void launch_mlp_adam(float *wm, uint16_t *wb, const float *g, float *m, float *v, float lr, int t,
