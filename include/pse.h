@@ -480,7 +480,7 @@ pse_status pse_batch_sample(pse_batch *batch, uint64_t seed, uint64_t counter, d
  * replica of each (grid, support, precision) group (pse_batch_set_positions
  * first) and the others take its choice; the near-field product's lanes per
  * target are tuned on every replica's own positions, and then every replica
- * of one product kernel form (block edge, halo form, Lanczos scalar type)
+ * of one product kernel form (block edge, Lanczos scalar type)
  * takes the choice of most of the form's particles, so that a captured step
  * runs each form in one launch.  Synchronises every stream. */
 pse_status pse_batch_autotune(pse_batch *batch);
@@ -498,8 +498,8 @@ pse_status pse_batch_latency(pse_batch *batch, float *ms);
  * and one synchronisation for the whole batch, against about 45 launches
  * and two host waits per replica on the eager path.  Inside the graph each
  * stage of the step is one launch for all replicas that share its kernel:
- * binning, neighbour build (block edge, halo form), noise, Krylov start,
- * every Lanczos iteration (product per block edge, halo form and lanes per
+ * binning, neighbour build (block edge), noise, Krylov start,
+ * every Lanczos iteration (product per block edge and lanes per
  * target; vector kernels and checks for all), wave-space part (grid size,
  * support), combination, final sum and the read-back of every replica's
  * flags and Krylov state, each workgroup finding its replica and block in

@@ -1236,29 +1236,28 @@ pse_status pse_batch_autotune(pse_batch *b) {
     const pse_status st = autotune_spmv(c, nullptr);
     if (st != PSE_OK) return st;
   }
-  // then one choice per kernel form (block edge, halo form, Lanczos scalar
-  // type): the one most particles of the form chose.  A captured step runs
+  // then one choice per kernel form (block edge, Lanczos scalar type): the one most particles of the form chose.  A captured step runs
   // each form's replicas in one launch per iteration, so fewer forms mean
   // fewer, fuller launches; the eager path uses the same choice.
   struct Tally {
-    int B, unwrap, dbl;
+    int B, dbl;
     long w[5];
   };
   std::vector<Tally> t;
   for (pse_ctx *c : b->ctx) {
     if (c->dbl || !c->lds_B) continue;
-    const int uw = c->d.nc >= c->lds_B + 3 ? 1 : 0, ad = c->acc_dbl ? 1 : 0;
+    const int ad = c->acc_dbl ? 1 : 0;
     const int G = c->tune_spmv_lanes ? c->tune_spmv_lanes : 3;
     size_t g = 0;
-    while (g < t.size() && !(t[g].B == c->lds_B && t[g].unwrap == uw && t[g].dbl == ad)) ++g;
-    if (g == t.size()) t.push_back(Tally{c->lds_B, uw, ad, {0, 0, 0, 0, 0}});
+    while (g < t.size() && !(t[g].B == c->lds_B && t[g].dbl == ad)) ++g;
+    if (g == t.size()) t.push_back(Tally{c->lds_B, ad, {0, 0, 0, 0, 0}});
     t[g].w[G] += c->n;
   }
   for (pse_ctx *c : b->ctx) {
     if (c->dbl || !c->lds_B) continue;
-    const int uw = c->d.nc >= c->lds_B + 3 ? 1 : 0, ad = c->acc_dbl ? 1 : 0;
+    const int ad = c->acc_dbl ? 1 : 0;
     for (const Tally &x : t)
-      if (x.B == c->lds_B && x.unwrap == uw && x.dbl == ad) {
+      if (x.B == c->lds_B && x.dbl == ad) {
         int best = 3;
         for (int G = 2; G <= 4; ++G)
           if (x.w[G] > x.w[best]) best = G;
@@ -1345,7 +1344,6 @@ template <typename A> static pse_status lzb_setup(pse_batch *b) {
     q.ur = (float4 *)c->vbuf[7];
     q.cs = (float)c->d.cs;
     q.L = (float)c->d.L;
-    q.invL = (float)(1.0 / c->d.L);
     q.inv_dr = (float)(kTableK / c->p.rcut);
     q.self_r = (float)c->d.self_r;
     q.nc = c->d.nc;
@@ -1355,11 +1353,11 @@ template <typename A> static pse_status lzb_setup(pse_batch *b) {
     q.tol = (A)c->p.lanczos_tol;
     reps.push_back(q);
     z.members.push_back(r);
-    const int G = c->tune_spmv_lanes ? c->tune_spmv_lanes : 3, unwrap = c->d.nc >= c->lds_B + 3 ? 1 : 0;
+    const int G = c->tune_spmv_lanes ? c->tune_spmv_lanes : 3;
     size_t g = 0;
-    while (g < gr.size() && !(gr[g].B == c->lds_B && gr[g].G == G && gr[g].unwrap == unwrap)) ++g;
+    while (g < gr.size() && !(gr[g].B == c->lds_B && gr[g].G == G)) ++g;
     if (g == gr.size()) {
-      gr.push_back(LzGroup{c->lds_B, G, unwrap, 0, 0, nullptr});
+      gr.push_back(LzGroup{c->lds_B, G, 0, 0, nullptr});
       pm.emplace_back();
     }
     for (int blk = 0; blk < c->lds_blocks; ++blk) pm[g].push_back(make_int2(k, blk));
@@ -1413,7 +1411,7 @@ template <typename A> static void lzb_launch(pse_batch *b) {
 // The batched neighbour build of a captured step: every replica on the LDS
 // path without the overlap repulsion and without the preconditioner (whose
 // features follow the build inside its set_positions), grouped by block
-// edge and halo form.
+// edge.
 static pse_status nbr_setup(pse_batch *b) {
   const int R = (int)b->ctx.size();
   std::vector<NbrRep> reps;
@@ -1431,7 +1429,6 @@ static pse_status nbr_setup(pse_batch *b) {
     q.flags = c->flags;
     q.cs = (float)c->d.cs;
     q.L = (float)c->d.L;
-    q.invL = (float)(1.0 / c->d.L);
     q.rc2 = (float)(c->p.rcut * c->p.rcut);
     q.nc = c->d.nc;
     q.n = c->n;
@@ -1439,11 +1436,10 @@ static pse_status nbr_setup(pse_batch *b) {
     q.hcap = c->hcap;
     reps.push_back(q);
     b->nb_members.push_back(r);
-    const int unwrap = c->d.nc >= c->lds_B + 3 ? 1 : 0;
     size_t g = 0;
-    while (g < gr.size() && !(gr[g].B == c->lds_B && gr[g].unwrap == unwrap)) ++g;
+    while (g < gr.size() && !(gr[g].B == c->lds_B)) ++g;
     if (g == gr.size()) {
-      gr.push_back(NbrGroup{c->lds_B, unwrap, 0, 0, nullptr});
+      gr.push_back(NbrGroup{c->lds_B, 0, 0, nullptr});
       pm.emplace_back();
     }
     for (int blk = 0; blk < c->lds_blocks; ++blk) pm[g].push_back(make_int2(k, blk));

@@ -676,71 +676,94 @@ __global__ __launch_bounds__(256) void k_spmv_exact(const double4 *__restrict__ 
 // Needs nc >= B + 2 (no halo cell appears twice).  B = 1 ... 4: blocks of
 // more cells keep enough targets per workgroup when cells hold few
 // particles (small rc).
+//
+// The halo is handled as (B+2)^2 columns of B + 2 consecutive z cells: the
+// particles of a column are one contiguous run of the sorted order, or two
+// where the column wraps around the box.  Every column is staged at the
+// periodic image that continues the block's own coordinates across the box
+// face, relative to the block centre.  Pairs then need no minimum-image
+// correction: both particles sit in cells that touch, at the images in which
+// they touch, and with at least 3 cells of side >= rc the other images of the
+// pair are more than rc apart.  The staged coordinates are small (a few
+// cells), so their differences keep the precision of the relative position
+// rather than of the box size.
 template <int B> struct Halo {
   static constexpr int HB = B + 2;
   static constexpr int NH = HB * HB * HB;  // 27, 64, 125 or 216 halo cells
-  static constexpr int NT = B * B * B;     // target cells
+  static constexpr int NC = HB * HB;       // halo columns
+  static constexpr int NT = B * B;         // target columns
 };
 
 template <int B> struct HaloTab {
-  int start[Halo<B>::NH];     // global sorted index of each halo cell's first particle
-  int base[Halo<B>::NH + 1];  // exclusive prefix of the halo cell counts (LDS offsets)
-  int tcell[Halo<B>::NT];     // halo index of each target cell
-  int tpre[Halo<B>::NT + 1];  // exclusive prefix of the target cell counts
-  int ntc;                    // number of target cells (< B^3 at the partial last block)
+  int g1[Halo<B>::NC], n1[Halo<B>::NC];  // first run: sorted index, length
+  int g2[Halo<B>::NC];                   // second run (after the z face)
+  int base[Halo<B>::NC + 1];             // LDS index of each column's first particle; the halo size
+  int tl[Halo<B>::NT];                   // LDS index of each target column's first target
+  int tpre[Halo<B>::NT + 1];             // exclusive prefix of the target counts
 };
 
-// blk: the block of B^3 cells this workgroup serves (by default the
-// XCD-renumbered workgroup index)
+// blk: the block of B^3 cells this workgroup serves.  Columns past the box
+// in the partial last blocks are staged like the others; their cells are no
+// targets.  One wavefront, one lane per column: the column's cell starts are
+// read together and the prefix sums taken across lanes.
 template <int B>
 __device__ __forceinline__ void halo_setup(const int *__restrict__ cell_start, int nc, HaloTab<B> &ht, int blk) {
-  constexpr int HB = Halo<B>::HB, NH = Halo<B>::NH;
+  constexpr int HB = Halo<B>::HB, NC = Halo<B>::NC, NT = Halo<B>::NT;
   const int nb = (nc + B - 1) / B;
   const int bz = blk % nb, by = (blk / nb) % nb, bx = blk / (nb * nb);
   if (threadIdx.x < 64) {
-    // one wavefront scans the halo cells, 64 at a time, carrying the sum
     const int lane = threadIdx.x;
-    int carry = 0;
-    for (int h0 = 0; h0 < NH; h0 += 64) {
-      const int h = h0 + lane;
-      int cnt = 0;
-      if (h < NH) {
-        const int hx = h / (HB * HB), hy = (h / HB) % HB, hz = h % HB;
-        const int gx = (bx * B - 1 + hx + nc) % nc, gy = (by * B - 1 + hy + nc) % nc,
-                  gz = (bz * B - 1 + hz + nc) % nc;
-        const int c = (gx * nc + gy) * nc + gz;
-        const int a = cell_start[c];
-        cnt = cell_start[c + 1] - a;
-        ht.start[h] = a;
-      }
-      int v = cnt;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const int u = __shfl_up(v, off, 64);
-        if (lane >= off) v += u;
-      }
-      if (h < NH) ht.base[h + 1] = carry + v;
-      carry += __shfl(v, 63, 64);
+    const int hx = lane / HB, hy = lane % HB;
+    int len = 0, tlen = 0, toff = 0;
+    if (lane < NC) {
+      const int row = (((bx * B - 1 + hx + nc) % nc) * nc + (by * B - 1 + hy + nc) % nc) * nc;
+      const int zl = bz * B - 1, z0 = zl < 0 ? nc - 1 : zl;  // first cell of the column
+      const int split = min(HB, nc - z0);                    // cells before the face
+      const int a1 = cell_start[row + z0], e1 = cell_start[row + z0 + split];
+      const int a2 = cell_start[row], e2 = cell_start[row + HB - split];
+      // targets: cells bz B ... of this column, as far as the box goes
+      const int zt = bz * B, zn = min(B, nc - zt);
+      const int t0 = cell_start[row + zt], t1 = cell_start[row + zt + zn];
+      const bool targ = hx >= 1 && hx <= B && hy >= 1 && hy <= B && bx * B + hx - 1 < nc && by * B + hy - 1 < nc;
+      ht.g1[lane] = a1;
+      ht.n1[lane] = e1 - a1;
+      ht.g2[lane] = a2;
+      len = (e1 - a1) + (e2 - a2);
+      tlen = targ ? t1 - t0 : 0;
+      toff = zl < 0 ? (e1 - a1) + (t0 - a2) : t0 - a1;
     }
+    int v = len;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int u = __shfl_up(v, off, 64);
+      if (lane >= off) v += u;
+    }
+    if (lane < NC) ht.base[lane + 1] = v;
     if (lane == 0) ht.base[0] = 0;
+    // lane t < B^2 takes target column t = (ox, oy)
+    const int from = (lane / B + 1) * HB + lane % B + 1;
+    const int tl = __shfl(v - len + toff, from & 63, 64);
+    int w = __shfl(tlen, from & 63, 64);
+    if (lane >= NT) w = 0;
+    const int own = w;
+#pragma unroll
+    for (int off = 1; off < NT; off <<= 1) {
+      const int u = __shfl_up(w, off, 64);
+      if (lane >= off) w += u;
+    }
+    if (lane < NT) {
+      ht.tl[lane] = tl;
+      ht.tpre[lane] = w - own;
+    }
+    if (lane == NT - 1) ht.tpre[NT] = w;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int k = 0, acc = 0;
-    for (int ox = 0; ox < B; ++ox)
-      for (int oy = 0; oy < B; ++oy)
-        for (int oz = 0; oz < B; ++oz) {
-          if (bx * B + ox >= nc || by * B + oy >= nc || bz * B + oz >= nc) continue;
-          const int h = ((ox + 1) * HB + (oy + 1)) * HB + (oz + 1);
-          ht.tcell[k] = h;
-          ht.tpre[k] = acc;
-          acc += ht.base[h + 1] - ht.base[h];
-          ++k;
-        }
-    ht.tpre[k] = acc;
-    ht.ntc = k;
-  }
-  __syncthreads();
+}
+
+// Sorted index of particle k of a halo column.
+template <int B> __device__ __forceinline__ int column_at(const HaloTab<B> &ht, int col, int k) {
+  const int n1 = ht.n1[col];
+  return k < n1 ? ht.g1[col] + k : ht.g2[col] + (k - n1);
 }
 
 // The staged halo plus the zero-source slot fit the `hcap` records the
@@ -749,68 +772,54 @@ __device__ __forceinline__ void halo_setup(const int *__restrict__ cell_start, i
 // workgroup then stages nothing, raises *ovf and returns, and the caller
 // redoes that system with capacities sized for it.  Uniform per workgroup.
 template <int B> __device__ __forceinline__ bool halo_fits(const HaloTab<B> &ht, int hcap, int *ovf) {
-  const bool ok = ht.base[Halo<B>::NH] + 1 <= hcap;
+  const bool ok = ht.base[Halo<B>::NC] + 1 <= hcap;
   if (!ok && threadIdx.x == 0) atomicOr(ovf, 1);
   return ok;
 }
 
-// LDS index e -> halo cell (largest h with base[h] <= e).
-template <int B> __device__ __forceinline__ int halo_cell_of(const HaloTab<B> &ht, int e) {
-  int lo = 0, hi = Halo<B>::NH;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (ht.base[mid] <= e) lo = mid;
+// put(LDS index, sorted index, position relative to the block centre) for
+// every halo particle: one wavefront per column.
+template <int B, typename Put>
+__device__ __forceinline__ void halo_stage(const float4 *__restrict__ pos, const HaloTab<B> &ht, int nc, float cs,
+                                           float L, int blk, Put put) {
+  constexpr int HB = Halo<B>::HB, NC = Halo<B>::NC;
+  const int nb = (nc + B - 1) / B;
+  const int bz = blk % nb, by = (blk / nb) % nb, bx = blk / (nb * nb);
+  const float c0 = 0.5f * B * cs;
+  const float cx = bx * B * cs + c0, cy = by * B * cs + c0, cz = bz * B * cs + c0;
+  auto image = [&](int g) { return g < 0 ? -L : (g >= nc ? L : 0.0f); };
+  const float zs1 = image(bz * B - 1), zs2 = bz == 0 ? 0.0f : L;  // of the two runs
+  const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+  for (int col = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); col < NC; col += nw) {
+    const float xs = image(bx * B - 1 + col / HB), ys = image(by * B - 1 + col % HB);
+    const int b0 = ht.base[col], len = ht.base[col + 1] - b0, n1 = ht.n1[col], g1 = ht.g1[col], g2 = ht.g2[col];
+#pragma unroll 2
+    for (int k = lane; k < len; k += 64) {
+      const bool first = k < n1;
+      const int g = first ? g1 + k : g2 + (k - n1);
+      float4 q = pos[g];
+      q.x = (q.x - cx) + xs;
+      q.y = (q.y - cy) + ys;
+      q.z = (q.z - cz) + (first ? zs1 : zs2);
+      put(b0 + k, g, q);
+    }
+  }
+}
+
+// target i of the block -> (target column, LDS index, sorted index)
+template <int B>
+__device__ __forceinline__ void target_of(const HaloTab<B> &ht, int i, int &t, int &li, int &s) {
+  // largest target column t with tpre[t] <= i
+  t = 0;
+  int hi = Halo<B>::NT;
+  while (hi - t > 1) {
+    const int mid = (t + hi) >> 1;
+    if (ht.tpre[mid] <= i) t = mid;
     else hi = mid;
   }
-  return lo;
-}
-
-// LDS halo records: positions as float4, or as float3 where only the
-// coordinates are read (12 bytes: more workgroups per CU)
-__device__ __forceinline__ void halo_put(float4 *l, int e, const float4 &q) { l[e] = q; }
-__device__ __forceinline__ void halo_put(float3 *l, int e, const float4 &q) { l[e] = make_float3(q.x, q.y, q.z); }
-
-template <int B, typename LT>
-__device__ __forceinline__ void halo_stage(const float4 *__restrict__ g, LT *l, const HaloTab<B> &ht) {
-  const int total = ht.base[Halo<B>::NH];
-  for (int e = threadIdx.x; e < total; e += blockDim.x) {
-    const int h = halo_cell_of<B>(ht, e);
-    halo_put(l, e, g[ht.start[h] + (e - ht.base[h])]);
-  }
-}
-
-// Stage positions relative to the block centre c, each at its periodic image
-// nearest to c: pairs then need no minimum-image correction (valid when the
-// block half-width plus rc stays below L/2, i.e. nc >= B + 3), and the
-// staged coordinates are small (a few cells), so that their differences
-// keep the precision of the relative position rather than of the box size.
-template <int B, typename LT>
-__device__ __forceinline__ void halo_stage_unwrapped(const float4 *__restrict__ g, LT *l, const HaloTab<B> &ht,
-                                                     float cx, float cy, float cz, float L, float invL) {
-  const int total = ht.base[Halo<B>::NH];
-  for (int e = threadIdx.x; e < total; e += blockDim.x) {
-    const int h = halo_cell_of<B>(ht, e);
-    float4 q = g[ht.start[h] + (e - ht.base[h])];
-    q.x = min_image(q.x - cx, L, invL);
-    q.y = min_image(q.y - cy, L, invL);
-    q.z = min_image(q.z - cz, L, invL);
-    halo_put(l, e, q);
-  }
-}
-
-// target i of the block -> (halo cell index, LDS index, global sorted index)
-template <int B> __device__ __forceinline__ void target_of(const HaloTab<B> &ht, int i, int &h, int &li, int &s) {
-  // largest target cell j with tpre[j] <= i
-  int j = 0, hi = ht.ntc;
-  while (hi - j > 1) {
-    const int mid = (j + hi) >> 1;
-    if (ht.tpre[mid] <= i) j = mid;
-    else hi = mid;
-  }
-  h = ht.tcell[j];
-  const int off = i - ht.tpre[j];
-  li = ht.base[h] + off;
-  s = ht.start[h] + off;
+  li = ht.tl[t] + (i - ht.tpre[t]);
+  const int col = (t / B + 1) * Halo<B>::HB + t % B + 1;
+  s = column_at<B>(ht, col, li - ht.base[col]);
 }
 
 // Per-block halo sizes (largest goes to flags[4]) for sizing the LDS: one
@@ -843,15 +852,16 @@ __global__ __launch_bounds__(256) void k_halo_size(const int *__restrict__ cell_
 //   f_s = sum_{t: r < 2a} krep (2a - r) d / r,  d = x_s - x_t,
 // into frep[s] (the candidates' distances are at hand; overlapping pairs
 // are rare, so the branch is almost never taken).
-template <int B, bool UNWRAP, bool REP>
+template <int B, bool REP>
 __device__ __forceinline__ void nbr_lds_block(const float4 *__restrict__ pos, const int *__restrict__ cell_start,
-                                              int nc, float cs, int n, float L, float invL, float rc2,
+                                              int nc, float cs, int n, float L, float rc2,
                                               uint16_t *__restrict__ nbr, int *__restrict__ cnt_out, int cap,
                                               int *__restrict__ flags, float contact, float krep,
                                               float4 *__restrict__ frep, int hcap, int blk) {
-  constexpr int HB = Halo<B>::HB, NH = Halo<B>::NH;
+  constexpr int HB = Halo<B>::HB, NC = Halo<B>::NC;
   extern __shared__ float3 hpos3[];  // coordinates only
   __shared__ HaloTab<B> ht;
+  __shared__ int cbase[NC * HB + 1];  // LDS index of each halo cell's first particle (z fastest)
   // for each 4-bit hit mask: (offsets of the set bits in 16-bit fields, low
   // and high word; 0xFFFF in each used field, low and high word)
   __shared__ uint4 pack_tab[16];
@@ -868,23 +878,33 @@ __device__ __forceinline__ void nbr_lds_block(const float4 *__restrict__ pos, co
   }
   halo_setup<B>(cell_start, nc, ht, blk);
   if (!halo_fits<B>(ht, hcap, flags + 7)) return;
-  if (UNWRAP) {
+  {
     const int nb = (nc + B - 1) / B;
     const int bz = blk % nb, by = (blk / nb) % nb, bx = blk / (nb * nb);
-    const float c0 = 0.5f * B * cs;
-    halo_stage_unwrapped<B>(pos, hpos3, ht, bx * B * cs + c0, by * B * cs + c0, bz * B * cs + c0, L, invL);
-  } else {
-    halo_stage<B>(pos, hpos3, ht);
+    for (int h = threadIdx.x; h < NC * HB; h += blockDim.x) {
+      const int col = h / HB, hz = h % HB, gz = bz * B - 1 + hz;
+      const int row = (((bx * B - 1 + col / HB + nc) % nc) * nc + (by * B - 1 + col % HB + nc) % nc) * nc;
+      const int c = cell_start[row + (gz + nc) % nc];
+      const bool second = bz == 0 ? gz >= 0 : gz >= nc;
+      cbase[h] = ht.base[col] + (second ? ht.n1[col] + c - ht.g2[col] : c - ht.g1[col]);
+    }
+    if (threadIdx.x == 0) cbase[NC * HB] = ht.base[NC];
   }
+  halo_stage<B>(pos, ht, nc, cs, L, blk, [&](int e, int, const float4 &q) { hpos3[e] = make_float3(q.x, q.y, q.z); });
   __syncthreads();
-  const int ntarg = ht.tpre[ht.ntc];
+  const int ntarg = ht.tpre[Halo<B>::NT];
   unsigned long long mine = 0;
   int mx = 0;
   uint4 *row = (uint4 *)nbr;
   for (int i = threadIdx.x; i < ntarg; i += blockDim.x) {
-    int h, li, s;
-    target_of(ht, i, h, li, s);
-    const int ox = h / (HB * HB) - 1, oy = (h / HB) % HB - 1, oz = h % HB - 1;
+    int tc, li, s;
+    target_of<B>(ht, i, tc, li, s);
+    const int ox = tc / B, oy = tc % B;
+    int oz = 0;  // the target's cell in its column
+    {
+      const int h0 = ((ox + 1) * HB + oy + 1) * HB + 2;
+      while (oz < B - 1 && cbase[h0 + oz] <= li) ++oz;
+    }
     const float3 p = hpos3[li];
     int k = 0;
     float fx = 0.f, fy = 0.f, fz = 0.f;  // overlap repulsion (REP)
@@ -895,23 +915,18 @@ __device__ __forceinline__ void nbr_lds_block(const float4 *__restrict__ pos, co
     for (int dx = -1; dx <= 1; ++dx)
       for (int dy = -1; dy <= 1; ++dy) {
         const int hh = ((ox + 1 + dx) * HB + (oy + 1 + dy)) * HB + oz;
-        const int e = ht.base[hh + 3];
+        const int e = cbase[hh + 3];
         // four candidates per step: their LDS reads are in flight together
         // (up to 3 past the run, into the next cell or the 3 padding slots
         // after the halo; masked out below)
-        for (int j0 = ht.base[hh]; j0 < e; j0 += 4) {
+        for (int j0 = cbase[hh]; j0 < e; j0 += 4) {
           float3 q[4];
 #pragma unroll
           for (int u = 0; u < 4; ++u) q[u] = hpos3[j0 + u];
           unsigned hit = 0;
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            float ddx = p.x - q[u].x, ddy = p.y - q[u].y, ddz = p.z - q[u].z;
-            if (!UNWRAP) {
-              ddx = min_image(ddx, L, invL);
-              ddy = min_image(ddy, L, invL);
-              ddz = min_image(ddz, L, invL);
-            }
+            const float ddx = p.x - q[u].x, ddy = p.y - q[u].y, ddz = p.z - q[u].z;
             const float r2 = ddx * ddx + ddy * ddy + ddz * ddz;
             const int j = j0 + u;
             hit |= (j < e && j != li && r2 <= rc2) ? 1u << u : 0u;
@@ -949,7 +964,7 @@ __device__ __forceinline__ void nbr_lds_block(const float4 *__restrict__ pos, co
     if ((k & 7) && (k >> 3) < (cap >> 3)) {
       // the rest of the last chunk points at the zero-source slot the
       // product stages after the halo (index = halo size)
-      const uint64_t sent = (uint64_t)ht.base[NH];
+      const uint64_t sent = (uint64_t)ht.base[NC];
 #pragma unroll
       for (int sl = 1; sl < 8; ++sl) {
         if (sl < (k & 7)) continue;
@@ -967,23 +982,23 @@ __device__ __forceinline__ void nbr_lds_block(const float4 *__restrict__ pos, co
   nbr_stats(mine, mx, flags);
 }
 
-template <int B, bool UNWRAP, bool REP = false>
+template <int B, bool REP>
 __global__ __launch_bounds__(512) void k_nbr_lds(const float4 *__restrict__ pos, const int *__restrict__ cell_start,
-                                                 int nc, float cs, int n, float L, float invL, float rc2,
+                                                 int nc, float cs, int n, float L, float rc2,
                                                  uint16_t *__restrict__ nbr, int *__restrict__ cnt_out, int cap,
                                                  int *__restrict__ flags, float contact, float krep,
                                                  float4 *__restrict__ frep, int hcap) {
-  nbr_lds_block<B, UNWRAP, REP>(pos, cell_start, nc, cs, n, L, invL, rc2, nbr, cnt_out, cap, flags, contact, krep,
+  nbr_lds_block<B, REP>(pos, cell_start, nc, cs, n, L, rc2, nbr, cnt_out, cap, flags, contact, krep,
                                 frep, hcap, xcd_block(blockIdx.x, gridDim.x));
 }
 
 // The neighbour build of many systems (a batch of replicas) in one launch:
 // pmap lists (system, block of that system) per workgroup.
-template <int B, bool UNWRAP>
+template <int B>
 __global__ __launch_bounds__(512) void k_nbr_lds_batch(const NbrRep *__restrict__ reps, const int2 *__restrict__ pmap) {
   const int2 rb = pmap[blockIdx.x];
   const NbrRep &r = reps[rb.x];
-  nbr_lds_block<B, UNWRAP, false>(r.pos, r.cell_start, r.nc, r.cs, r.n, r.L, r.invL, r.rc2, r.nbr, r.cnt, r.cap,
+  nbr_lds_block<B, false>(r.pos, r.cell_start, r.nc, r.cs, r.n, r.L, r.rc2, r.nbr, r.cnt, r.cap,
                                   r.flags, 0.0f, 0.0f, nullptr, r.hcap, rb.y);
 }
 
@@ -998,34 +1013,26 @@ __global__ __launch_bounds__(512) void k_nbr_lds_batch(const NbrRep *__restrict_
 // lane shuffles (the minimum for f21).
 constexpr int kFeatQ = 16;    // queue entries per lane
 constexpr int kFeatNT = 512;  // lanes per workgroup (two workgroups per CU)
-template <int B, bool UNWRAP>
+template <int B>
 __global__ __launch_bounds__(kFeatNT) void k_feat_lds(const float4 *__restrict__ pos, const int *__restrict__ cell_start,
-                                                   int nc, float cs, int n, float L, float invL,
+                                                   int nc, float cs, int n, float L,
                                                    const uint16_t *__restrict__ nbr, const int *__restrict__ cnt,
                                                    const float2 *__restrict__ tab, float inv_dr, float inv_mu0,
                                                    float fself, float a, float near2, uint16_t *__restrict__ feat,
                                                    int hcap, int *__restrict__ ovf) {
-  constexpr int NH = Halo<B>::NH;
   constexpr int G = 3, GPW = 64 / G;
   extern __shared__ float4 hpos[];
   __shared__ HaloTab<B> ht;
   __shared__ uint16_t queue[kFeatQ * kFeatNT];
   __shared__ float2 ftab[kTableN];
   for (int k = threadIdx.x; k < kTableN; k += blockDim.x) ftab[k] = tab[k];
-  halo_setup<B>(cell_start, nc, ht, xcd_block(blockIdx.x, gridDim.x));
+  const int blk = xcd_block(blockIdx.x, gridDim.x);
+  halo_setup<B>(cell_start, nc, ht, blk);
   if (!halo_fits<B>(ht, hcap, ovf)) return;
-  if (UNWRAP) {
-    const int nb = (nc + B - 1) / B;
-    const int blk = xcd_block(blockIdx.x, gridDim.x);
-    const int bz = blk % nb, by = (blk / nb) % nb, bx = blk / (nb * nb);
-    const float c0 = 0.5f * B * cs;
-    halo_stage_unwrapped<B>(pos, hpos, ht, bx * B * cs + c0, by * B * cs + c0, bz * B * cs + c0, L, invL);
-  } else {
-    halo_stage<B>(pos, hpos, ht);
-  }
+  halo_stage<B>(pos, ht, nc, cs, L, blk, [&](int e, int, const float4 &q) { hpos[e] = q; });
   __syncthreads();
   const FGTable fg{ftab, inv_dr};
-  const int ntarg = ht.tpre[ht.ntc];
+  const int ntarg = ht.tpre[Halo<B>::NT];
   const uint4 *row = (const uint4 *)nbr;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int grp = lane / G, g = lane - grp * G;
@@ -1035,19 +1042,14 @@ __global__ __launch_bounds__(kFeatNT) void k_feat_lds(const float4 *__restrict__
     const int i = i0 + wave * GPW + grp;
     const bool act = ingrp && i < ntarg;
     int h = 0, li = 0, s = 0;
-    if (act) target_of(ht, i, h, li, s);
+    if (act) target_of<B>(ht, i, h, li, s);
     const float4 p = hpos[li];
     FeatAcc<float> acc;
     acc.init(0.0f);
     int nq = 0;
     // one near pair into the sums (F, G - F from the LDS table)
     auto add = [&](const float4 &q) {
-      float ddx = p.x - q.x, ddy = p.y - q.y, ddz = p.z - q.z;
-      if (!UNWRAP) {
-        ddx = min_image(ddx, L, invL);
-        ddy = min_image(ddy, L, invL);
-        ddz = min_image(ddz, L, invL);
-      }
+      const float ddx = p.x - q.x, ddy = p.y - q.y, ddz = p.z - q.z;
       const float r2 = ddx * ddx + ddy * ddy + ddz * ddz;
       const bool nz = r2 > 1e-24f;
       const float ir = nz ? __frsqrt_rn(r2) : 0.0f;
@@ -1076,12 +1078,7 @@ __global__ __launch_bounds__(kFeatNT) void k_feat_lds(const float4 *__restrict__
       for (int u = 0; u < 8; ++u) {
         const int j = (wd[u >> 1] >> (16 * (u & 1))) & 0xFFFF;
         const float4 q = hpos[kb + u < c ? j : li];
-        float ddx = p.x - q.x, ddy = p.y - q.y, ddz = p.z - q.z;
-        if (!UNWRAP) {
-          ddx = min_image(ddx, L, invL);
-          ddy = min_image(ddy, L, invL);
-          ddz = min_image(ddz, L, invL);
-        }
+        const float ddx = p.x - q.x, ddy = p.y - q.y, ddz = p.z - q.z;
         const float r2 = ddx * ddx + ddy * ddy + ddz * ddz;
         if (kb + u < c && r2 < near2) {
           myq[kFeatNT * nq] = (uint16_t)j;
@@ -1120,21 +1117,19 @@ __global__ __launch_bounds__(kFeatNT) void k_feat_lds(const float4 *__restrict__
 // halves of 4 (padding entries read the zero source), the LDS reads of a half
 // in flight together.  Registers are held to 64 so that two 1024-lane
 // workgroups share a compute unit: one stages its halo while the other
-// computes.  With UNWRAP the staged positions are the images nearest the
-// block centre.
+// computes.
 // A Lanczos iteration passes `done`, the flag of its state: once set the
 // product is skipped (null: always formed).  With PC (Lanczos on
 // A = P M_r P^T): src holds P^T u and the epilogue forms out = P M_r src;
 // Pm holds the rows of P_i as (x, y, z, 0).
-template <int B, bool UNWRAP, bool PC, int G>
+template <int B, bool PC, int G>
 __device__ __forceinline__ void spmv_lds_block(const float4 *__restrict__ pos, const float4 *__restrict__ src,
                                                const int *__restrict__ cell_start, int nc, float cs, int n, int hcap,
-                                               float L, float invL, const uint16_t *__restrict__ nbr,
+                                               float L, const uint16_t *__restrict__ nbr,
                                                const int *__restrict__ cnt, const float2 *__restrict__ tab,
                                                float inv_dr, float self_r, float4 *__restrict__ out,
                                                const int *__restrict__ done, int *__restrict__ ovf,
                                                const float4 *__restrict__ Pm, int blk) {
-  constexpr int NH = Halo<B>::NH;
   static_assert(G >= 2 && G <= 4, "lanes per target");
   constexpr int GPW = 64 / G;               // groups per wavefront (lane 63 idle at G = 3)
   extern __shared__ float4 smem[];
@@ -1148,51 +1143,31 @@ __device__ __forceinline__ void spmv_lds_block(const float4 *__restrict__ pos, c
   // a halo past the capacity stages nothing and computes no target
   const bool fits = halo_fits<B>(ht, hcap, ovf);
   if (fits) {
-    const int nb = (nc + B - 1) / B;
-    const int bz = blk % nb, by = (blk / nb) % nb, bx = blk / (nb * nb);
-    const float c0 = 0.5f * B * cs;
-    const float cx = bx * B * cs + c0, cy = by * B * cs + c0, cz = bz * B * cs + c0;
-    const int total = ht.base[NH];
     // slot `total`: a source with zero vector at the block centre, read by
     // the padding entries of the neighbour chunks (contributes exactly 0)
     // coordinates are staged in units of the table spacing rc / kTableK:
     // r is then the table coordinate itself (the (G - F) term is invariant)
     if (threadIdx.x == 0) {
-      // (UNWRAP: coordinates relative to the block centre)
-      hA[total] = UNWRAP ? make_float4(0.0f, 0.0f, 0.0f, 0.0f)
-                         : make_float4(cx * inv_dr, cy * inv_dr, cz * inv_dr, 0.0f);
+      const int total = ht.base[Halo<B>::NC];
+      hA[total] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
       hB[total] = make_float2(0.0f, 0.0f);
     }
-    for (int e = threadIdx.x; e < total; e += blockDim.x) {
-      const int h = halo_cell_of<B>(ht, e);
-      const int gi = ht.start[h] + (e - ht.base[h]);
-      float4 q = pos[gi];
+    halo_stage<B>(pos, ht, nc, cs, L, blk, [&](int e, int gi, const float4 &q) {
       const float4 v = src[gi];
-      if (UNWRAP) {
-        q.x = min_image(q.x - cx, L, invL);
-        q.y = min_image(q.y - cy, L, invL);
-        q.z = min_image(q.z - cz, L, invL);
-      }
-      q.x *= inv_dr;
-      q.y *= inv_dr;
-      q.z *= inv_dr;
-      q.w = v.x;
-      hA[e] = q;
+      hA[e] = make_float4(q.x * inv_dr, q.y * inv_dr, q.z * inv_dr, v.x);
       hB[e] = make_float2(v.y, v.z);
-    }
+    });
   }
   __syncthreads();
-  const int ntarg = fits ? ht.tpre[ht.ntc] : 0;
-  const float Ls = L * inv_dr, invLs = invL / inv_dr;  // box in table units
+  const int ntarg = fits ? ht.tpre[Halo<B>::NT] : 0;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int grp = lane / G, g = lane - grp * G;
   const bool ingrp = grp < GPW;
-  
   for (int i0 = 0; i0 < ntarg; i0 += (int)(blockDim.x >> 6) * GPW) {
     const int i = i0 + wave * GPW + grp;
     const bool act = ingrp && i < ntarg;
     int h = 0, li = 0, s = 0;
-    if (act) target_of(ht, i, h, li, s);
+    if (act) target_of<B>(ht, i, h, li, s);
     const float4 pa = hA[li];
     const float2 pb = hB[li];
     float ax = 0.f, ay = 0.f, az = 0.f;
@@ -1225,11 +1200,6 @@ __device__ __forceinline__ void spmv_lds_block(const float4 *__restrict__ pos, c
           dx[u] = pa.x - q[u].x;
           dy[u] = pa.y - q[u].y;
           dz[u] = pa.z - q[u].z;
-          if (!UNWRAP) {
-            dx[u] = min_image(dx[u], Ls, invLs);
-            dy[u] = min_image(dy[u], Ls, invLs);
-            dz[u] = min_image(dz[u], Ls, invLs);
-          }
           const float r2 = fmaxf(dx[u] * dx[u] + dy[u] * dy[u] + dz[u] * dz[u], 1e-20f);
           rinv[u] = __frsqrt_rn(r2);
           const float uu = r2 * rinv[u];
@@ -1281,13 +1251,13 @@ __device__ __forceinline__ void spmv_lds_block(const float4 *__restrict__ pos, c
   }
 }
 
-template <int B, bool UNWRAP, bool PC = false, int G = 3>
+template <int B, bool PC = false, int G = 3>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_spmv_lds(
     const float4 *__restrict__ pos, const float4 *__restrict__ src, const int *__restrict__ cell_start, int nc, float cs,
-    int n, int hcap, float L, float invL, const uint16_t *__restrict__ nbr, const int *__restrict__ cnt,
+    int n, int hcap, float L, const uint16_t *__restrict__ nbr, const int *__restrict__ cnt,
     const float2 *__restrict__ tab, float inv_dr, float self_r, float4 *__restrict__ out,
     const int *__restrict__ done, int *__restrict__ ovf, const float4 *__restrict__ Pm = nullptr) {
-  spmv_lds_block<B, UNWRAP, PC, G>(pos, src, cell_start, nc, cs, n, hcap, L, invL, nbr, cnt, tab, inv_dr, self_r, out,
+  spmv_lds_block<B, PC, G>(pos, src, cell_start, nc, cs, n, hcap, L, nbr, cnt, tab, inv_dr, self_r, out,
                                    done, ovf, Pm, xcd_block(blockIdx.x, gridDim.x));
 }
 
@@ -1785,24 +1755,24 @@ __global__ __launch_bounds__(1024) void k_lz_step(const typename vec4<T>::type *
 // one particle, as in the single-system kernels).
 __device__ __forceinline__ int lz_parts(int n) { return min(kRedBlock, (n + 255) / 256); }
 
-template <int B, bool UNWRAP, typename A, int G>
+template <int B, typename A, int G>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_spmv_lds_batch(
     const LzRep<A> *__restrict__ reps, const int2 *__restrict__ pmap, int m) {
   const int2 rb = pmap[blockIdx.x];
   const LzRep<A> &r = reps[rb.x];
-  spmv_lds_block<B, UNWRAP, false, G>(r.pos, r.V + (size_t)m * r.n, r.cell_start, r.nc, r.cs, r.n, r.hcap, r.L, r.invL,
+  spmv_lds_block<B, false, G>(r.pos, r.V + (size_t)m * r.n, r.cell_start, r.nc, r.cs, r.n, r.hcap, r.L,
                                       r.nbr, r.cnt, r.tab, r.inv_dr, r.self_r, r.t, m > 0 ? &r.st->done : nullptr,
                                       r.ovf, nullptr, rb.y);
 }
 
 // M_r F of the systems whose record carries forces (the others' blocks exit)
-template <int B, bool UNWRAP, typename A, int G>
+template <int B, typename A, int G>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_spmv_lds_batch_plain(
     const LzRep<A> *__restrict__ reps, const int2 *__restrict__ pmap) {
   const int2 rb = pmap[blockIdx.x];
   const LzRep<A> &r = reps[rb.x];
   if (!r.fs) return;
-  spmv_lds_block<B, UNWRAP, false, G>(r.pos, r.fs, r.cell_start, r.nc, r.cs, r.n, r.hcap, r.L, r.invL, r.nbr, r.cnt,
+  spmv_lds_block<B, false, G>(r.pos, r.fs, r.cell_start, r.nc, r.cs, r.n, r.hcap, r.L, r.nbr, r.cnt,
                                       r.tab, r.inv_dr, r.self_r, r.ur, nullptr, r.ovf, nullptr, rb.y);
 }
 
@@ -2187,26 +2157,19 @@ template <typename K> static void allow_lds(K kernel, size_t bytes) {
 void launch_nbr_lds(pse_ctx *c) {
   ProfScope ps(c, PSE_STAGE_NBR);
   const size_t smem = sizeof(float3) * (size_t)(c->hcap + 3);  // 3 slots read past the last cell
-  const float L = (float)c->d.L, invL = (float)(1.0 / c->d.L), rc2 = (float)(c->p.rcut * c->p.rcut);
+  const float L = (float)c->d.L, rc2 = (float)(c->p.rcut * c->p.rcut);
   auto *nb = (uint16_t *)c->nbr;
-  const bool unwrap = c->d.nc >= c->lds_B + 3;
   auto go = [&](auto kern) {
     allow_lds(kern, smem);
     kern<<<c->lds_blocks, 512, smem, c->stream>>>((const float4 *)c->pos_s, c->cell_start, c->d.nc, (float)c->d.cs,
-                                                  c->n, L, invL, rc2, nb, c->nbr_cnt, c->nbr_cap, c->flags,
+                                                  c->n, L, rc2, nb, c->nbr_cnt, c->nbr_cap, c->flags,
                                                   (float)(2.0 * c->p.a), (float)c->rep_k, (float4 *)c->vbuf[kRepBuf],
                                                   c->hcap);
   };
   const bool rep = c->rep_k > 0;
   with_block_edge(c->lds_B, [&](auto b) {
     constexpr int BE = decltype(b)::value;
-    if (rep) {
-      if (unwrap) go(k_nbr_lds<BE, true, true>);
-      else go(k_nbr_lds<BE, false, true>);
-    } else {
-      if (unwrap) go(k_nbr_lds<BE, true>);
-      else go(k_nbr_lds<BE, false>);
-    }
+    rep ? go(k_nbr_lds<BE, true>) : go(k_nbr_lds<BE, false>);
   });
 }
 
@@ -2215,12 +2178,8 @@ void launch_nbr_batch(hipStream_t s, const NbrRep *reps, const NbrGroup *groups,
     const NbrGroup &gr = groups[g];
     with_block_edge(gr.B, [&](auto b) {
       constexpr int BE = decltype(b)::value;
-      auto go = [&](auto kern) {
-        allow_lds(kern, gr.smem);
-        kern<<<gr.nblk, 512, gr.smem, s>>>(reps, gr.pmap);
-      };
-      if (gr.unwrap) go(k_nbr_lds_batch<BE, true>);
-      else go(k_nbr_lds_batch<BE, false>);
+      allow_lds(k_nbr_lds_batch<BE>, gr.smem);
+      k_nbr_lds_batch<BE><<<gr.nblk, 512, gr.smem, s>>>(reps, gr.pmap);
     });
   }
 }
@@ -2229,44 +2188,36 @@ void launch_nbr_batch(hipStream_t s, const NbrRep *reps, const NbrGroup *groups,
 void launch_feat_lds(pse_ctx *c) {
   ProfScope ps(c, PSE_STAGE_PRECOND);
   const size_t smem = sizeof(float4) * (size_t)c->hcap;
-  const float L = (float)c->d.L, invL = (float)(1.0 / c->d.L);
-  const bool unwrap = c->d.nc >= c->lds_B + 3;
+  const float L = (float)c->d.L;
   const float inv_mu0 = (float)(1.0 / c->d.mu0), fself = (float)(c->d.self_r / c->d.mu0);
   const float near2 = (float)(20.25 * c->p.a * c->p.a);  // r < 4.5a
-  auto go = [&](auto kern) {
-    allow_lds(kern, smem);
-    kern<<<c->lds_blocks, kFeatNT, smem, c->stream>>>((const float4 *)c->pos_s, c->cell_start, c->d.nc,
-                                                     (float)c->d.cs, c->n, L, invL, (const uint16_t *)c->nbr, c->nbr_cnt,
-                                                  (const float2 *)c->table, (float)(kTableK / c->p.rcut), inv_mu0,
-                                                  fself, (float)c->p.a, near2, c->pc_feat, c->hcap, c->flags + 7);
-  };
   with_block_edge(c->lds_B, [&](auto b) {
     constexpr int BE = decltype(b)::value;
-    if (unwrap) go(k_feat_lds<BE, true>);
-    else go(k_feat_lds<BE, false>);
+    allow_lds(k_feat_lds<BE>, smem);
+    k_feat_lds<BE><<<c->lds_blocks, kFeatNT, smem, c->stream>>>(
+        (const float4 *)c->pos_s, c->cell_start, c->d.nc, (float)c->d.cs, c->n, L, (const uint16_t *)c->nbr, c->nbr_cnt,
+        (const float2 *)c->table, (float)(kTableK / c->p.rcut), inv_mu0, fself, (float)c->p.a, near2, c->pc_feat,
+        c->hcap, c->flags + 7);
   });
 }
 
 template <bool PC = false>
 static void spmv_lds(pse_ctx *c, const float4 *src, float4 *out, const int *done = nullptr) {
   const size_t smem = (sizeof(float4) + sizeof(float2)) * (size_t)c->hcap;
-  const float L = (float)c->d.L, invL = (float)(1.0 / c->d.L);
+  const float L = (float)c->d.L;
   const auto *nb = (const uint16_t *)c->nbr;
   const float inv_dr = (float)(kTableK / c->p.rcut), self_r = (float)c->d.self_r;
-  const bool unwrap = c->d.nc >= c->lds_B + 3;
   auto go = [&](auto kernel) {
     allow_lds(kernel, smem);
     kernel<<<c->lds_blocks, 1024, smem, c->stream>>>((const float4 *)c->pos_s, src, c->cell_start, c->d.nc,
-                                                      (float)c->d.cs, c->n, c->hcap, L, invL, nb, c->nbr_cnt,
+                                                      (float)c->d.cs, c->n, c->hcap, L, nb, c->nbr_cnt,
                                                       c->table, inv_dr, self_r, out, done, c->flags + 7,
                                                       (const float4 *)c->pc_P);
   };
   auto pick = [&](auto g) {
     constexpr int G = decltype(g)::value;
     with_block_edge(c->lds_B, [&](auto b) {
-      constexpr int BE = decltype(b)::value;
-      if (unwrap) go(k_spmv_lds<BE, true, PC, G>);
-      else go(k_spmv_lds<BE, false, PC, G>);
+      go(k_spmv_lds<decltype(b)::value, PC, G>);
     });
   };
   // lanes per target: 3 built in (the best measured at phi = 0.3 with
@@ -2414,7 +2365,7 @@ template <typename T, typename A> void launch_lz_iters(pse_ctx *c, int m0, int k
 }
 
 // The batched Krylov loop: per iteration the product of every group of
-// systems sharing a block edge, halo form and lanes per target, then the
+// systems sharing a block edge and lanes per target, then the
 // vector work and the checks of all systems.
 template <typename A>
 void launch_lz_batch(hipStream_t s, const LzRep<A> *reps, const LzGroup *groups, int ngroups,
@@ -2430,8 +2381,7 @@ void launch_lz_batch(hipStream_t s, const LzRep<A> *reps, const LzGroup *groups,
         };
         auto pick = [&](auto gl) {
           constexpr int GL = decltype(gl)::value;
-          if (gr.unwrap) go(k_spmv_lds_batch<BE, true, A, GL>);
-          else go(k_spmv_lds_batch<BE, false, A, GL>);
+          go(k_spmv_lds_batch<BE, A, GL>);
         };
         if (gr.G == 2) pick(std::integral_constant<int, 2>{});
         else if (gr.G == 4) pick(std::integral_constant<int, 4>{});
@@ -2597,8 +2547,7 @@ void launch_lz_batch_plain(hipStream_t s, const LzRep<A> *reps, const LzGroup *g
       };
       auto pick = [&](auto gl) {
         constexpr int GL = decltype(gl)::value;
-        if (gr.unwrap) go(k_spmv_lds_batch_plain<BE, true, A, GL>);
-        else go(k_spmv_lds_batch_plain<BE, false, A, GL>);
+        go(k_spmv_lds_batch_plain<BE, A, GL>);
       };
       if (gr.G == 2) pick(std::integral_constant<int, 2>{});
       else if (gr.G == 4) pick(std::integral_constant<int, 4>{});

@@ -25,9 +25,8 @@ constexpr size_t kLdsPerCU = 160 * 1024;  // LDS of one gfx950 compute unit
 constexpr int kInterpLanes = 512;         // built-in interpolation workgroup (one wavefront per particle)
 // largest dynamic + table LDS of one workgroup of the staged near-field kernels
 constexpr size_t kLdsBudget = 150 * 1024;
-// static LDS of the staged near-field product beside its F/G table: the
-// halo table of block edge B (cell starts and prefix sums of the (B+2)^3 halo
-// cells and the B^3 target cells) plus reduction slots
+// static LDS of the staged near-field kernels beside the F/G table, at most:
+// the halo table of block edge B and the cell bases of the neighbour build
 constexpr size_t lds_static_extra(int B) {
   return 4 * (2 * (size_t)(B + 2) * (B + 2) * (B + 2) + 2 * (size_t)B * B * B + 3) + 256;
 }
@@ -141,7 +140,7 @@ struct SampMaps {
 };
 
 // One system of a batched neighbour build (LDS path, no repulsion), and the
-// systems sharing one kernel (block edge, halo form): pmap lists (system,
+// systems sharing one kernel (block edge): pmap lists (system,
 // block) for each of the nblk workgroups, smem the largest halo's LDS.
 struct NbrRep {
   const float4 *pos;
@@ -149,11 +148,11 @@ struct NbrRep {
   uint16_t *nbr;
   int *cnt;
   int *flags;
-  float cs, L, invL, rc2;
+  float cs, L, rc2;
   int nc, n, cap, hcap;
 };
 struct NbrGroup {
-  int B, unwrap, nblk;
+  int B, nblk;
   size_t smem;
   const int2 *pmap;
 };
@@ -174,16 +173,16 @@ template <typename A> struct LzRep {
   LzState<A> *st;
   const double2 *nodes;     // quadrature of the tridiagonal root
   A *partials;              // [0, kRedBlock): |u|^2; [kRedBlock, 2 kRedBlock): alpha_m
-  float cs, L, invL, inv_dr, self_r;
+  float cs, L, inv_dr, self_r;
   int nc, n, hcap, maxit;
   A tol;
 };
 
 // The systems of a batched Krylov loop whose LDS products share one kernel:
-// block edge B, lanes per target G, halo form; pmap lists (system, block)
+// block edge B, lanes per target G; pmap lists (system, block)
 // for each of the nblk workgroups, smem the largest halo's LDS.
 struct LzGroup {
-  int B, G, unwrap, nblk;
+  int B, G, nblk;
   size_t smem;
   const int2 *pmap;
 };
