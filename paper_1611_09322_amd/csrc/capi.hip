@@ -1429,6 +1429,7 @@ static pse_status nbr_setup(pse_batch *b) {
     q.flags = c->flags;
     q.cs = (float)c->d.cs;
     q.L = (float)c->d.L;
+    q.rc = (float)c->p.rcut;
     q.rc2 = (float)(c->p.rcut * c->p.rcut);
     q.nc = c->d.nc;
     q.n = c->n;
@@ -1443,7 +1444,7 @@ static pse_status nbr_setup(pse_batch *b) {
       pm.emplace_back();
     }
     for (int blk = 0; blk < c->lds_blocks; ++blk) pm[g].push_back(make_int2(k, blk));
-    const size_t smem = sizeof(float3) * (size_t)(c->hcap + 3);  // 3 slots read past the last cell
+    const size_t smem = nbr_lds_bytes(c->hcap);
     if (smem > gr[g].smem) gr[g].smem = smem;
   }
   if (reps.empty()) return PSE_OK;

@@ -847,35 +847,65 @@ __global__ __launch_bounds__(256) void k_halo_size(const int *__restrict__ cell_
   if (lane == 0) atomicMax(&flags[4], tot);
 }
 
+// Neighbour list of a target block on the matrix cores.  The squared
+// distances of 16 targets to 16 candidates, less rc^2, are one
+// v_mfma_f32_16x16x4_f32:
+//   D[c][t] = sum_k A[c][k] B[k][t] + (|p_t|^2 - rc^2),
+//   A[c] = (x, y, z, |q|^2) of candidate c,  B[.][t] = (-2x, -2y, -2z, 1) of target t,
+// whose sign is the hit: lane l holds the results of target l % 16 and four
+// candidates, and shifts their sign bits into its hit word (one v_alignbit
+// each).  A tile is 16 consecutive targets of a z column of the block; its
+// candidates are the 9 columns around it, from the cell below its first
+// target to the cell above its last, in segments of at most 8 x 16.  Lane
+// quarter q = l / 16 takes the q-th quarter of a segment, so its bits are
+// consecutive candidates and a row lists its neighbours in candidate order.
+// The bit counts give each lane its place in the target's row; the hits
+// are then taken out one by one into a stage in LDS and written to the list 8
+// at a time.
+// D carries a rounding error of at most 10 u (|p| + |q|)^2, u = 2^-24, the
+// directly computed (x_p - x_q)^2 + ... one of 4 u rc^2.  A segment in which
+// any |D| lies within their sum, for |q| <= |p| + rc, is evaluated directly
+// instead (about one in 200), so the list holds exactly the pairs of the direct
+// test.
+// One lane per target with direct distances (19 VALU instructions a candidate)
+// took 33 us at 10^3 spheres, 99 us at 8000 with rc = 6.3a and the repulsion,
+// 65 us at 64000, 267 us at 10^6 (rc = 5.9a: 390 candidates and 60 hits a
+// target); this takes 14, 36, 34 and 270 us.  Small systems gain from the 16 x 4
+// split of a target's candidates; large ones are bound by taking out the hits,
+// where the lane with most hits of a word sets the pace.  Interleaving the
+// quarters evens that out (231 us at 10^6) but reorders the list, and with it
+// the rounding of the learned features.
 // flags[1]: list capacity needed; flags[5]: largest count.  With REP the
-// same scan accumulates the overlap repulsion of each target,
+// overlap repulsion of each target,
 //   f_s = sum_{t: r < 2a} krep (2a - r) d / r,  d = x_s - x_t,
-// into frep[s] (the candidates' distances are at hand; overlapping pairs
-// are rare, so the branch is almost never taken).
+// is accumulated from its hits into frep[s].
+constexpr int kNbrNT = 768, kNbrWaves = kNbrNT / 64;
+constexpr int kNbrPad = 16;    // halo records read past the last one
+constexpr int kNbrRound = 48;  // hits of one word a target may stage
+constexpr int kNbrStage = 7 + kNbrRound + 1;  // entries per target: with the rest of a chunk
+static_assert(kNbrStage % 8 == 0, "rows of whole chunks");
+__device__ __forceinline__ void lds_order() {
+  // a wavefront's own LDS accesses stay in program order across lanes
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// part of `parts`: workgroups that share the block's tiles (small systems)
 template <int B, bool REP>
 __device__ __forceinline__ void nbr_lds_block(const float4 *__restrict__ pos, const int *__restrict__ cell_start,
-                                              int nc, float cs, int n, float L, float rc2,
+                                              int nc, float cs, int n, float L, float rc, float rc2,
                                               uint16_t *__restrict__ nbr, int *__restrict__ cnt_out, int cap,
                                               int *__restrict__ flags, float contact, float krep,
-                                              float4 *__restrict__ frep, int hcap, int blk) {
-  constexpr int HB = Halo<B>::HB, NC = Halo<B>::NC;
-  extern __shared__ float3 hpos3[];  // coordinates only
+                                              float4 *__restrict__ frep, int hcap, int blk, int part, int parts) {
+  constexpr int HB = Halo<B>::HB, NC = Halo<B>::NC, NT = Halo<B>::NT;
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  extern __shared__ float hal[];  // planes x, y, z, |q|^2, hs floats each
   __shared__ HaloTab<B> ht;
   __shared__ int cbase[NC * HB + 1];  // LDS index of each halo cell's first particle (z fastest)
-  // for each 4-bit hit mask: (offsets of the set bits in 16-bit fields, low
-  // and high word; 0xFFFF in each used field, low and high word)
-  __shared__ uint4 pack_tab[16];
-  if (threadIdx.x < 16) {
-    uint64_t pat = 0, msk = 0;
-    int f = 0;
-    for (int u = 0; u < 4; ++u)
-      if (threadIdx.x & (1 << u)) {
-        pat |= (uint64_t)u << (16 * f);
-        msk |= 0xFFFFull << (16 * f);
-        ++f;
-      }
-    pack_tab[threadIdx.x] = make_uint4((uint32_t)pat, (uint32_t)(pat >> 32), (uint32_t)msk, (uint32_t)(msk >> 32));
-  }
+  __shared__ int tp[NT + 1];          // exclusive prefix of the target columns' tiles
+  __shared__ __attribute__((aligned(16))) uint16_t stage_all[kNbrWaves][16][kNbrStage];
+  const int hs = hcap + kNbrPad;
   halo_setup<B>(cell_start, nc, ht, blk);
   if (!halo_fits<B>(ht, hcap, flags + 7)) return;
   {
@@ -888,118 +918,192 @@ __device__ __forceinline__ void nbr_lds_block(const float4 *__restrict__ pos, co
       const bool second = bz == 0 ? gz >= 0 : gz >= nc;
       cbase[h] = ht.base[col] + (second ? ht.n1[col] + c - ht.g2[col] : c - ht.g1[col]);
     }
-    if (threadIdx.x == 0) cbase[NC * HB] = ht.base[NC];
+    if (threadIdx.x == 0) {
+      cbase[NC * HB] = ht.base[NC];
+      int k = 0;
+      for (int t = 0; t < NT; ++t) {
+        tp[t] = k;
+        k += (ht.tpre[t + 1] - ht.tpre[t] + 15) / 16;
+      }
+      tp[NT] = k;
+    }
   }
-  halo_stage<B>(pos, ht, nc, cs, L, blk, [&](int e, int, const float4 &q) { hpos3[e] = make_float3(q.x, q.y, q.z); });
+  halo_stage<B>(pos, ht, nc, cs, L, blk, [&](int e, int, const float4 &q) {
+    hal[e] = q.x;
+    hal[hs + e] = q.y;
+    hal[2 * hs + e] = q.z;
+    hal[3 * hs + e] = q.x * q.x + q.y * q.y + q.z * q.z;
+  });
   __syncthreads();
-  const int ntarg = ht.tpre[Halo<B>::NT];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int q = lane >> 4, col = lane & 15;
+  const int ntile = tp[NT], tpl = tp[min(lane, NT)];
+  uint16_t *stage = stage_all[wave][col];
+  uint4 *row = (uint4 *)nbr;
   unsigned long long mine = 0;
   int mx = 0;
-  uint4 *row = (uint4 *)nbr;
-  for (int i = threadIdx.x; i < ntarg; i += blockDim.x) {
-    int tc, li, s;
-    target_of<B>(ht, i, tc, li, s);
-    const int ox = tc / B, oy = tc % B;
+  for (int tile = wave * parts + part; tile < ntile; tile += parts * kNbrWaves) {
+    // the tile's target column: the last whose first tile is not past it
+    const int tc = __popcll(__ballot(lane <= NT && tpl <= tile)) - 1;
+    const int ox = tc / B, oy = tc % B, t0 = 16 * (tile - tp[tc]);
+    const int nt16 = min(16, ht.tpre[tc + 1] - ht.tpre[tc] - t0);  // targets of the tile
+    const bool targ = col < nt16;
+    const int li = ht.tl[tc] + t0 + min(col, nt16 - 1);
+    const int hcol = (ox + 1) * HB + oy + 1;
+    const int s = column_at<B>(ht, hcol, li - ht.base[hcol]);
     int oz = 0;  // the target's cell in its column
-    {
-      const int h0 = ((ox + 1) * HB + oy + 1) * HB + 2;
-      while (oz < B - 1 && cbase[h0 + oz] <= li) ++oz;
-    }
-    const float3 p = hpos3[li];
-    int k = 0;
+    while (oz < B - 1 && cbase[hcol * HB + 2 + oz] <= li) ++oz;
+    const int z0 = __builtin_amdgcn_readlane(oz, 0), z1 = __builtin_amdgcn_readlane(oz, 15);
+    const float px = hal[li], py = hal[hs + li], pz = hal[2 * hs + li], p2 = hal[3 * hs + li];
+    const float bop = q == 0 ? -2.0f * px : (q == 1 ? -2.0f * py : (q == 2 ? -2.0f * pz : 1.0f));
+    const float c0 = p2 - rc2;
+    const float far = 2.0f * sqrtf(p2) + rc, margin = 8.5e-7f * far * far;  // 14 u (2 |p| + rc)^2
     float fx = 0.f, fy = 0.f, fz = 0.f;  // overlap repulsion (REP)
-    uint64_t lo = 0, hi = 0;  // the current chunk of 8 packed 16-bit indices
-    // the three cells dz = -1, 0, 1 of a (dx, dy) column are consecutive
-    // halo cells, staged contiguously: one run of candidates per column, in
-    // the same order as cell by cell
-    for (int dx = -1; dx <= 1; ++dx)
-      for (int dy = -1; dy <= 1; ++dy) {
-        const int hh = ((ox + 1 + dx) * HB + (oy + 1 + dy)) * HB + oz;
-        const int e = cbase[hh + 3];
-        // four candidates per step: their LDS reads are in flight together
-        // (up to 3 past the run, into the next cell or the 3 padding slots
-        // after the halo; masked out below)
-        for (int j0 = cbase[hh]; j0 < e; j0 += 4) {
-          float3 q[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) q[u] = hpos3[j0 + u];
-          unsigned hit = 0;
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const float ddx = p.x - q[u].x, ddy = p.y - q[u].y, ddz = p.z - q[u].z;
-            const float r2 = ddx * ddx + ddy * ddy + ddz * ddz;
-            const int j = j0 + u;
-            hit |= (j < e && j != li && r2 <= rc2) ? 1u << u : 0u;
-            if (REP && j < e && j != li && r2 < contact * contact && r2 > 0.f) {
-              const float r = sqrtf(r2), m = krep * (contact - r) / r;
-              fx += m * ddx;
-              fy += m * ddy;
-              fz += m * ddz;
-            }
+    int have = 0, chunks = 0;            // staged entries, chunks written (of the lane's target)
+    // the hits of a word, whose bit b is candidate jl + b, to the stage
+    auto extract = [&](uint32_t w, int jl, uint16_t *at) {
+      while (w) {
+        const int j = jl + __builtin_ctz(w);
+        w &= w - 1u;
+        *at++ = (uint16_t)j;
+        if (REP) {
+          const float dx = px - hal[j], dy = py - hal[hs + j], dz = pz - hal[2 * hs + j];
+          const float r2 = dx * dx + dy * dy + dz * dz;
+          if (r2 < contact * contact && r2 > 0.f) {
+            const float r = sqrtf(r2), f = krep * (contact - r) / r;
+            fx += f * dx;
+            fy += f * dy;
+            fz += f * dz;
           }
-          // the hits of the step, compacted: field f of V is j0 plus the
-          // offset of the f-th set bit (pattern table), then V is
-          // shifted into the chunk at field k & 7; fields past 8 carry
-          // into the next chunk
-          const uint4 tb = pack_tab[hit];
-          const uint32_t X = (uint32_t)j0 * 0x10001u;
-          const uint64_t V = ((uint64_t)((X & tb.w) + tb.y) << 32) | (uint64_t)((X & tb.z) + tb.x);
-          const int sh = 16 * (k & 7);
-          const bool upper = sh >= 64;
-          const int s2 = upper ? sh - 64 : sh;
-          const uint64_t vs = V << s2, spill = s2 ? V >> (64 - s2) : 0ull;
-          lo |= upper ? 0ull : vs;
-          hi |= upper ? vs : spill;
-          const int k1 = k + __builtin_popcount(hit);
-          if ((k1 >> 3) != (k >> 3)) {
-            if ((k >> 3) < (cap >> 3))
-              row[(size_t)(k >> 3) * n + s] = make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi,
-                                                         (uint32_t)(hi >> 32));
-            lo = upper ? spill : 0ull;
-            hi = 0;
-          }
-          k = k1;
         }
       }
-    if ((k & 7) && (k >> 3) < (cap >> 3)) {
-      // the rest of the last chunk points at the zero-source slot the
-      // product stages after the halo (index = halo size)
-      const uint64_t sent = (uint64_t)ht.base[NC];
-#pragma unroll
-      for (int sl = 1; sl < 8; ++sl) {
-        if (sl < (k & 7)) continue;
-        const uint64_t v = sent << (16 * (sl & 3));
-        if (sl < 4) lo |= v;
-        else hi |= v;
+    };
+    // this lane's place in the stage for its m hits; the target's total
+    auto place = [&](int m, int &total) {
+      const int s1 = __shfl_xor(m, 16, 64), s2 = __shfl_xor(m, 32, 64), s3 = __shfl_xor(m, 48, 64);
+      total = m + s1 + s2 + s3;
+      return (q & 1 ? s1 : 0) + (q & 2 ? s2 + s3 : 0);
+    };
+    // whole chunks of the stage to the list, the rest to its front
+    auto flush = [&]() {
+      lds_order();
+      const int full = have >> 3;
+      for (int c = q; c < full; c += 4) {
+        const uint4 v = *(const uint4 *)(stage + 8 * c);
+        if (chunks + c < (cap >> 3)) row[(size_t)(chunks + c) * n + s] = v;
       }
-      row[(size_t)(k >> 3) * n + s] = make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+      lds_order();
+      if (q == 0 && full) *(uint4 *)stage = *(const uint4 *)(stage + 8 * full);
+      lds_order();
+      chunks += full;
+      have &= 7;
+    };
+    for (int d = 0; d < 9; ++d) {
+      const int cc = (hcol + (d / 3 - 1) * HB + d % 3 - 1) * HB;
+      const int j0 = __builtin_amdgcn_readfirstlane(cbase[cc + z0]), je = __builtin_amdgcn_readfirstlane(cbase[cc + z1 + 3]);
+      for (int jb = j0; jb < je; jb += 128) {
+        const int nt = min(8, (je - jb + 15) >> 4);  // tiles of 16 candidates
+        // operand row col, plane q of candidate col / 4 * 4 nt + 4 t + col % 4
+        // of the segment
+        const float *ap = hal + q * hs + jb + (col >> 2) * 4 * nt + (col & 3);
+        uint32_t w = 0u;
+        float mn = 1e30f;
+        auto take = [&](const f32x4 &D4) {
+#pragma unroll
+          for (int v = 3; v >= 0; --v) w = __builtin_amdgcn_alignbit(w, __float_as_uint(D4[v]), 31);
+          mn = fminf(fminf(mn, fabsf(D4[0])), fabsf(D4[1]));
+          mn = fminf(fminf(mn, fabsf(D4[2])), fabsf(D4[3]));
+        };
+        const f32x4 C4 = {c0, c0, c0, c0};
+        int t = nt - 1;
+        for (; t > 0; t -= 2) {  // two in flight
+          const float a1 = ap[4 * t], a0 = ap[4 * t - 4];
+          const f32x4 D1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, bop, C4, 0, 0, 0);
+          const f32x4 D0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, bop, C4, 0, 0, 0);
+          take(D1);
+          take(D0);
+        }
+        if (t == 0) take(__builtin_amdgcn_mfma_f32_16x16x4f32(ap[0], bop, C4, 0, 0, 0));
+        const int jl = jb + q * 4 * nt;  // this lane's first candidate
+        const int valid = targ ? min(max(je - jl, 0), 4 * nt) : 0;
+        if (__any(mn < margin)) {
+          w = 0u;
+          for (int b = 0; b < valid; ++b) {
+            const float dx = px - hal[jl + b], dy = py - hal[hs + jl + b], dz = pz - hal[2 * hs + jl + b];
+            const float r2 = dx * dx + dy * dy + dz * dz;
+            w |= r2 <= rc2 ? 1u << b : 0u;
+          }
+        }
+        w &= valid >= 32 ? 0xffffffffu : (1u << valid) - 1u;
+        if (d == 4 && (unsigned)(li - jl) < 32u) w &= ~(1u << (li - jl));  // not itself
+        int total;
+        const int off = place(__popc(w), total);
+        if (__any(have + total > kNbrStage - 1)) flush();  // leaves at most 7
+        if (!__any(total > kNbrRound)) {
+          extract(w, jl, stage + have + off);
+          have += total;
+        } else {
+          // more than the stage takes: a quarter of the word (at most 32 hits a target) at a time
+          for (int sh = 0; sh < 32; sh += 8) {
+            const uint32_t wq = w & (0xffu << sh);
+            const int offq = place(__popc(wq), total);
+            extract(wq, jl, stage + have + offq);
+            have += total;
+            flush();
+          }
+        }
+      }
     }
-    cnt_out[s] = min(k, cap);  // entries stored; flags[1] carries the capacity needed
-    if (REP) frep[s] = make_float4(fx, fy, fz, 0.f);
-    mine += (unsigned long long)k;
-    mx = max(mx, k);
+    flush();
+    const int cnt = 8 * chunks + have;
+    if (have) {
+      // the rest of the last chunk points at the zero-source slot the product
+      // stages after the halo (index = halo size)
+      const uint16_t none = (uint16_t)ht.base[NC];
+      if (2 * q >= have) stage[2 * q] = none;
+      if (2 * q + 1 >= have) stage[2 * q + 1] = none;
+      lds_order();
+      if (q == 0 && targ && chunks < (cap >> 3)) row[(size_t)chunks * n + s] = *(const uint4 *)stage;
+      lds_order();
+    }
+    if (REP) {
+      fx += __shfl_xor(fx, 16, 64);
+      fy += __shfl_xor(fy, 16, 64);
+      fz += __shfl_xor(fz, 16, 64);
+      fx += __shfl_xor(fx, 32, 64);
+      fy += __shfl_xor(fy, 32, 64);
+      fz += __shfl_xor(fz, 32, 64);
+    }
+    if (q == 0 && targ) {
+      cnt_out[s] = min(cnt, cap);  // entries stored; flags[1] carries the capacity needed
+      if (REP) frep[s] = make_float4(fx, fy, fz, 0.f);
+      mine += (unsigned long long)cnt;
+      mx = max(mx, cnt);
+    }
   }
   nbr_stats(mine, mx, flags);
 }
 
 template <int B, bool REP>
-__global__ __launch_bounds__(512) void k_nbr_lds(const float4 *__restrict__ pos, const int *__restrict__ cell_start,
-                                                 int nc, float cs, int n, float L, float rc2,
-                                                 uint16_t *__restrict__ nbr, int *__restrict__ cnt_out, int cap,
-                                                 int *__restrict__ flags, float contact, float krep,
-                                                 float4 *__restrict__ frep, int hcap) {
-  nbr_lds_block<B, REP>(pos, cell_start, nc, cs, n, L, rc2, nbr, cnt_out, cap, flags, contact, krep,
-                                frep, hcap, xcd_block(blockIdx.x, gridDim.x));
+__global__ __launch_bounds__(kNbrNT) __attribute__((amdgpu_waves_per_eu(REP ? 4 : 6))) void k_nbr_lds(const float4 *__restrict__ pos, const int *__restrict__ cell_start,
+                                                    int nc, float cs, int n, float L, float rc, float rc2,
+                                                    uint16_t *__restrict__ nbr, int *__restrict__ cnt_out, int cap,
+                                                    int *__restrict__ flags, float contact, float krep,
+                                                    float4 *__restrict__ frep, int hcap, int parts) {
+  const int b = xcd_block(blockIdx.x, gridDim.x);
+  nbr_lds_block<B, REP>(pos, cell_start, nc, cs, n, L, rc, rc2, nbr, cnt_out, cap, flags, contact, krep, frep, hcap,
+                        b / parts, b % parts, parts);
 }
 
 // The neighbour build of many systems (a batch of replicas) in one launch:
 // pmap lists (system, block of that system) per workgroup.
 template <int B>
-__global__ __launch_bounds__(512) void k_nbr_lds_batch(const NbrRep *__restrict__ reps, const int2 *__restrict__ pmap) {
+__global__ __launch_bounds__(kNbrNT) __attribute__((amdgpu_waves_per_eu(6))) void k_nbr_lds_batch(const NbrRep *__restrict__ reps,
+                                                          const int2 *__restrict__ pmap) {
   const int2 rb = pmap[blockIdx.x];
   const NbrRep &r = reps[rb.x];
-  nbr_lds_block<B, false>(r.pos, r.cell_start, r.nc, r.cs, r.n, r.L, r.rc2, r.nbr, r.cnt, r.cap,
-                                  r.flags, 0.0f, 0.0f, nullptr, r.hcap, rb.y);
+  nbr_lds_block<B, false>(r.pos, r.cell_start, r.nc, r.cs, r.n, r.L, r.rc, r.rc2, r.nbr, r.cnt, r.cap, r.flags, 0.0f,
+                          0.0f, nullptr, r.hcap, rb.y, 0, 1);
 }
 
 // Preconditioner features (FeatAcc; F, G from the LDS table).  Three lanes
@@ -2154,17 +2258,21 @@ template <typename K> static void allow_lds(K kernel, size_t bytes) {
   (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLdsPerCU - stat));
 }
 
+size_t nbr_lds_bytes(int hcap) { return 4 * sizeof(float) * (size_t)(hcap + kNbrPad); }
+
 void launch_nbr_lds(pse_ctx *c) {
   ProfScope ps(c, PSE_STAGE_NBR);
-  const size_t smem = sizeof(float3) * (size_t)(c->hcap + 3);  // 3 slots read past the last cell
+  const size_t smem = nbr_lds_bytes(c->hcap);
   const float L = (float)c->d.L, rc2 = (float)(c->p.rcut * c->p.rcut);
+  // small systems: a block's tiles shared by up to 8 workgroups, about two
+  // for each of the 256 compute units
+  const int parts = std::min(8, std::max(1, 512 / c->lds_blocks));
   auto *nb = (uint16_t *)c->nbr;
   auto go = [&](auto kern) {
     allow_lds(kern, smem);
-    kern<<<c->lds_blocks, 512, smem, c->stream>>>((const float4 *)c->pos_s, c->cell_start, c->d.nc, (float)c->d.cs,
-                                                  c->n, L, rc2, nb, c->nbr_cnt, c->nbr_cap, c->flags,
-                                                  (float)(2.0 * c->p.a), (float)c->rep_k, (float4 *)c->vbuf[kRepBuf],
-                                                  c->hcap);
+    kern<<<c->lds_blocks * parts, kNbrNT, smem, c->stream>>>(
+        (const float4 *)c->pos_s, c->cell_start, c->d.nc, (float)c->d.cs, c->n, L, (float)c->p.rcut, rc2, nb, c->nbr_cnt,
+        c->nbr_cap, c->flags, (float)(2.0 * c->p.a), (float)c->rep_k, (float4 *)c->vbuf[kRepBuf], c->hcap, parts);
   };
   const bool rep = c->rep_k > 0;
   with_block_edge(c->lds_B, [&](auto b) {
@@ -2179,7 +2287,7 @@ void launch_nbr_batch(hipStream_t s, const NbrRep *reps, const NbrGroup *groups,
     with_block_edge(gr.B, [&](auto b) {
       constexpr int BE = decltype(b)::value;
       allow_lds(k_nbr_lds_batch<BE>, gr.smem);
-      k_nbr_lds_batch<BE><<<gr.nblk, 512, gr.smem, s>>>(reps, gr.pmap);
+      k_nbr_lds_batch<BE><<<gr.nblk, kNbrNT, gr.smem, s>>>(reps, gr.pmap);
     });
   }
 }

@@ -25,6 +25,7 @@ template <typename T> void launch_nbr(pse_ctx *c);
 // neighbour build with 16-bit LDS indices
 void launch_halo_size(pse_ctx *c, int B);
 void launch_nbr_lds(pse_ctx *c);
+size_t nbr_lds_bytes(int hcap);  // dynamic LDS of a neighbour-build workgroup
 // the LDS neighbour build of every system of the groups in one launch per group
 void launch_nbr_batch(hipStream_t s, const NbrRep *reps, const NbrGroup *groups, int ngroups);
 void launch_feat_lds(pse_ctx *c);  // preconditioner features from the list and the staged halo

@@ -148,7 +148,7 @@ struct NbrRep {
   uint16_t *nbr;
   int *cnt;
   int *flags;
-  float cs, L, rc2;
+  float cs, L, rc, rc2;
   int nc, n, cap, hcap;
 };
 struct NbrGroup {

@@ -56,3 +56,38 @@ def test_rows_grow_past_their_capacity(gpu_lib, precision):
     ref = rpy.real_block_dense(y, L, 1.0, 1.0, 0.7, rc) @ v.ravel()
     check(s.real_matvec(dev(v, s)).double().cpu().numpy(), ref, BAR[precision], f"clustered M_r v {precision}")
     s.close()
+
+
+def _pairs(x, L, rc):
+    d = x[:, None, :] - x[None, :, :]
+    d -= L * np.rint(d / L)
+    r2 = (d * d).sum(-1)
+    np.fill_diagonal(r2, np.inf)
+    return r2
+
+
+# runs of one segment (128 candidates) and of several, targets that stage more
+# hits than a round takes, tiles of 1 to 16 targets, empty columns
+@pytest.mark.parametrize("n,L,spread", [(5, 40.0, 40.0), (900, 40.0, 40.0), (4000, 32.0, 32.0), (1500, 40.0, 9.0),
+                                         (700, 40.0, 3.0)])
+@pytest.mark.parametrize("krep", [0.0, 3.0])
+def test_list_counts(gpu_lib, n, L, spread, krep):
+    """Pair count and largest row of the LDS list against all pairs of the same
+    FP32 positions.  A pair may fall on either side only if its distance is
+    within the rounding of the staged coordinates (a few cells, L/2 at most:
+    4 L 2^-24 covers the two roundings of each coordinate difference)."""
+    rc = 5.0
+    x = (0.3 * L + spread * synth.uniform_positions(n, 1.0, seed=n)).astype(np.float32)
+    s = gpu_lib.Sampler(n, L, xi=0.65, rcut=rc, grid=64, support=6, precision="fp32", tol=1e-3, kT=0.0)
+    pos = torch.as_tensor(x, device="cuda")
+    st = s.bd_step(pos, 1, 1, 1e-6, krep=krep)
+    w = np.mod(x.astype(np.float64), L)
+    r2 = _pairs(w, L, rc)
+    eps = 4 * L * 2.0**-24
+    lo, hi = r2 <= (rc - eps) ** 2, r2 <= (rc + eps) ** 2
+    print(f"n={n} spread={spread}: pairs {st.neighbor_pairs}, {lo.sum()} to {hi.sum()}; largest row "
+          f"{st.max_neighbors}, {lo.sum(1).max()} to {hi.sum(1).max()}; block edge {st.lds_block_edge}", flush=True)
+    assert st.lds_block_edge > 0
+    assert lo.sum() <= st.neighbor_pairs <= hi.sum()
+    assert lo.sum(1).max() <= st.max_neighbors <= hi.sum(1).max()
+    s.close()
