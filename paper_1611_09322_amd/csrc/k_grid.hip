@@ -872,18 +872,36 @@ DI void spread_tile_block(const typename vec4<T>::type *__restrict__ pos, const 
 // a product of a (16 x K) matrix of x weights with a (K x 16) matrix of
 // per-particle (y, z) terms, K the particles whose support reaches the
 // block.  One workgroup owns a tile of 16 x 8 x (8 NW) nodes and lists the
-// particles overlapping it (from the linked cells, as the VALU form does);
-// each of its 4 NW wavefronts owns a 16 x 4 x 4 sub-tile, keeps its own list
-// of the particles that reach it (contiguous, in candidate order) and runs
-// three v_mfma_f32_16x16x4_f32 (one per component) per four listed
-// particles.  Operand layout: lane l holds A[x = l % 16][particle l / 16]
+// particles overlapping it (from the linked cells, as the VALU form does)
+// into a ring; each of its 4 NW wavefronts owns a 16 x 4 x 4 sub-tile, picks
+// from every batch of kSpreadBatch listed particles the ones that reach it
+// (in candidate order) and runs three v_mfma_f32_16x16x4_f32 (one per
+// component) per four of them.  Operand layout: lane l holds A[x = l % 16][particle l / 16]
 // and B[particle l / 16][column l % 16], column = 4 y + z; the result gives
 // lane l rows 4 (l / 16) .. + 3 of column l % 16.  Weights outside a
 // particle's P-node support along an axis are exactly zero, so every
 // product outside the P^3 support adds +0.  The particle order, and with it
-// the result, is fixed: no atomics, every node written once.  Needs M a
+// the result, is fixed: no atomics, every node written once.
+// A listed particle reaches a third of the sub-tiles of a 16 x 8 x 16 tile, so
+// its 1-D weights are evaluated once for the tile and a step reads its
+// operands from LDS.  10^6 particles on 256^3 nodes (P = 8): 312 us against
+// 363 us with the weights evaluated in every step; listing takes 85 us of it,
+// the weights 40 us, and the steps 170 us: 33 matrix instructions a particle
+// (110 us of matrix-core time, a node block of 16 x 4 x 4 for a support of
+// 8^3) and their operand reads.  Batches of 192 took 318 us; components folded
+// into the x weights and weights evaluated on the support only, 316 us.  Needs M a
 // multiple of 16 and 8 NW, M >= 2 max(16, 8 NW) + P.
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+constexpr int kSpreadBatch = 128;
+// Steps C, C + 2, .. 14 in pairs (their LDS reads are in flight together)
+// while entries are left; lane 16 kp + C of R holds the entry of row kp.
+template <int C, typename F> DI void spread_steps(int R, int left, F &&step2) {
+  step2(__builtin_amdgcn_mov_dpp(R, 0x150 + C, 0xF, 0xF, true),  // row broadcast of lane C
+        __builtin_amdgcn_mov_dpp(R, 0x151 + C, 0xF, 0xF, true));
+  if constexpr (C + 2 < 16) {
+    if (left > 4 * C + 8) spread_steps<C + 2>(R, left, step2);
+  }
+}
 template <int P, int NW>
 DI void spread_mfma_block(const float4 *__restrict__ pos, const float4 *__restrict__ f,
                           const int *__restrict__ cell_start, int nc, float cs, int M, float h, float invh,
@@ -891,11 +909,15 @@ DI void spread_mfma_block(const float4 *__restrict__ pos, const float4 *__restri
   constexpr int TX = 16, TY = 8, TZ = 8 * NW;
   constexpr int NV = 4 * NW;  // wavefronts = sub-tiles: 2 along y, 2 NW along z
   constexpr int NT = 64 * NV;
-  __shared__ float4 lpu[NT + 1];     // image coordinate of the particle nearest the tile
-  __shared__ float4 lf[NT + 1];      // its force
-  __shared__ int ls0[NT + 1];        // first support node per axis (tile-local) + 64, 8 bits each
-  __shared__ uint16_t sidx[NV][NT];  // per sub-tile, contiguous over the listing wavefronts
-  __shared__ int scnt[NV][NV];       // [sub-tile][wavefront that listed them]
+  constexpr int EB = kSpreadBatch;            // particles per weight batch
+  constexpr int QC = NT + EB;                 // ring of listed particles: a round and an incomplete batch
+  constexpr int WS = TX + TY + TZ + 4;        // a row of weights and the force
+  __shared__ float4 lpu[QC];                  // image coordinate of the particle nearest the tile; first
+                                              // support node per axis (tile-local) + 64, 8 bits each, in w
+  __shared__ int lt[QC];                      // its index
+  __shared__ __attribute__((aligned(16))) float wt[(EB + 1) * WS];  // rows wx (TX), wy (TY), wz (TZ), f; row EB zero
+  __shared__ uint16_t sidx[NV][EB + 8];       // per sub-tile: byte offsets of its rows
+  __shared__ int scnt[NV];                    // hits of each listing wavefront
   // the cell columns of one batch: start and length of the first z run,
   // start of the wrapped second run, inclusive prefix of the run lengths
   __shared__ int colA1[64], colN1[64], colA2[64], colEnd[64];
@@ -911,11 +933,75 @@ DI void spread_mfma_block(const float4 *__restrict__ pos, const float4 *__restri
   f32x4_t acc[3];
 #pragma unroll
   for (int c = 0; c < 3; ++c) acc[c] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-  if (threadIdx.x == 0) {  // the empty entry: support offsets -64 reach no node of the tile
-    lpu[NT] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    lf[NT] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    ls0[NT] = 0;
-  }
+  if (threadIdx.x < WS) wt[EB * WS + threadIdx.x] = 0.0f;
+  int head = 0, nq = 0;  // ring: first entry, entries
+  // the sums of the m <= EB entries from the ring's head
+  auto batch = [&](int m) {
+    // this sub-tile's entries, in order, with eight empty ones after the last
+    int total = 0;
+#pragma unroll
+    for (int b = 0; b < EB; b += 64) {
+      const int e = b + lane;
+      int r = head + e;
+      r -= r >= QC ? QC : 0;
+      const int sp = e < m ? __float_as_int(lpu[r].w) : 0;
+      const int sy = ((sp >> 8) & 255) - 64 - y0, sz = ((sp >> 16) & 255) - 64 - z0;
+      const bool in = e < m && sy <= 3 && sy + P - 1 >= 0 && sz <= 3 && sz + P - 1 >= 0;
+      const unsigned long long bal = __ballot(in);
+      if (in) sidx[wave][total + __popcll(bal & ((1ull << lane) - 1ull))] = (uint16_t)(4 * e * WS);
+      total += __popcll(bal);
+    }
+    if (lane < 8) sidx[wave][total + lane] = (uint16_t)(4 * EB * WS);
+    // 8 lanes per entry evaluate its weights, zero outside its support
+    const int r8 = threadIdx.x & 7;
+    for (int e = threadIdx.x >> 3; e < m; e += NT / 8) {
+      int r = head + e;
+      r -= r >= QC ? QC : 0;
+      const float4 pv = lpu[r];
+      float4 fv;
+      if (r8 == 0) fv = f[lt[r]];
+      const int sp = __float_as_int(pv.w);
+      const int sx = (sp & 255) - 64, sy = ((sp >> 8) & 255) - 64, sz = ((sp >> 16) & 255) - 64;
+      float *w = wt + e * WS + r8;
+      auto put = [&](int at, int node, int t0d, float p, int s0, float c) {
+        const float d = (float)(t0d + node) * h - p;
+        const float g = c * gauss_exp(-d * d * inv2s2);
+        w[at] = (unsigned)(node - s0) < (unsigned)P ? g : 0.0f;
+      };
+#pragma unroll
+      for (int k = 0; k < TX; k += 8) put(k, k + r8, t0x, pv.x, sx, norm);
+      put(TX, r8, t0y, pv.y, sy, 1.0f);
+#pragma unroll
+      for (int k = 0; k < TZ; k += 8) put(TX + TY + k, k + r8, t0z, pv.z, sz, 1.0f);
+      if (r8 == 0) *(float4 *)(w + TX + TY + TZ) = fv;
+    }
+    __syncthreads();
+    // steps of four entries, sixteen at a time: lane (kp, col) reads the row
+    // offset of entry kp of step col, which step col takes by a row broadcast
+    const char *wa = (const char *)(wt + col), *wy = (const char *)(wt + TX + y0 + yc),
+               *wz = (const char *)(wt + TX + TY + z0 + zc), *wf = (const char *)(wt + TX + TY + TZ);
+    auto step2 = [&](int o0, int o1) {
+      const float x0 = *(const float *)(wa + o0), x1 = *(const float *)(wa + o1);
+      const float y0 = *(const float *)(wy + o0), y1 = *(const float *)(wy + o1);
+      const float z0 = *(const float *)(wz + o0), z1 = *(const float *)(wz + o1);
+      const float4 f0 = *(const float4 *)(wf + o0), f1 = *(const float4 *)(wf + o1);
+      const float b0 = y0 * z0, b1 = y1 * z1;
+      acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(x0, b0 * f0.x, acc[0], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x0, b0 * f0.y, acc[1], 0, 0, 0);
+      acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(x0, b0 * f0.z, acc[2], 0, 0, 0);
+      acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(x1, b1 * f1.x, acc[0], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x1, b1 * f1.y, acc[1], 0, 0, 0);
+      acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(x1, b1 * f1.z, acc[2], 0, 0, 0);
+    };
+    for (int k = 0; k < total; k += 64) {
+      const int R = sidx[wave][min(k + 4 * col + kp, EB + 7)];
+      spread_steps<0>(R, total - k, step2);
+    }
+    head += m;
+    head -= head >= QC ? QC : 0;
+    nq -= m;
+    __syncthreads();  // the weights and the ring are rewritten next
+  };
   int cl[3], cn[3];
   {
     const float inv_cs = 1.0f / cs;
@@ -967,7 +1053,7 @@ DI void spread_mfma_block(const float4 *__restrict__ pos, const float4 *__restri
     __syncthreads();
     const int ntot = colEnd[63];
     {
-      for (int c0 = 0; c0 < ntot; c0 += NT) {
+      for (int c0 = 0; c0 < max(ntot, 1); c0 += NT) {
         const int ci = c0 + (int)threadIdx.x;
         int t = 0, s0[3] = {0, 0, 0};
         float pu[3] = {0.0f, 0.0f, 0.0f};
@@ -996,74 +1082,28 @@ DI void spread_mfma_block(const float4 *__restrict__ pos, const float4 *__restri
             hit = hit && (s0[d] <= tt[d] - 1) && (s0[d] + P - 1 >= 0);
           }
         }
-        const unsigned long long below = (1ull << lane) - 1ull;
+        // the hits to the ring, in candidate order
         const unsigned long long bal = __ballot(hit);
-        const int e = 64 * wave + __popcll(bal & below);
-        // sub-tiles reached: y quarters ylo..yhi, z quarters zlo..zhi
-        const int ylo = s0[1] > 0 ? s0[1] >> 2 : 0, yhi = min(1, (s0[1] + P - 1) >> 2);
-        const int zlo = s0[2] > 0 ? s0[2] >> 2 : 0, zhi = min(2 * NW - 1, (s0[2] + P - 1) >> 2);
-        unsigned long long bw[NV];
+        if (lane == 0) scnt[wave] = __popcll(bal);
+        __syncthreads();
+        int off = nq, add = 0;
 #pragma unroll
-        for (int w = 0; w < NV; ++w) {
-          const int qy = w & 1, qz = w >> 1;
-          bw[w] = __ballot(hit && qy >= ylo && qy <= yhi && qz >= zlo && qz <= zhi);
-          if (lane == 0) scnt[w][wave] = __popcll(bw[w]);
+        for (int from = 0; from < NV; ++from) {
+          const int cw = scnt[from];
+          add += cw;
+          off += from < wave ? cw : 0;
         }
         if (hit) {
-          lpu[e] = make_float4(pu[0], pu[1], pu[2], 0.0f);
-          const float4 fv = f[t];
-          lf[e] = make_float4(fv.x, fv.y, fv.z, 0.0f);
-          ls0[e] = (s0[0] + 64) | ((s0[1] + 64) << 8) | ((s0[2] + 64) << 16);
+          int r = head + off + __popcll(bal & ((1ull << lane) - 1ull));
+          r -= r >= QC ? QC : 0;
+          lpu[r] = make_float4(pu[0], pu[1], pu[2],
+                               __int_as_float((s0[0] + 64) | ((s0[1] + 64) << 8) | ((s0[2] + 64) << 16)));
+          lt[r] = t;
         }
+        nq += add;
         __syncthreads();
-        // sub-tile lists in listing-wavefront order: lane w < NV sums the
-        // counts of sub-tile w (its offset for this wavefront and its total)
-        int offl = 0, totl = 0;
-        if (lane < NV) {
-#pragma unroll
-          for (int from = 0; from < NV; ++from) {
-            const int cw = scnt[lane][from];
-            totl += cw;
-            offl += from < wave ? cw : 0;
-          }
-        }
-#pragma unroll
-        for (int w = 0; w < NV; ++w) {
-          const int off = __builtin_amdgcn_readlane(offl, w);
-          if ((bw[w] >> lane) & 1ull) sidx[w][off + __popcll(bw[w] & below)] = (uint16_t)e;
-        }
-        const int total = __builtin_amdgcn_readlane(totl, wave);
-        __syncthreads();
-        // steps of four list entries; slots past the end read the empty
-        // entry NT (zero force, support out of reach), so the loop is
-        // branch-free.  The next step's entry is read while this one runs.
-        auto entry = [&](int k) {
-          const int idx = k + kp;
-          const int ee = sidx[wave][min(idx, total - 1)];
-          return idx < total ? ee : NT;
-        };
-        int ee_n = entry(0);
-        float4 pv_n = lpu[ee_n], fv_n = lf[ee_n];
-        int sp_n = ls0[ee_n];
-        for (int k = 0; k < total; k += 4) {
-          const float4 pv = pv_n, fv = fv_n;
-          const int sp = sp_n;
-          ee_n = entry(k + 4);
-          pv_n = lpu[ee_n];
-          fv_n = lf[ee_n];
-          sp_n = ls0[ee_n];
-          const int ix = col - ((sp & 255) - 64), iy = y0 + yc - (((sp >> 8) & 255) - 64),
-                    iz = z0 + zc - (((sp >> 16) & 255) - 64);
-          const float dx = (float)(t0x + col) * h - pv.x, dy = (float)(t0y + y0 + yc) * h - pv.y,
-                      dz = (float)(t0z + z0 + zc) * h - pv.z;
-          const float ex = norm * gauss_exp(-dx * dx * inv2s2), eyz = gauss_exp(-(dy * dy + dz * dz) * inv2s2);
-          const float wx = (unsigned)ix < (unsigned)P ? ex : 0.0f;
-          const float wyz = ((unsigned)iy < (unsigned)P && (unsigned)iz < (unsigned)P) ? eyz : 0.0f;
-          acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(wx, wyz * fv.x, acc[0], 0, 0, 0);
-          acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(wx, wyz * fv.y, acc[1], 0, 0, 0);
-          acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(wx, wyz * fv.z, acc[2], 0, 0, 0);
-        }
-        __syncthreads();  // the list and the counts are rewritten next
+        const bool last = cb + 64 >= ncol && c0 + NT >= ntot;
+        while (nq >= EB || (last && nq > 0)) batch(min(nq, EB));
       }
     }
   }
@@ -1078,11 +1118,9 @@ DI void spread_mfma_block(const float4 *__restrict__ pos, const float4 *__restri
 }
 
 template <int P, int NW>
-__global__ __launch_bounds__(256 * NW) void k_spread_mfma(const float4 *__restrict__ pos,
-                                                          const float4 *__restrict__ f,
-                                                          const int *__restrict__ cell_start, int nc, float cs, int M,
-                                                          float h, float invh, float inv2s2, float norm,
-                                                          float *__restrict__ grid) {
+__global__ __launch_bounds__(256 * NW) __attribute__((amdgpu_waves_per_eu(NW == 1 ? 5 : 8))) void k_spread_mfma(
+    const float4 *__restrict__ pos, const float4 *__restrict__ f, const int *__restrict__ cell_start, int nc, float cs,
+    int M, float h, float invh, float inv2s2, float norm, float *__restrict__ grid) {
   const int lin = xcd_block(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z),
                             gridDim.x * gridDim.y * gridDim.z);
   spread_mfma_block<P, NW>(pos, f, cell_start, nc, cs, M, h, invh, inv2s2, norm, grid, lin, gridDim.x, gridDim.y);
@@ -1243,11 +1281,14 @@ static bool spread_mfma_valid(int M, int P, int nw) {
   return nw <= 4 && M % 16 == 0 && M % tz == 0 && M >= 2 * tmax + P;
 }
 
-// Built-in tile depth (8 nw): the matrix-core form is fastest with the
-// smallest tiles (16 x 8 x 8, measured at 256^3 to 512^3); the VALU tiles
-// with 8 x 8 x 32 from 128^3 up (measured best at 256^3 against depths 16
-// and 64).
+// Built-in tile depth (8 nw).  The matrix-core form: depth 16 where its tiles
+// fill the compute units (from 128^3: 1024 tiles), as it lists and weighs a
+// particle for fewer tiles (10^6 particles, 256^3: 305 us against 382 at depth
+// 8 and 386 at depth 32; 2 10^5, 128^3: 85 us against 98); depth 8 on smaller
+// grids (8000 particles, 64^3: 12 us against 16).  The VALU tiles: 8 x 8 x 32
+// from 128^3 up (measured best at 256^3 against depths 16 and 64).
 int spread_default_nw(int M, int P, bool fp32) {
+  if (fp32 && M >= 128 && spread_mfma_valid(M, P, 2)) return 2;
   if (fp32 && spread_mfma_valid(M, P, 1)) return 1;
   int nw = M >= 128 ? 4 : (M >= 64 ? 2 : 1);
   while (nw > 1 && !spread_nw_valid(M, P, nw)) nw >>= 1;
