@@ -7,6 +7,7 @@
 #include <unordered_set>
 
 #include "launch.hpp"
+#include "philox.hpp"
 
 namespace pse {
 
@@ -2055,23 +2056,6 @@ __global__ __launch_bounds__(256) void k_finalize_krylov(const int *__restrict__
 }
 
 // ------------------------------------------------ Philox noise for z1
-__device__ __forceinline__ void philox4x64_10(uint64_t c[4], uint64_t k0, uint64_t k1) {
-#pragma unroll
-  for (int r = 0; r < 10; ++r) {
-    if (r) {
-      k0 += 0x9E3779B97F4A7C15ull;
-      k1 += 0xBB67AE8584CAA73Bull;
-    }
-    const uint64_t lo0 = 0xD2E7470EE14C6C93ull * c[0], hi0 = __umul64hi(0xD2E7470EE14C6C93ull, c[0]);
-    const uint64_t lo1 = 0xCA5A826395121157ull * c[2], hi1 = __umul64hi(0xCA5A826395121157ull, c[2]);
-    const uint64_t n0 = hi1 ^ c[1] ^ k0, n2 = hi0 ^ c[3] ^ k1;
-    c[0] = n0;
-    c[1] = lo1;
-    c[2] = n2;
-    c[3] = lo0;
-  }
-}
-
 template <typename T> __device__ __forceinline__ void box_muller(uint64_t wa, uint64_t wb, T &na, T &nb);
 template <> __device__ __forceinline__ void box_muller<double>(uint64_t wa, uint64_t wb, double &na, double &nb) {
   const double ua = ((double)(wa >> 11) + 0.5) * 0x1.0p-53;
