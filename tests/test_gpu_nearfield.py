@@ -11,7 +11,7 @@ import torch
 
 import synth
 from oracle import rpy
-from parity import FP32_NEAR_BAR_DENSE, check
+from parity import FP32_NEAR_BAR_DENSE, check, cutoff_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -90,4 +90,26 @@ def test_list_counts(gpu_lib, n, L, spread, krep):
     assert st.lds_block_edge > 0
     assert lo.sum() <= st.neighbor_pairs <= hi.sum()
     assert lo.sum(1).max() <= st.max_neighbors <= hi.sum(1).max()
+    s.close()
+
+
+@pytest.mark.parametrize("corner", [0.0, 1.0])
+def test_largest_halo_in_first_or_last_block(gpu_lib, corner):
+    """The halo capacity is the largest over all blocks: a cluster in the
+    first or in the last of 2197 blocks of a nearly empty box (more blocks
+    than the wavefronts that walk them), rows of M_r v against brute force."""
+    rc, L, xi = 4.0, 209.0, 0.56
+    g = np.arange(7) * 2.05
+    c = np.stack(np.meshgrid(g, g, g, indexing="ij"), -1).reshape(-1, 3)
+    c = 0.5 + c if corner == 0.0 else L - 0.5 - c
+    rest = np.random.default_rng(3300).uniform(0.2 * L, 0.8 * L, (40, 3))
+    x = np.concatenate([rest, c])
+    n = len(x)
+    s = gpu_lib.Sampler(n, L, xi=xi, rcut=rc, grid=256, support=8, tol=1e-6, precision="fp32")
+    s.set_positions(dev(x, s))
+    v = synth.normals(3301, (n, 3))
+    w = s.real_matvec(dev(v, s)).double().cpu().numpy()
+    rows = np.arange(n)
+    check(w, rpy.real_matvec_rows(x, v, rows, L, 1.0, 1.0, xi, rc), FP32_NEAR_BAR_DENSE, f"corner {corner}",
+          skip_rows=cutoff_rows(x, L, rc, rows))
     s.close()
