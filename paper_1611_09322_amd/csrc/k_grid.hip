@@ -1273,7 +1273,7 @@ static bool spread_mfma_valid(int M, int P, int nw) {
 // Built-in tile depth (8 nw).  The matrix-core form: depth 16 where its tiles
 // fill the compute units (from 128^3: 1024 tiles), as it lists and weighs a
 // particle for fewer tiles (10^6 particles, 256^3: 305 us against 382 at depth
-// 8 and 386 at depth 32; 2 10^5, 128^3: 85 us against 98); depth 8 on smaller
+// 8 and 386 at depth 32; 2 10^5, 192^3: 85 us against 98); depth 8 on smaller
 // grids (8000 particles, 64^3: 12 us against 16).  The VALU tiles: 8 x 8 x 32
 // from 128^3 up (measured best at 256^3 against depths 16 and 64).
 int spread_default_nw(int M, int P, bool fp32) {
