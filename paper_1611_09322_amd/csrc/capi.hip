@@ -437,7 +437,14 @@ pse_status set_positions_impl(pse_ctx *c, const void *pos) {
   // the previous choice; blocks of more cells keep enough targets per
   // workgroup when cells hold few particles.  Without such a B, the largest
   // whose halo fits the budget of one workgroup.
+  // The list is first built at the last edge, with room for a halo an eighth
+  // larger than the last largest one, before the halo sizes are read back: one
+  // wait less per call (a step of 1000 spheres 220 -> 188 us, of 64007
+  // 444 -> 420 us).  If the sizes read then would have led to another edge or
+  // do not fit, the search and the build are run as for a first configuration.
   c->lds_B = 0;
+  bool built = false;
+  pse_status st = PSE_OK;
   if (sizeof(T) == 4) {
     auto lds_bytes = [](int hmax) {
       // one halo slot more: the zero source read by padding entries
@@ -455,7 +462,32 @@ pse_status set_positions_impl(pse_ctx *c, const void *pos) {
       return PSE_OK;
     };
     const int start = c->lds_B_pref ? c->lds_B_pref : 4;
-    int pick = 0;
+    auto room2 = [](int B) { return kLdsPerCU / 2 - lds_static_extra(B); };  // two workgroups per CU
+    auto use = [&](int B, int hcap) {
+      c->lds_B = B;
+      c->hcap = hcap;
+      const int nb = (c->d.nc + B - 1) / B;
+      c->lds_blocks = nb * nb * nb;
+    };
+    if (c->halo_last) {
+      int room = c->halo_last + c->halo_last / 8 + 16;
+      while (room > c->halo_last && lds_bytes(room) > room2(start)) --room;
+      launch_halo_size(c, start);
+      use(start, room + 1);
+      st = build_neighbors<T>(c);
+      if (st != PSE_OK) return st;
+      if (c->flags_h[0]) return PSE_ERR_NONFINITE;
+      hm[start] = c->flags_h[4];
+      if (hm[start] <= room && lds_bytes(hm[start]) <= room2(start)) {
+        use(start, hm[start] + 1);
+        c->halo_last = hm[start];
+        built = true;
+      } else {
+        c->lds_B = 0;
+        if (hipMemsetAsync(c->flags, 0, sizeof(int) * 8, c->stream) != hipSuccess) return PSE_ERR_HIP;
+      }
+    }
+    int pick = built ? start : 0;
     // B >= 2 with two workgroups per CU, then B >= 2 with one, then B = 1
     for (int pass = 0; pass < 3 && !pick; ++pass) {
       for (int B = pass < 2 ? start : 1; B >= (pass < 2 ? 2 : 1) && !pick; --B) {
@@ -464,18 +496,20 @@ pse_status set_positions_impl(pse_ctx *c, const void *pos) {
           const pse_status hs = halo_max(B);
           if (hs != PSE_OK) return hs;
         }
-        const size_t lim = pass == 0 ? kLdsPerCU / 2 - lds_static_extra(B) : kLdsBudget;
-        if (hm[B] <= 65535 && lds_bytes(hm[B]) <= lim) pick = B;
+        const size_t lim = pass == 0 ? room2(B) : kLdsBudget;
+        if (hm[B] <= 65535 && lds_bytes(hm[B]) <= lim) {
+          pick = B;
+          c->halo_last = pass == 0 ? hm[B] : 0;
+        }
       }
     }
-    if (pick) {
-      c->lds_B = c->lds_B_pref = pick;
-      c->hcap = hm[pick] + 1;
-      const int nb = (c->d.nc + pick - 1) / pick;
-      c->lds_blocks = nb * nb * nb;
+    if (pick && !built) {
+      c->lds_B_pref = pick;
+      use(pick, hm[pick] + 1);
     }
+    if (!pick) c->halo_last = 0;
   }
-  pse_status st = build_neighbors<T>(c);
+  if (!built) st = build_neighbors<T>(c);
   if (st != PSE_OK) return st;
   if (c->flags_h[0]) return PSE_ERR_NONFINITE;
   if (c->flags_h[1] > c->nbr_cap) {

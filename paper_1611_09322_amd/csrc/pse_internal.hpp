@@ -381,6 +381,7 @@ struct pse_ctx {
   int tune_spmv_lanes = 0;
   int lds_B = 0;
   int lds_B_pref = 0;  // block edge of the last configuration (the search starts there)
+  int halo_last = 0;   // its largest halo, if that edge left room for two workgroups per CU; else 0
   int hcap = 0;
   int lds_blocks = 0;
   // learned block preconditioner (params.precond == 1); pc_suspend is set

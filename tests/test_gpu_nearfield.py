@@ -113,3 +113,35 @@ def test_largest_halo_in_first_or_last_block(gpu_lib, corner):
     check(w, rpy.real_matvec_rows(x, v, rows, L, 1.0, 1.0, xi, rc), FP32_NEAR_BAR_DENSE, f"corner {corner}",
           skip_rows=cutoff_rows(x, L, rc, rows))
     s.close()
+
+
+def test_list_follows_changing_halos(gpu_lib):
+    """One sampler given positions whose largest halo stays, grows past the
+    room kept for it (a quarter of the spheres drawn together), shrinks again
+    and, in between, holds a position that is not finite: rows of M_r v
+    against brute force each time, the refusal as such, and the first
+    positions' product reproduced bit for bit."""
+    n, rc, L, xi = 3000, 4.6, 46.5, 0.7
+    x0 = synth.uniform_positions(n, L, seed=3400)
+    x1 = x0 + 0.3 * synth.normals(3401, (n, 3))
+    x2 = x0.copy()
+    x2[: n // 4] *= 0.25
+    s = gpu_lib.Sampler(n, L, xi=xi, rcut=rc, grid=64, support=6, tol=1e-6, precision="fp32")
+    v = synth.normals(3402, (n, 3))
+    rows = np.arange(0, n, 7)
+    first = None
+    for k, x in enumerate([x0, x1, x2, None, x2, x0, x0]):
+        if x is None:
+            bad = x0.copy()
+            bad[5, 1] = np.nan
+            with pytest.raises(gpu_lib.PSEError):
+                s.set_positions(dev(bad, s))
+            continue
+        s.set_positions(dev(x, s))
+        w = s.real_matvec(dev(v, s)).double().cpu().numpy()
+        check(w[rows], rpy.real_matvec_rows(x, v, rows, L, 1.0, 1.0, xi, rc), FP32_NEAR_BAR_DENSE, f"positions {k}",
+              skip_rows=cutoff_rows(x, L, rc, rows))
+        if k == 5:
+            first = w
+    assert np.array_equal(w, first)
+    s.close()
