@@ -287,7 +287,9 @@ pse_status pse_sample_with_noise(pse_ctx *ctx, const void *z1_dev, const void *W
  * the noise as pse_sample does (key seed, counter step).  F_ext: forces_dev
  * (n x 3) or NULL.  F_rep: the overlap repulsion of near-hard spheres,
  *   F_rep,i = sum_{j: r_ij < 2a} krep (2a - r_ij) (x_i - x_j) / r_ij,
- * accumulated by the neighbour-list scan itself (krep = 0: none).  The
+ * accumulated by the neighbour-list scan itself (krep = 0: none), which looks
+ * at the cells of side >= rcut around a sphere's own: with rcut < 2a it sees
+ * every such pair where box / cells >= 2a (pse_derived.cells).  The
  * deterministic and stochastic wave terms share one FFT pair (Sec. III).
  * disp_dev (n x 3) receives the displacement, or NULL.  Synchronises as
  * pse_set_positions and pse_sample do.

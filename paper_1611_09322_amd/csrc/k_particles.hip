@@ -891,7 +891,10 @@ __global__ __launch_bounds__(kHaloNT) void k_halo_size(const int *__restrict__ c
 // flags[1]: list capacity needed; flags[5]: largest count.  With REP the
 // overlap repulsion of each target,
 //   f_s = sum_{t: r < 2a} krep (2a - r) d / r,  d = x_s - x_t,
-// is accumulated from its hits into frep[s].
+// is accumulated into frep[s]: from its hits (kRepHits) where rc >= 2a, as in
+// every chosen parameter set; else (kRepAll) from all candidates in the cells
+// around its own, as in the global list.
+enum Rep { kRepNone, kRepHits, kRepAll };
 constexpr int kNbrNT = 768, kNbrWaves = kNbrNT / 64;
 constexpr int kNbrPad = 16;    // halo records read past the last one
 constexpr int kNbrRound = 48;  // hits of one word a target may stage
@@ -905,7 +908,7 @@ __device__ __forceinline__ void lds_order() {
 }
 
 // part of `parts`: workgroups that share the block's tiles (small systems)
-template <int B, bool REP>
+template <int B, Rep REP>
 __device__ __forceinline__ void nbr_lds_block(const float4 *__restrict__ pos, const int *__restrict__ cell_start,
                                               int nc, float cs, int n, float L, float rc, float rc2,
                                               uint16_t *__restrict__ nbr, int *__restrict__ cnt_out, int cap,
@@ -973,22 +976,23 @@ __device__ __forceinline__ void nbr_lds_block(const float4 *__restrict__ pos, co
     const float far = 2.0f * sqrtf(p2) + rc, margin = 8.5e-7f * far * far;  // 14 u (2 |p| + rc)^2
     float fx = 0.f, fy = 0.f, fz = 0.f;  // overlap repulsion (REP)
     int have = 0, chunks = 0;            // staged entries, chunks written (of the lane's target)
+    auto repel = [&](int j) {
+      const float dx = px - hal[j], dy = py - hal[hs + j], dz = pz - hal[2 * hs + j];
+      const float r2 = dx * dx + dy * dy + dz * dz;
+      if (r2 < contact * contact && r2 > 0.f) {
+        const float r = sqrtf(r2), f = krep * (contact - r) / r;
+        fx += f * dx;
+        fy += f * dy;
+        fz += f * dz;
+      }
+    };
     // the hits of a word, whose bit b is candidate jl + b, to the stage
     auto extract = [&](uint32_t w, int jl, uint16_t *at) {
       while (w) {
         const int j = jl + __builtin_ctz(w);
         w &= w - 1u;
         *at++ = (uint16_t)j;
-        if (REP) {
-          const float dx = px - hal[j], dy = py - hal[hs + j], dz = pz - hal[2 * hs + j];
-          const float r2 = dx * dx + dy * dy + dz * dz;
-          if (r2 < contact * contact && r2 > 0.f) {
-            const float r = sqrtf(r2), f = krep * (contact - r) / r;
-            fx += f * dx;
-            fy += f * dy;
-            fz += f * dz;
-          }
-        }
+        if (REP == kRepHits) repel(j);
       }
     };
     // this lane's place in the stage for its m hits; the target's total
@@ -1049,6 +1053,10 @@ __device__ __forceinline__ void nbr_lds_block(const float4 *__restrict__ pos, co
         }
         w &= valid >= 32 ? 0xffffffffu : (1u << valid) - 1u;
         if (d == 4 && (unsigned)(li - jl) < 32u) w &= ~(1u << (li - jl));  // not itself
+        if (REP == kRepAll) {
+          const int jhi = min(jl + valid, cbase[cc + oz + 3]);
+          for (int j = max(jl, cbase[cc + oz]); j < jhi; ++j) repel(j);
+        }
         int total;
         const int off = place(__popc(w), total);
         if (__any(have + total > kNbrStage - 1)) flush();  // leaves at most 7
@@ -1097,7 +1105,7 @@ __device__ __forceinline__ void nbr_lds_block(const float4 *__restrict__ pos, co
   nbr_stats(mine, mx, flags);
 }
 
-template <int B, bool REP>
+template <int B, Rep REP>
 __global__ __launch_bounds__(kNbrNT) __attribute__((amdgpu_waves_per_eu(REP ? 4 : 6))) void k_nbr_lds(const float4 *__restrict__ pos, const int *__restrict__ cell_start,
                                                     int nc, float cs, int n, float L, float rc, float rc2,
                                                     uint16_t *__restrict__ nbr, int *__restrict__ cnt_out, int cap,
@@ -1115,7 +1123,7 @@ __global__ __launch_bounds__(kNbrNT) __attribute__((amdgpu_waves_per_eu(6))) voi
                                                           const int2 *__restrict__ pmap) {
   const int2 rb = pmap[blockIdx.x];
   const NbrRep &r = reps[rb.x];
-  nbr_lds_block<B, false>(r.pos, r.cell_start, r.nc, r.cs, r.n, r.L, r.rc, r.rc2, r.nbr, r.cnt, r.cap, r.flags, 0.0f,
+  nbr_lds_block<B, kRepNone>(r.pos, r.cell_start, r.nc, r.cs, r.n, r.L, r.rc, r.rc2, r.nbr, r.cnt, r.cap, r.flags, 0.0f,
                           0.0f, nullptr, r.hcap, rb.y, 0, 1);
 }
 
@@ -2271,10 +2279,11 @@ void launch_nbr_lds(pse_ctx *c) {
         (const float4 *)c->pos_s, c->cell_start, c->d.nc, (float)c->d.cs, c->n, L, (float)c->p.rcut, rc2, nb, c->nbr_cnt,
         c->nbr_cap, c->flags, (float)(2.0 * c->p.a), (float)c->rep_k, (float4 *)c->vbuf[kRepBuf], c->hcap, parts);
   };
-  const bool rep = c->rep_k > 0;
   with_block_edge(c->lds_B, [&](auto b) {
     constexpr int BE = decltype(b)::value;
-    rep ? go(k_nbr_lds<BE, true>) : go(k_nbr_lds<BE, false>);
+    if (!(c->rep_k > 0)) go(k_nbr_lds<BE, kRepNone>);
+    else if (c->p.rcut >= 2.0 * c->p.a) go(k_nbr_lds<BE, kRepHits>);
+    else go(k_nbr_lds<BE, kRepAll>);
   });
 }
 

@@ -122,3 +122,36 @@ def test_short_run_keeps_spheres_apart(gpu_lib):
         assert moved > 0.05
     assert dmin[5000.0] > 1.8
     assert dmin[0.0] < dmin[5000.0] - 0.2
+
+
+@pytest.mark.parametrize("precond", [0, 1])
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "mixed"])
+def test_repulsion_beyond_the_cutoff(gpu_lib, precision, precond):
+    """A cutoff below contact (rc = 1.9a): the repulsion covers every pair with
+    r < 2a, also those outside the near-field list, in every list form (cells
+    of side 2.03a).  Overlaps beyond the cutoff are 0.03a on average; FP32
+    coordinates of size L = 20a round to 2e-6a (1e-4 of an overlap, well
+    inside the bar of the LDS path's test), FP64 ones to 4e-15a."""
+    import torch
+
+    x, L = synth.hard_spheres(600, 0.3, seed=1900, sweeps=20)
+    rc, krep, dt = 1.9, 2.0, 0.05
+    assert L / int(L / rc) >= 2.0
+    x = 0.97 * x  # in the same box: contacts move to 1.94a and more
+    x[1] = x[0] + [1.2, 0.3, -0.4]  # and some within the cutoff
+    x[3] = x[2] + [0.0, 1.85, 0.0]
+    F, near = rep_force(x, L, 1.0, krep), rep_force(x, L, 0.5 * rc, krep)
+    touched = [int(np.count_nonzero(np.linalg.norm(f, axis=1))) for f in (F, near)]
+    print(f"overlapping spheres: {touched[0]}, within the cutoff: {touched[1]}", flush=True)
+    assert touched[0] > 100 and touched[1] >= 4
+    s = gpu_lib.Sampler(len(x), L, xi=0.7, rcut=rc, grid=64, support=6, tol=1e-6, kT=0.0, precision=precision,
+                        precond=precond)
+    pos = torch.as_tensor(x, dtype=s.dtype, device="cuda")
+    disp = torch.empty_like(pos)
+    st = s.bd_step(pos, 2, 0, dt, krep=krep, disp=disp)
+    assert (st.lds_block_edge > 0) == (precision != "fp64")
+    ref = s.mobility_apply(torch.as_tensor(F, dtype=s.dtype, device="cuda")) * dt
+    torch.cuda.synchronize()
+    check(disp.double().cpu().numpy(), ref.double().cpu().numpy(), 1e-11 if precision == "fp64" else 1e-3,
+          f"repulsion beyond the cutoff, {precision}, precond {precond}")
+    s.close()
