@@ -101,26 +101,36 @@ int nbr_capacity(const pse_ctx *c) {
   return (cap + 7) & ~7;
 }
 
-// The list (and FP64 pair coefficients) at a capacity.  Products fall back to
-// evaluating the coefficients where they find no memory.
+// The list at a capacity; the FP64 pair coefficients go with it (take_coef
+// brings them back).
 bool alloc_list(pse_ctx *c, int cap) {
   if (c->nbr) (void)hipFree(c->nbr);
   if (c->nbr_coef) (void)hipFree(c->nbr_coef);
   c->nbr = nullptr;
   c->nbr_coef = nullptr;
   c->nbr_cap = 0;
-  const size_t slots = (size_t)cap * c->n;
-  if (hipMalloc((void **)&c->nbr, sizeof(int) * slots) != hipSuccess) {
+  if (hipMalloc((void **)&c->nbr, sizeof(int) * (size_t)cap * c->n) != hipSuccess) {
     c->nbr = nullptr;
     (void)hipGetLastError();
     return false;
   }
   c->nbr_cap = cap;
-  if (c->dbl && hipMalloc((void **)&c->nbr_coef, sizeof(double2) * slots) != hipSuccess) {
-    c->nbr_coef = nullptr;
-    (void)hipGetLastError();
-  }
   return true;
+}
+
+// The FP64 pair coefficients, four times the list: optional, as products
+// without them evaluate the closed forms.  Taken after everything a context
+// needs, and only up to half of the memory then free, so that what is allocated
+// later still finds room.
+void take_coef(pse_ctx *c) {
+  if (!c->dbl) return;
+  const size_t bytes = sizeof(double2) * (size_t)c->nbr_cap * c->n;
+  size_t avail = 0, total = 0;
+  if (hipMemGetInfo(&avail, &total) == hipSuccess && bytes <= avail / 2 &&
+      hipMalloc((void **)&c->nbr_coef, bytes) == hipSuccess)
+    return;
+  c->nbr_coef = nullptr;
+  (void)hipGetLastError();
 }
 
 WaveCoef wave_coef(const pse_ctx *c, double det_scale, double sto_scale, uint64_t seed, uint64_t counter) {
@@ -516,6 +526,7 @@ pse_status set_positions_impl(pse_ctx *c, const void *pos) {
     const int cap = (c->flags_h[1] + 32 + 7) & ~7;
     c->graph_stale = true;  // a captured graph holds the old list
     if (!alloc_list(c, cap)) return PSE_ERR_OOM;
+    take_coef(c);
     if (hipMemsetAsync(c->flags, 0, sizeof(int) * 8, c->stream) != hipSuccess) return PSE_ERR_HIP;
     st = build_neighbors<T>(c);
     if (st != PSE_OK) return st;
@@ -899,7 +910,8 @@ const char *pse_status_string(pse_status s) {
   return "unknown status";
 }
 
-pse_status pse_create(const pse_params *p, void *stream, pse_ctx **out) {
+// pse_create without the optional buffers.
+static pse_status create_ctx(const pse_params *p, void *stream, pse_ctx **out) {
   if (!p || !out) return PSE_ERR_INVALID_ARG;
   *out = nullptr;
   Derived d;
@@ -995,6 +1007,12 @@ pse_status pse_create(const pse_params *p, void *stream, pse_ctx **out) {
   }
   *out = c;
   return PSE_OK;
+}
+
+pse_status pse_create(const pse_params *p, void *stream, pse_ctx **out) {
+  const pse_status st = create_ctx(p, stream, out);
+  if (st == PSE_OK) take_coef(*out);
+  return st;
 }
 
 pse_status pse_destroy(pse_ctx *ctx) {
@@ -1178,13 +1196,14 @@ pse_status pse_batch_create(const pse_params *p, int32_t n_rep, void *stream, ps
   }
   for (int r = 0; r < n_rep; ++r) {
     pse_ctx *c = nullptr;
-    const pse_status st = pse_create(&p[r], b->streams[r % S], &c);
+    const pse_status st = create_ctx(&p[r], b->streams[r % S], &c);
     if (st != PSE_OK) {
       free_batch(b);
       return st;
     }
     b->ctx.push_back(c);
   }
+  for (pse_ctx *c : b->ctx) take_coef(c);
   *out = b;
   return PSE_OK;
 }
@@ -1685,6 +1704,7 @@ static pse_status batch_capture(pse_batch *b) {
     if (cap > c->nbr_cap) {
       if (hipStreamSynchronize(c->stream) != hipSuccess) return PSE_ERR_HIP;
       if (!alloc_list(c, cap)) return PSE_ERR_OOM;
+      take_coef(c);
     }
     int it = (c->last_iters < 2 ? 2 : c->last_iters) + b->g_extra;
     c->graph_iters = it > c->lz_maxit ? c->lz_maxit : it;
