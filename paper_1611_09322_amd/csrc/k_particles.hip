@@ -1534,7 +1534,9 @@ __device__ __forceinline__ bool tridiag_root_quadrature(int n, double d, double 
     if (i > 1) x *= -lane_value(e, i - 1) * X[i * 64 + lane];
     X[i * 64 + lane] = x;
   }
-  // lane k sums row k over the nodes (rotated columns: no bank conflicts)
+  // lane k sums row k over the nodes (rotated columns: no bank conflicts); the
+  // columns are the other lanes'
+  lds_order();
   double a[4] = {0.0, 0.0, 0.0, 0.0};
   if (lane < n) {
     for (int j = 0; j < 64; j += 4)
@@ -1624,7 +1626,7 @@ __device__ double tridiag_root_ql(int n, double d, double e, double *Q, int &ok)
     }
     if (!ok) break;
   }
-  __builtin_amdgcn_wave_barrier();
+  lds_order();  // row 0 is lane 0's
   const double root = sqrt(d > 0.0 ? d : 0.0);
   double acc = 0;
   for (int j = 0; j < n; ++j) acc += Q[j * 64 + lane] * lane_value(root, j) * Q[j * 64];
