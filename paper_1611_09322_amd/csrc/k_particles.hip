@@ -1492,41 +1492,39 @@ __device__ __forceinline__ double rcp_newton(double x) {
 }
 
 // s = T^{1/2} e_1 for the n x n tridiagonal T (lane j holds the diagonal d[j]
-// and e[j], which couples j and j + 1), by the quadrature
+// and e[j], which couples j and j + 1), Gershgorin bound in (1/4, 1], by the
+// quadrature
 //   lambda^{1/2} = sum_j w_j lambda / (lambda + t_j),   lambda in [1e-13, 1]
 // (lz_quadrature; relative error 2e-15 there): lane j solves
-// (T + t_j) x_j = T e_1 and s = sum_j w_j x_j.  T is scaled by an even power of
-// two so that its Gershgorin bound lies in (1/4, 1].  Eliminating from the last
+// (T + t_j) x_j = T e_1 and s = sum_j w_j x_j.  Eliminating from the last
 // row up leaves one stored factor per row: with pivots D_i, r_i = 1 / D_i,
 //   x_0 = (D_0 - t) r_0,  x_1 = e_0 t r_0 r_1,  x_i = -e_{i-1} r_i x_{i-1}.
 // A step of the elimination is one reciprocal and two FMAs for all nodes at
 // once: about a microsecond at five rows, where the eigen-decomposition's
-// chain of rotations took 10 (22 at eight rows).  False when some pivot
-// is not positive (T indefinite to rounding, or not finite): the
-// caller then takes the eigen-decomposition, which clamps.  X: 64 n values.
+// chain of rotations took 10 (22 at eight rows).  False when some eigenvalue
+// is below the range (T nearly singular or indefinite; between -t_j and 0 the
+// sum has poles), or T is not finite: the caller then takes the
+// eigen-decomposition, which clamps.  The test is on the trailing minors p of
+// T - 1e-13, two FMAs a row beside the elimination; a minor that underflows
+// counts as not positive.  X: 64 n values.
 __device__ __forceinline__ bool tridiag_root_quadrature(int n, double d, double e, const double2 *__restrict__ nodes,
                                                         double *X, double &s) {
   const int lane = threadIdx.x & 63;
   const double2 tw = nodes[lane];
-  const double el = __shfl_up(e, 1, 64), g = fabs(d) + fabs(e) + (lane ? fabs(el) : 0.0);
-  double bound = 0.0;
-  for (int j = 0; j < n; ++j) bound = fmax(bound, lane_value(g, j));
-  if (!(bound > 0.0) || !isfinite(bound)) return false;
-  int ex = ilogb(bound) + 1;
-  ex += ex & 1;
-  d = ldexp(d, -ex);
-  e = ldexp(e, -ex);
   double D = lane_value(d, n - 1), r = 0.0;
-  bool pos = true;
+  double p = D - kRootLow, p1 = 1.0;  // minors of the rows from i on and from i + 1 on
+  bool pos = p > 0.0;
   for (int i = n - 1; i > 0; --i) {
-    const double Dt = D + tw.x, ei = lane_value(e, i - 1);
-    pos = pos && Dt > 0.0;
-    r = rcp_newton(Dt);
+    const double ei = lane_value(e, i - 1), di = lane_value(d, i - 1), e2 = ei * ei;
+    r = rcp_newton(D + tw.x);
     X[i * 64 + lane] = r;
-    D = fma(-ei * ei, r, lane_value(d, i - 1));
+    D = fma(-e2, r, di);
+    const double p0 = fma(di - kRootLow, p, -e2 * p1);
+    p1 = p;
+    p = p0;
+    pos = pos && p > 0.0;
   }
-  pos = pos && D + tw.x > 0.0;
-  if (!__all(pos)) return false;
+  if (!pos) return false;  // (the same in every lane)
   const double r0 = rcp_newton(D + tw.x);
   X[lane] = tw.y * D * r0;
   double x = lane_value(e, 0) * (tw.y * tw.x * r0) * r;  // r = r_1 here
@@ -1543,30 +1541,25 @@ __device__ __forceinline__ bool tridiag_root_quadrature(int n, double d, double 
 #pragma unroll
       for (int u = 0; u < 4; ++u) a[u] += X[lane * 64 + ((j + u + lane) & 63)];
   }
-  s = ldexp((a[0] + a[1]) + (a[2] + a[3]), ex / 2);
+  s = (a[0] + a[1]) + (a[2] + a[3]);
   return true;
 }
 
-// The same by implicit QL with Wilkinson-type shifts, negative eigenvalues
-// taken as 0.  Lane k owns row k of the eigenvector matrix Q (stored
-// column-major in LDS).  Returns s_k in lane k.
-// double serial chain of rotations bounds it, so each rotation is kept short:
+// The same by implicit QL with Wilkinson-type shifts (A. Dubrulle, R. S. Martin
+// and J. H. Wilkinson, "The implicit QL algorithm", Numer. Math. 12, 1968),
+// negative eigenvalues taken as 0.  Lane k owns row k of the eigenvector
+// matrix Q (stored column-major in LDS).  Returns s_k in lane k.
+// A serial chain of rotations bounds it, so each rotation is kept short:
 // uniform values are read from their lane as scalars instead of through LDS
 // permutes, one reciprocal square root gives r, 1/r and with them the sine
 // and cosine (no hypot, no divisions), the deflation test looks at every
 // lane at once, and the updated column of Q stays in a register for the
-// next rotation.  T is scaled by a power of two to diagonal entries of order
-// 1, which keeps f^2 + g^2 in range.
+// next rotation.  Entries of order 1 keep f^2 + g^2 in range.
 __device__ double tridiag_root_ql(int n, double d, double e, double *Q, int &ok) {
   const int lane = threadIdx.x & 63;
   const double eps = 2.2e-16, tiny = 1e-290;
   for (int j = 0; j < n; ++j) Q[j * 64 + lane] = (lane == j) ? 1.0 : 0.0;
   ok = 1;
-  const double d0 = lane_value(d, 0);
-  int ex = d0 > 0.0 && isfinite(d0) ? ilogb(d0) : 0;
-  ex -= ex & 1;  // even: the square root's scale is a power of two too
-  d = ldexp(d, -ex);
-  e = ldexp(e, -ex);
   for (int l = 0; l < n; ++l) {
     int iter = 0;
     while (true) {
@@ -1627,10 +1620,31 @@ __device__ double tridiag_root_ql(int n, double d, double e, double *Q, int &ok)
     if (!ok) break;
   }
   lds_order();  // row 0 is lane 0's
-  const double root = sqrt(d > 0.0 ? d : 0.0);
+  const double root = sqrt(d < 0.0 ? 0.0 : d);  // (NaN stays)
   double acc = 0;
   for (int j = 0; j < n; ++j) acc += Q[j * 64 + lane] * lane_value(root, j) * Q[j * 64];
-  return ldexp(acc, ex / 2);
+  return acc;
+}
+
+// s = T^{1/2} e_1 by the quadrature, or by QL outside its range, at n = 1
+// (where QL is one square root) and with force_ql, on T scaled by an even power of two, so that the root's scale is
+// a power of two too.  True if by the quadrature; ok = 0 if neither.
+__device__ __forceinline__ bool tridiag_root(int n, double d, double e, const double2 *__restrict__ nodes, double *X,
+                                             bool force_ql, double &s, int &ok) {
+  const int lane = threadIdx.x & 63;
+  const double el = __shfl_up(e, 1, 64), g = fabs(d) + fabs(e) + (lane ? fabs(el) : 0.0);
+  double bound = 0.0;  // Gershgorin
+  for (int j = 0; j < n; ++j) bound = fmax(bound, lane_value(g, j));
+  const bool scaled = bound > 0.0 && isfinite(bound);
+  int ex = scaled ? ilogb(bound) + 1 : 0;
+  ex += ex & 1;
+  d = ldexp(d, -ex);
+  e = ldexp(e, -ex);
+  ok = 1;
+  const bool quad = scaled && n > 1 && !force_ql && tridiag_root_quadrature(n, d, e, nodes, X, s);
+  if (!quad) s = tridiag_root_ql(n, d, e, X, ok);
+  s = ldexp(s, ex / 2);
+  return quad;
 }
 
 // After iteration m: beta_{m+1} (from the partial sums of |u_{m+1}|^2, or set
@@ -1664,9 +1678,9 @@ __device__ __forceinline__ void lz_check_body(const A *__restrict__ partials, in
   const int nn = m + 1;
   const double d = lane < nn ? (double)st->alpha[lane] : 0.0;
   const double e = lane < nn - 1 ? (double)st->beta[lane + 1] : 0.0;
-  int ok = 1;
-  double sk = 0.0;
-  if (!tridiag_root_quadrature(nn, d, e, nodes, Q, sk)) sk = tridiag_root_ql(nn, d, e, Q, ok);
+  int ok;
+  double sk;
+  tridiag_root(nn, d, e, nodes, Q, false, sk, ok);
   const double sold = lane < m ? (double)st->s[lane] : 0.0;
   const double dif = lane < nn ? sk - sold : 0.0;
   double num = 0.0, den = 0.0, scale2 = 0.0;
@@ -1694,6 +1708,20 @@ template <typename A>
 __global__ __launch_bounds__(64) void k_lz_check(const A *__restrict__ partials, int nparts, LzState<A> *st, int m,
                                                  A tol, int max_iter, const double2 *__restrict__ nodes) {
   lz_check_body<A>(partials, nparts, st, m, tol, max_iter, nodes);
+}
+
+// The check's root alone, for pse_internal_tridiag_root: path 1 by the
+// quadrature, 0 by QL, -1 if it found none.
+__global__ __launch_bounds__(64) void k_tridiag_root(int n, const double *__restrict__ d, const double *__restrict__ e,
+                                                     const double2 *__restrict__ nodes, bool force_ql,
+                                                     double *__restrict__ s, int *__restrict__ path) {
+  __shared__ double X[kMaxIter * 64];
+  const int lane = threadIdx.x;
+  double sk;
+  int ok;
+  const bool quad = tridiag_root(n, lane < n ? d[lane] : 0.0, lane < n - 1 ? e[lane] : 0.0, nodes, X, force_ql, sk, ok);
+  if (lane < n) s[lane] = sk;
+  if (lane == 0) *path = !ok ? -1 : (quad ? 1 : 0);
 }
 
 // Sum of nparts partial sums in a fixed order, valid in every thread of
@@ -2747,3 +2775,30 @@ INST_TA(float, double)
 INST_TA(double, double)
 
 }  // namespace pse
+
+// The square root of the Krylov check on a given matrix (host arrays d[n],
+// e[n - 1], s[n]; no part of the API): 1 by the quadrature, 0 by QL, -1 not
+// found, -2 invalid n or no device.
+extern "C" int pse_internal_tridiag_root(int force_ql, int n, const double *d, const double *e, double *s) {
+  using namespace pse;
+  if (n < 1 || n > kMaxIter) return -2;
+  struct Bufs {
+    double2 nodes[kRootNodes];
+    double d[kMaxIter], e[kMaxIter], s[kMaxIter];
+    int path;
+  } h{}, *dev = nullptr;
+  lz_quadrature(h.nodes);
+  for (int i = 0; i < n; ++i) h.d[i] = d[i];
+  for (int i = 0; i + 1 < n; ++i) h.e[i] = e[i];
+  if (hipMalloc((void **)&dev, sizeof h) != hipSuccess) return -2;
+  int path = -2;
+  if (hipMemcpy(dev, &h, sizeof h, hipMemcpyHostToDevice) == hipSuccess) {
+    k_tridiag_root<<<1, 64>>>(n, dev->d, dev->e, dev->nodes, force_ql != 0, dev->s, &dev->path);
+    if (hipMemcpy(&h, dev, sizeof h, hipMemcpyDeviceToHost) == hipSuccess) {
+      path = h.path;
+      for (int i = 0; i < n; ++i) s[i] = h.s[i];
+    }
+  }
+  (void)hipFree(dev);
+  return path;
+}

@@ -81,7 +81,7 @@ bool tridiag_sqrt_e1_host(int m, const double *dd, const double *ee, double *s) 
 // from sinh by descending Landen steps on the small modulus k (imaginary
 // argument), which loses no digits near u = K'.
 void lz_quadrature(double2 *tw) {
-  const double k2 = 1e-13, k = std::sqrt(k2), pi = 3.14159265358979323846;
+  const double k2 = kRootLow, k = std::sqrt(k2), pi = 3.14159265358979323846;
   double a = 1.0, b = k;
   for (int i = 0; i < 12; ++i) {  // arithmetic-geometric mean of 1 and k
     const double t = 0.5 * (a + b);

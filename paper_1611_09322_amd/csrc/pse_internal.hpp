@@ -296,9 +296,10 @@ bool precond_targets(const double *x, int n, double L, double a, double xi, doub
 bool fft_size_supported(int M);
 // s = T^{1/2} e_1 of an m x m symmetric tridiagonal (lanczos_host.cpp)
 bool tridiag_sqrt_e1_host(int m, const double *d, const double *e, double *s);
-// nodes of lambda^{1/2} = sum_j w_j lambda / (lambda + t_j) on [1e-13, 1]
+// nodes of lambda^{1/2} = sum_j w_j lambda / (lambda + t_j) on [kRootLow, 1]
 // (lanczos_host.cpp)
 constexpr int kRootNodes = 64;
+constexpr double kRootLow = 1e-13;
 void lz_quadrature(double2 *tw);
 
 }  // namespace pse
