@@ -1417,6 +1417,19 @@ template <typename A> __device__ __forceinline__ int lz_exponent(A alpha) {
   return e - (e & 1);
 }
 
+// FP32 sums of iteration 0 take <z, t> as 2^-k <z, t>, k the exponent of |z| = b0
+// (the later vectors are of order 1): |z|^2 mu0 may leave the range where
+// |z|^2 and mu0 are well inside.  Powers of two change no digit.
+template <typename A> __device__ __forceinline__ int lz_start_exponent(A b0) {
+  return sizeof(A) == 4 && b0 > A(0) && isfinite(b0) ? ilogb(b0) : 0;
+}
+template <typename T4, typename T> __device__ __forceinline__ T4 scaled3(T4 a, T c) {
+  a.x *= c;
+  a.y *= c;
+  a.z *= c;
+  return a;
+}
+
 // State before iteration 0 from z2 = |z|^2 (one thread).
 template <typename A> __device__ __forceinline__ void lz_begin(LzState<A> *st, A z2) {
   const A b0 = sqrt(z2);
@@ -1750,7 +1763,8 @@ __global__ __launch_bounds__(256) void k_lz_norm(const typename vec4<T>::type *_
   if (threadIdx.x == 0) partials[blockIdx.x] = v;
 }
 
-// Block partial sums of <u_m, t>.  Computed here rather than in the LDS
+// Block partial sums of <u_m, t>, in iteration 0 (z2parts: the partial sums of
+// |z|^2) scaled by 2^-k.  Computed here rather than in the LDS
 // product's epilogue: without the reduction the product needs no register
 // spills (64 VGPRs), which costs far more than this extra pass over two
 // vectors.  The workgroup past the nparts partial sums, if launched, starts
@@ -1758,12 +1772,16 @@ __global__ __launch_bounds__(256) void k_lz_norm(const typename vec4<T>::type *_
 template <typename T, typename A>
 __device__ __forceinline__ void lz_alpha_block(const typename vec4<T>::type *__restrict__ t,
                                                const typename vec4<T>::type *__restrict__ u, int n, LzState<A> *st,
-                                               bool test, A *__restrict__ apart, int blk, int nparts) {
+                                               bool test, const A *z2parts, A *__restrict__ apart, int blk,
+                                               int nparts) {
   __shared__ A sh[16];
   if (test && st->done) return;
+  T sc = T(1);
+  if (sizeof(A) == 4 && z2parts) sc = ldexp(T(1), -lz_start_exponent(sqrt(lz_parts_sum(z2parts, nparts, sh))));
   A v = 0;
 #pragma unroll 4
-  for (int i = blk * blockDim.x + threadIdx.x; i < n; i += nparts * blockDim.x) v = dot3(v, t[i], u[i]);
+  for (int i = blk * blockDim.x + threadIdx.x; i < n; i += nparts * blockDim.x)
+    v = dot3(v, t[i], sizeof(A) == 4 ? scaled3(u[i], sc) : u[i]);
   v = block_sum(v, sh);
   if (threadIdx.x == 0) apart[blk] = v;
 }
@@ -1787,7 +1805,8 @@ __global__ __launch_bounds__(256) void k_lz_alpha(const typename vec4<T>::type *
   // (beside a check, which may set `done` meanwhile, the flag is not tested:
   // the sums of a finished process are not used)
   if ((int)blockIdx.x < nparts)
-    lz_alpha_block<T, A>(t, u, n, st, (int)gridDim.x == nparts, partials + kRedBlock, blockIdx.x, nparts);
+    lz_alpha_block<T, A>(t, u, n, st, (int)gridDim.x == nparts, m == 0 ? partials : nullptr, partials + kRedBlock,
+                         blockIdx.x, nparts);
   else
     lz_side_block<A>(partials, nparts, st, m, tol, max_iter, nodes);
 }
@@ -1805,7 +1824,8 @@ __device__ __forceinline__ void lz_update_block(const typename vec4<T>::type *__
   __shared__ A sh[16];
   if (st->done) return;
   const A rs = st->rs[m];
-  const A al = lz_parts_sum(partials + kRedBlock, nparts, sh) * rs * rs;
+  const A al = lz_parts_sum(partials + kRedBlock, nparts, sh) * rs *
+               (m == 0 ? ldexp(rs, lz_start_exponent(st->beta[0])) : rs);
   if (blk == 0 && threadIdx.x == 0) st->alpha[m] = al;
   T c1, c2, c3;
   lz_coef<T, A>(st, m, al, c1, c2, c3);
@@ -1852,7 +1872,7 @@ __device__ __forceinline__ void lz_step_block(const typename vec4<T>::type *__re
   using T4 = typename vec4<T>::type;
   __shared__ A sh[16];
   __shared__ A al_s;
-  __shared__ int stop;
+  __shared__ int stop, k_s;
   if (threadIdx.x == 0) stop = 0;
   if (m > 0 && st->done) return;
   const T4 *u = V + (size_t)m * n, *uprev = m > 0 ? u - n : nullptr;
@@ -1865,14 +1885,18 @@ __device__ __forceinline__ void lz_step_block(const typename vec4<T>::type *__re
     if (threadIdx.x == 0) {
       lz_begin(st, z2);
       stop = st->done;
+      k_s = lz_start_exponent(st->beta[0]);
     }
+    if (sizeof(A) == 4) __syncthreads();
   }
+  const int k = sizeof(A) == 4 && m == 0 ? k_s : 0;
+  const T sc = ldexp(T(1), -k);
   A v = 0;
 #pragma unroll 4
-  for (int i = threadIdx.x; i < n; i += 1024) v = dot3(v, t[i], u[i]);
+  for (int i = threadIdx.x; i < n; i += 1024) v = dot3(v, t[i], sizeof(A) == 4 ? scaled3(u[i], sc) : u[i]);
   v = block_sum(v, sh);
   if (threadIdx.x == 0) {
-    const A al = v * st->rs[m] * st->rs[m];
+    const A al = v * st->rs[m] * ldexp(st->rs[m], k);
     st->alpha[m] = al;
     al_s = al;
   }
@@ -1936,7 +1960,8 @@ __global__ __launch_bounds__(256) void k_lz_alpha_batch(const LzRep<A> *__restri
   if ((int)blockIdx.x < vm.nv) {
     const int2 rb = vm.vmap[blockIdx.x];
     const LzRep<A> &r = reps[rb.x];
-    lz_alpha_block<float, A>(r.t, r.V + (size_t)m * r.n, r.n, r.st, m > 0, r.partials + kRedBlock, rb.y, lz_parts(r.n));
+    lz_alpha_block<float, A>(r.t, r.V + (size_t)m * r.n, r.n, r.st, m > 0, m == 0 ? r.partials : nullptr,
+                             r.partials + kRedBlock, rb.y, lz_parts(r.n));
   } else {
     const LzRep<A> &r = reps[vm.big[blockIdx.x - vm.nv]];
     lz_side_block<A>(r.partials, lz_parts(r.n), r.st, 0, r.tol, r.maxit, r.nodes);

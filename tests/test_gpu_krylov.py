@@ -72,3 +72,22 @@ def test_vector_work_by_size(gpu_lib, n, precision):
     check(again.double().cpu().numpy(), ref.double().cpu().numpy(), bar,
           f"root twice n={n} {precision} iters {st.lanczos_iters}")
     s.close()
+
+
+@pytest.mark.parametrize("n", [321, 4097])
+@pytest.mark.parametrize("eta,power", [(5e10, -55), (3e-11, 50)])
+def test_start_vector_of_any_magnitude(gpu_lib, eta, power, n):
+    """The FP32 sample of 2^k z is 2^k times that of z, bit for bit, wherever
+    |z|^2 is in range: scaling by powers of two is exact.  |z|^2 mu0 leaves
+    the range of FP32 here (mu0 = 1e-12 and 1.8e9)."""
+    L = (4 * np.pi * n / 0.6) ** (1 / 3)  # phi = 0.2
+    x = synth.uniform_positions(n, L, seed=6)
+    s = gpu_lib.Sampler(n, L, eta=eta, xi=0.7, rcut=4.5, grid=64, support=6, tol=1e-3, precision="fp32")
+    s.set_positions(torch.as_tensor(x, dtype=s.dtype, device="cuda"))
+    z = torch.as_tensor(synth.normals(13, (n, 3)), dtype=s.dtype, device="cuda")
+    y, st = s.real_sample(z)
+    y2, st2 = s.real_sample(z * 2.0**power)
+    print(f"n={n} eta={eta:g}: iterations {st.lanczos_iters}, of the scaled vector {st2.lanczos_iters}", flush=True)
+    assert st.converged == st2.converged == 1 and st.lanczos_iters == st2.lanczos_iters
+    assert torch.equal(y * 2.0**power, y2)
+    s.close()
