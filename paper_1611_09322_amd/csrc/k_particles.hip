@@ -554,7 +554,9 @@ __device__ __forceinline__ void pair_coef(T r2, const FG &fg, T self_r, T &Fm, T
 // FP64: both coefficients of every list entry, evaluated once per
 // configuration.  The closed forms take six transcendental functions a pair;
 // evaluated inside every product they were 112 us of the 116 us a product of
-// 1000 particles took, 7 products a sample.
+// 1000 particles took, 7 products a sample.  Positions without a product pay
+// them too (300000 particles: list 435 -> 275 us, coefficients 460 us, so
+// set_positions 506 -> 772 us, with one product 1100 -> 961 us).
 __global__ __launch_bounds__(256) void k_pair_coef(const double4 *__restrict__ pos, const int *__restrict__ nbr,
                                                    const int *__restrict__ cnt, int n, int cap, double L, double invL,
                                                    FGExact fg, double self_r, double2 *__restrict__ coef) {
@@ -687,7 +689,9 @@ __global__ __launch_bounds__(256) void k_spmv_exact(const double4 *__restrict__ 
 // they touch, and with at least 3 cells of side >= rc the other images of the
 // pair are more than rc apart.  The staged coordinates are small (a few
 // cells), so their differences keep the precision of the relative position
-// rather than of the box size.
+// rather than of the box size, except in the columns taken across a box face:
+// there the distance to the block centre, of size L, is rounded first (at most
+// L 2^-25).
 template <int B> struct Halo {
   static constexpr int HB = B + 2;
   static constexpr int NH = HB * HB * HB;  // 27, 64, 125 or 216 halo cells
@@ -1399,7 +1403,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
 // more workgroup of iteration m + 1's k_lz_alpha, and only the last
 // iteration's is a launch of its own.  Iteration m + 1 is then speculative:
 // what it writes (the next basis slot, alpha, beta) is not read once the
-// state is done.  A captured step, which queues more iterations than it
+// state is done.  A sample that needs fewer iterations than the one before pays
+// one product more for it (115 us at 10^6 spheres), any other saves a launch of
+// about 5 us an iteration.  A captured step, which queues more iterations than it
 // needs, checks before the next product instead (no speculation).
 __device__ __forceinline__ float dot3(float acc, const float4 &a, const float4 &b) {
   return acc + (a.x * b.x + a.y * b.y + a.z * b.z);

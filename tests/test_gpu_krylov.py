@@ -91,3 +91,27 @@ def test_start_vector_of_any_magnitude(gpu_lib, eta, power, n):
     assert st.converged == st2.converged == 1 and st.lanczos_iters == st2.lanczos_iters
     assert torch.equal(y * 2.0**power, y2)
     s.close()
+
+
+@pytest.mark.parametrize("precision,tol", [("mixed", 1e-5), ("fp32", 1e-5)])
+def test_vector_work_over_many_particles(gpu_lib, precision, tol):
+    """More than the 1024 workgroups of the vector kernels take at once (256
+    particles each): the root applied twice, as above, on a lattice with a
+    jitter of 0.15a that leaves spheres 2.1a apart (no nearly coincident ones,
+    whose slow modes a 2-norm rule does not bound row by row)."""
+    g = 67
+    L = 2.4 * g
+    x = 2.4 * np.stack(np.meshgrid(*[np.arange(g)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    n = len(x)
+    assert n > 1024 * 256
+    x = x + 0.15 * (2.0 * synth.uniform_positions(n, 1.0, seed=14) - 1.0)
+    s = gpu_lib.Sampler(n, L, xi=0.7, rcut=4.5, grid=192, support=6, tol=tol, precision=precision)
+    s.set_positions(torch.as_tensor(x, dtype=s.dtype, device="cuda"))
+    z = torch.as_tensor(synth.normals(15, (n, 3)), dtype=s.dtype, device="cuda")
+    y, st = s.real_sample(z)
+    assert st.converged == 1
+    again, _ = s.real_sample(y.clone())
+    ref = s.real_matvec(z)
+    check(again.double().cpu().numpy(), ref.double().cpu().numpy(), 6 * tol + 2 * FP32_NEAR_BAR_DENSE,
+          f"root twice n={n} {precision} iters {st.lanczos_iters}")
+    s.close()
